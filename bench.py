@@ -69,7 +69,7 @@ TF_COUNTERS = {"sources_sha256_16": "ebcfe029a2e781b1", "fetch_kib": 230771.5, "
                # SQ_INSTS_VALU and SQ_VALU_MFMA_BUSY_CYCLES of one step's launch
                # per FLOP of the class blocks that step ran (7.2503e13)
                "valu_per_flop": 6.984e10 / 7.2503e13, "mfma_busy_cycles_per_flop": 9.393e10 / 7.2503e13}
-TF_SOURCES = ("paper_2306_16705_amd/csrc/model_bf16.hip",)
+TF_SOURCES = ("paper_2306_16705_amd/csrc/transformer.hpp", "paper_2306_16705_amd/csrc/transformer_list.hip")
 
 
 def sources_hash(files):

@@ -1,10 +1,12 @@
 """Builds the HIP shared library ``libnnqs_eloc.so`` for gfx950, in-tree."""
 from __future__ import annotations
 
+import concurrent.futures
 import glob
 import os
 import shutil
 import subprocess
+import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -25,18 +27,25 @@ def sources() -> list[str]:
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-def build(verbose: bool = False) -> str:
-    """Compile every HIP source into one shared library (always recompiles)."""
-    out_tmp = LIB + ".tmp"
-    cmd = [hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wno-unused-command-line-argument",
-           f"-I{INCLUDE}", f"-I{CSRC}", "-o", out_tmp, *sources()]
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed ({r.returncode}):\n{r.stderr[-8000:]}")
+
+
+def build(verbose: bool = False) -> str:
+    """Compile every HIP source (in parallel) and link one shared library (always recompiles)."""
+    out_tmp = LIB + ".tmp"
+    flags = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC",
+             "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+             "-Wno-unused-command-line-argument", f"-I{INCLUDE}", f"-I{CSRC}"]
+    with tempfile.TemporaryDirectory() as tmp:
+        jobs = [(s, os.path.join(tmp, os.path.basename(s) + ".o")) for s in sources()]
+        with concurrent.futures.ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as pool:
+            list(pool.map(lambda j: _run([hipcc(), *flags, "-c", j[0], "-o", j[1]], verbose), jobs))
+        _run([hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", out_tmp, *[o for _, o in jobs]], verbose)
     os.replace(out_tmp, LIB)
     return LIB
 

@@ -1,61 +1,19 @@
-// BF16 MFMA forward of the amplitude transformer and the phase MLP (the
-// networks of Section 3.1 / Fig. 2; phase MLP sizes of Section 4.1), for the
-// shape d_model 64, 4 heads, FFN 256, phase hidden 512, K <= 64 orbitals.
+// Phase MLP on BF16 MFMA, the BF16 / FP8 copies of the weights, and the
+// launches of the reduced-precision network (phase MLP sizes of Section 4.1;
+// the transformer's kernel body is in transformer.hpp), for the shape d_model
+// 64, 4 heads, FFN 256, phase hidden 512, K <= 64 orbitals.
 //
-// Transformer: two 64-lane waves own one configuration (64 sequence rows;
-// rows >= K are padding that no real row attends to), each holding the
-// residual stream of 32 rows in registers as eight 16x16 FP32 accumulator
-// tiles of v_mfma_f32_16x16x32_bf16; eight waves per block serve four
-// configurations, two waves per SIMD.  Every matrix product runs on that
-// MFMA with BF16 operands and FP32 accumulation: LayerNorm output -> LDS
-// (BF16) -> A tiles; weights are staged transposed (k contiguous) in LDS,
-// shared by the block, and read as B tiles.  Attention is computed
-// transposed, S^T = K Q^T, so that each lane owns one query and the causal
-// softmax over keys is a register reduction plus two cross-lane steps;
-// O^T = V^T P^T.  LayerNorm, softmax, GELU and the output head stay FP32.
-//
-// Phase MLP: a second kernel runs bits[128 x 128] @ W1 and
-// GELU(z1)[128 x 512] @ W2 on the same MFMA for 128 configurations per block,
-// each wave owning 64 output columns (weight fragments from L2, read once per
-// block pass; z1 in LDS).
+// Phase MLP: bits[128 x 128] @ W1 and GELU(z1)[128 x 512] @ W2 on the 16x16x32
+// MFMA for 128 configurations per block, each wave owning 64 output columns
+// (weight fragments from L2, read once per block pass; z1 in LDS).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
 
-#include "model.hpp"
+#include "transformer.hpp"
 
 namespace nnqs {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int kD = 64, kH = 4, kDh = 16, kF = 256, kP = 512, kRows = 64;
-constexpr int kLd = 72;        // padded LDS row length (BF16) of 64-wide tiles
-constexpr int kQLd = 24;       // padded row length of the per-head Q / K tiles
-constexpr int kPhaseBits = 128;
-
-// Device layout of the BF16 weights (element offsets into d_bf16).
-struct Bf16Layout {
-    int64_t layer0, layer_stride;   // per layer: wqkvT[192][64] woT[64][64] w1T[256][64] w2T[64][256]
-    int64_t ph_w1T, ph_w2T, total;  // ph_w1T[512][128] (rows: hidden unit, cols: bit), ph_w2T[512][512]
-};
-// FP32 vectors (element offsets into d_f32).
-struct F32Layout {
-    int64_t tok_emb, pos_emb, layer0, layer_stride;  // per layer: ln1_g ln1_b bqkv[192] bo ln2_g ln2_b b1[256] b2
-    int64_t lnf_g, lnf_b, head_w, head_b, bias, ph_b1, ph_b2, ph_w3, ph_b3, gelu, total;
-};
-
-// The transformer's FFN GELU, v * Phi(v), takes the normal CDF Phi from a
-// table of kGeluN (value, step) pairs at spacing 1/kGeluScale on [-8, 8):
-// linear interpolation errs by at most h^2/8 max|Phi''| = 3e-5 (h = 1/32),
-// well below the BF16 rounding of the result; Phi is clamped to its end
-// values outside the range (Phi(-8) = 6e-16).  It replaces the exp and
-// reciprocal of a closed-form erf by one LDS read (16384 GELUs per layer and
-// configuration make this the largest VALU cost of the forward).
-constexpr int kGeluN = 512;
-constexpr float kGeluScale = 32.0f, kGeluOff = 256.0f, kGeluMaxU = 511.99997f;
 
 static Bf16Layout bf16_layout(int L) {
     Bf16Layout o{};
@@ -87,814 +45,6 @@ static F32Layout f32_layout(int K, int L) {
     o.gelu = at; at += 2 * kGeluN;
     o.total = at;
     return o;
-}
-
-// per-layer FP32 vector offsets
-constexpr int kV_ln1_g = 0, kV_ln1_b = 64, kV_bqkv = 128, kV_bo = 320, kV_ln2_g = 384, kV_ln2_b = 448,
-              kV_b1 = 512, kV_b2 = 768;
-// FP8 scales of one layer's six weight matrices (q, k, v, o, w1, w2): for
-// each, the power of two s applied before quantisation and 1/s.
-constexpr int kV_f8 = 832;
-
-struct Bf16View {
-    int K, L, n_up, n_dn;
-    const __bf16 *wb;
-    const uint8_t *w8;  // FP8 E4M3 copy of the transformer matrices, same element layout as wb
-    const float *wf;
-    Bf16Layout bl;
-    F32Layout fl;
-};
-
-// ------------------------------------------------------------ fragments
-// v_mfma_f32_16x16x32_bf16 operand layout: A/B lane l holds row/column
-// (l & 15) and k = 8 (l >> 4) .. 8 (l >> 4) + 7; the accumulator lane l holds
-// column (l & 15) and rows 4 (l >> 4) .. 4 (l >> 4) + 3.
-__device__ __forceinline__ f32x4 mfma16(const bf16x8 &a, const bf16x8 &b, const f32x4 &c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
-
-__device__ __forceinline__ bf16x8 lds_frag(const __bf16 *base, int row, int ld, int k0) {
-    return *reinterpret_cast<const bf16x8 *>(base + row * ld + k0);
-}
-
-__device__ __forceinline__ float dpp_row_sum(float v) {
-    // sum over the 16 lanes of a DPP row (all lanes receive the total)
-    v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0xB1, 0xF, 0xF, true));  // xor 1
-    v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x4E, 0xF, 0xF, true));  // xor 2
-    v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x141, 0xF, 0xF, true)); // half mirror
-    v += __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), 0x140, 0xF, 0xF, true)); // mirror
-    return v;
-}
-
-__device__ __forceinline__ float gelu32(float v) { return gelu_bf16path(v); }
-
-// GELU from the LDS table (see kGeluN): u = 32 (v + 8) clamped to [0, 512),
-// entry floor(u), fraction u - floor(u).
-__device__ __forceinline__ float gelu_tab(const float2 *tab, float v) {
-    const float u = __builtin_amdgcn_fmed3f(fmaf(v, kGeluScale, kGeluOff), 0.0f, kGeluMaxU);
-    const float2 e = tab[(int)u];
-    return v * fmaf(__builtin_amdgcn_fractf(u), e.y, e.x);
-}
-
-// Cooperative copy of `rows` rows of `cols` BF16 (global, row stride gld) into
-// LDS rows of stride lld.  cols is a multiple of 8.
-__device__ __forceinline__ void stage_rows(__bf16 *dst, int lld, const __bf16 *src, int gld, int rows, int cols) {
-    const int per_row = cols / 8;
-    for (int e = threadIdx.x; e < rows * per_row; e += blockDim.x) {
-        const int rr = e / per_row, cc = (e - rr * per_row) * 8;
-        *reinterpret_cast<bf16x8 *>(dst + rr * lld + cc) = *reinterpret_cast<const bf16x8 *>(src + (int64_t)rr * gld + cc);
-    }
-}
-
-// Operands of the four weight products (QKV, output, FFN in and out):
-// BF16 on v_mfma_f32_16x16x32_bf16, or OCP FP8 E4M3 bytes on
-// v_mfma_f32_16x16x32_fp8_fp8 (same lane layout, eight 1-byte elements per
-// lane; activations are not scaled, each weight matrix has a power-of-two
-// scale that the accumulators undo).
-template <bool kF8>
-struct Op;
-
-template <>
-struct Op<false> {
-    typedef __bf16 T;
-    typedef bf16x8 Frag;
-    static constexpr int ld = kLd;  // padded LDS row length of 64-wide tiles
-    static __device__ __forceinline__ Frag frag(const T *base, int row, int k0) { return lds_frag(base, row, ld, k0); }
-    static __device__ __forceinline__ f32x4 mma(const Frag &a, const Frag &b, const f32x4 &c) { return mfma16(a, b, c); }
-    static __device__ __forceinline__ T cvt(float v) { return (__bf16)v; }
-};
-
-template <>
-struct Op<true> {
-    typedef uint8_t T;
-    typedef long Frag;
-    static constexpr int ld = 80;  // bytes; keeps 16-byte staging stores aligned
-    static __device__ __forceinline__ Frag frag(const T *base, int row, int k0) {
-        return *reinterpret_cast<const long *>(base + row * ld + k0);
-    }
-    static __device__ __forceinline__ f32x4 mma(const Frag &a, const Frag &b, const f32x4 &c) {
-        return __builtin_amdgcn_mfma_f32_16x16x32_fp8_fp8(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ T cvt(float v) {  // E4M3, round to nearest even, saturated at 448
-        return (T)(__builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(v, -448.f, 448.f), 0.f, 0, false) & 0xff);
-    }
-};
-
-__device__ __forceinline__ uint32_t fp8x4(const f32x4 &v) {
-    int r = 0;
-    r = __builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(v[0], -448.f, 448.f),
-                                        __builtin_amdgcn_fmed3f(v[1], -448.f, 448.f), r, false);
-    r = __builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(v[2], -448.f, 448.f),
-                                        __builtin_amdgcn_fmed3f(v[3], -448.f, 448.f), r, true);
-    return (uint32_t)r;
-}
-
-// Cooperative copy of `rows` rows of `cols` operands (global, row stride
-// gld) into LDS rows of stride lld, in 16-byte pieces.
-template <typename T>
-__device__ __forceinline__ void stage_rows_t(T *dst, int lld, const T *src, int gld, int rows, int cols) {
-    constexpr int per16 = 16 / (int)sizeof(T);
-    const int per_row = cols / per16;
-    for (int e = threadIdx.x; e < rows * per_row; e += blockDim.x) {
-        const int rr = e / per_row, cc = (e - rr * per_row) * per16;
-        *reinterpret_cast<uint4 *>(dst + rr * lld + cc) = *reinterpret_cast<const uint4 *>(src + (int64_t)rr * gld + cc);
-    }
-}
-
-// ------------------------------------------------------ transformer forward
-// Work of one launch, in one of two modes.
-//  * Sample mode: configurations keys[0..n), every row evaluated; log|psi|
-//    to logabs[i].  With `kv_out` and `pre_out` it also keeps, per configuration,
-//    every layer's keys and values (BF16, as the attention used them) and the
-//    prefix sums pre[i][b] of its per-position log-probabilities over the
-//    first 16 b positions: the cache that list mode reads.
-//  * List mode: connected configurations x' of cached samples, as chunk-local
-//    connection indices e (key xkeys[e], sample e / C) sorted into four
-//    classes (hdr = {count[4], offset[4]} on the device).  Class b holds the
-//    x' whose first position that differs from their sample lies at or after
-//    16 b: by causality the rows s <= 16 b of x' equal the sample's, so only
-//    row blocks b..3 are evaluated; their attention reads the keys and values
-//    of blocks < b from the sample's cache, and the log-probabilities of
-//    positions < 16 b are the sample's prefix sum.  log|psi| goes to xla[e].
-//    Results are bit-identical to sample mode on x' (same per-row arithmetic,
-//    same summation order).
-struct TfArgs {
-    const uint64_t *keys;
-    int64_t n;
-    double *logabs;
-    __bf16 *kv_out;        // sample mode: cache written (may be null)
-    double *pre_out;
-    const __bf16 *kv_in;   // list mode: cache read
-    const double *pre_in;
-    const int32_t *list;
-    const int64_t *hdr;
-    const uint64_t *xkeys;
-    int64_t C;
-    double *xla;
-    int list_mode;
-    int cond_pos;      // sample mode, batch sampling: position whose conditionals are written
-    double *cond_out;  // [n][4] masked log-probabilities of the four tokens there (may be null)
-};
-
-// A block evaluates one tile of 16 row-block slots (16 rows each), two per
-// wave.  Class-0 tiles hold four configurations, wave pair (2c, 2c+1) owning
-// configuration c's row blocks {0, 3} and {1, 2} (row block b attends to
-// b + 1 key blocks, and 1 + 4 = 2 + 3); class b > 0 tiles hold
-// floor(16 / (4 - b)) configurations whose blocks b..3 fill consecutive slots.
-constexpr int kSlots = 16;
-constexpr int kVLd = 24;  // padded row length of a slot's V^T (16 keys)
-constexpr int kKvPerHead = 64 * kDh + kDh * 64;  // cached K [64][16] then V^T [16][64]
-
-__device__ __forceinline__ int cls_cpt(int cls) { return cls == 0 ? 4 : cls == 1 ? 5 : cls == 2 ? 8 : 16; }
-
-__device__ __forceinline__ void slot_info(int cls, int q, int &c, int &rb) {
-    if (cls == 0) {
-        c = q >> 2;
-        const int r = q & 3;
-        rb = r == 0 ? 0 : r == 1 ? 3 : r == 2 ? 1 : 2;
-    } else {
-        const int nb = 4 - cls;
-        c = q / nb;
-        rb = cls + (q - c * nb);
-    }
-}
-
-__device__ __forceinline__ int slot_of(int cls, int c, int kb) {
-    if (cls == 0) return 4 * c + (kb == 0 ? 0 : kb == 1 ? 2 : kb == 2 ? 3 : 1);
-    return c * (4 - cls) + (kb - cls);
-}
-
-struct Tile32 {
-    f32x4 t[8];  // tile (j, cb) = t[j * 4 + cb]: own slot j, column block cb
-};
-
-// acc += X_j[16 rows][0..k_len) (LDS, row stride Op::ld) @ W for both own
-// slots, Wt[n][k] in LDS.
-template <bool kF8>
-__device__ __forceinline__ void gemm_slots(Tile32 &acc, const typename Op<kF8>::T *X0, const typename Op<kF8>::T *X1,
-                                           const typename Op<kF8>::T *Wt, int k_len) {
-    typedef Op<kF8> OP;
-    const int l = threadIdx.x & 63;
-    const int r = l & 15, kq = 8 * (l >> 4);
-    for (int ks = 0; ks < k_len; ks += 32) {
-        typename OP::Frag a[2], b[4];
-        a[0] = OP::frag(X0, r, ks + kq);
-        a[1] = OP::frag(X1, r, ks + kq);
-#pragma unroll
-        for (int cb = 0; cb < 4; cb++) b[cb] = OP::frag(Wt, cb * 16 + r, ks + kq);
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-            for (int cb = 0; cb < 4; cb++) acc.t[j * 4 + cb] = OP::mma(a[j], b[cb], acc.t[j * 4 + cb]);
-    }
-}
-
-// Normalised rows (h - mean) / sqrt(var + eps) of both own slots into X_j
-// (LDS).  The LayerNorm's scale and shift are folded into the weights of the
-// product that reads X.
-template <bool kF8>
-__device__ __forceinline__ void normalize_rows(const Tile32 &h, typename Op<kF8>::T *X0, typename Op<kF8>::T *X1) {
-    typedef Op<kF8> OP;
-    const int l = threadIdx.x & 63;
-    const int c = l & 15, r0 = 4 * (l >> 4);
-#pragma unroll
-    for (int j = 0; j < 2; j++) {
-        typename OP::T *X = j ? X1 : X0;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            float s = 0.f, s2 = 0.f;
-#pragma unroll
-            for (int cb = 0; cb < 4; cb++) {
-                const float v = h.t[j * 4 + cb][i];
-                s += v;
-                s2 = fmaf(v, v, s2);
-            }
-            const float mean = dpp_row_sum(s) * (1.0f / kD);
-            const float var = fmaxf(dpp_row_sum(s2) * (1.0f / kD) - mean * mean, 0.0f);
-            const float rstd = rsqrtf(var + 1e-5f);
-            const float sh = -mean * rstd;
-#pragma unroll
-            for (int cb = 0; cb < 4; cb++) X[(r0 + i) * OP::ld + cb * 16 + c] = OP::cvt(fmaf(h.t[j * 4 + cb][i], rstd, sh));
-        }
-    }
-}
-
-// The residual stream is kept transposed: tile t[j * 4 + db] of slot j holds,
-// in lane l, sequence row (l & 15) of the slot and model columns
-// 16 db + 4 (l >> 4) + i, i = 0..3.  Products that feed it are computed as
-// C^T = W^T A^T (weights as the A operand, activations as the B operand), so
-// each lane's four outputs are consecutive columns of one row: LDS stores of
-// normalised rows and GELU outputs are one 8-byte write per four values.
-// acc^T += W^T X_j^T for both own slots; Wt[n][k] in LDS, X_j row-major.
-template <bool kF8>
-__device__ __forceinline__ void gemm_slots_t(Tile32 &acc, const typename Op<kF8>::T *X0, const typename Op<kF8>::T *X1,
-                                             const typename Op<kF8>::T *Wt, int k_len) {
-    typedef Op<kF8> OP;
-    const int l = threadIdx.x & 63;
-    const int r = l & 15, kq = 8 * (l >> 4);
-    for (int ks = 0; ks < k_len; ks += 32) {
-        typename OP::Frag a[4], b[2];
-        b[0] = OP::frag(X0, r, ks + kq);
-        b[1] = OP::frag(X1, r, ks + kq);
-#pragma unroll
-        for (int db = 0; db < 4; db++) a[db] = OP::frag(Wt, db * 16 + r, ks + kq);
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-#pragma unroll
-            for (int db = 0; db < 4; db++) acc.t[j * 4 + db] = OP::mma(a[db], b[j], acc.t[j * 4 + db]);
-    }
-}
-
-// Four consecutive values of one row into LDS (BF16, or FP8 E4M3).
-template <bool kF8>
-__device__ __forceinline__ void store4(typename Op<kF8>::T *dst, const f32x4 &v);
-template <>
-__device__ __forceinline__ void store4<false>(__bf16 *dst, const f32x4 &v) {
-    bf16x4 o;
-#pragma unroll
-    for (int i = 0; i < 4; i++) o[i] = (__bf16)v[i];
-    *reinterpret_cast<bf16x4 *>(dst) = o;
-}
-template <>
-__device__ __forceinline__ void store4<true>(uint8_t *dst, const f32x4 &v) {
-    int r = 0;
-    r = __builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(v[0], -448.f, 448.f),
-                                        __builtin_amdgcn_fmed3f(v[1], -448.f, 448.f), r, false);
-    r = __builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(v[2], -448.f, 448.f),
-                                        __builtin_amdgcn_fmed3f(v[3], -448.f, 448.f), r, true);
-    *reinterpret_cast<int *>(dst) = r;
-}
-
-// Mean and 1/sqrt(var + eps) of the row of slot j held by this lane's group
-// of four lanes (l, l ^ 16, l ^ 32, l ^ 48), one-pass statistics.
-__device__ __forceinline__ void row_stats_t(const Tile32 &h, int j, float &rstd, float &shift) {
-    float s = 0.f, s2 = 0.f;
-#pragma unroll
-    for (int db = 0; db < 4; db++)
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const float v = h.t[j * 4 + db][i];
-            s += v;
-            s2 = fmaf(v, v, s2);
-        }
-    s += __shfl_xor(s, 16, 64);
-    s2 += __shfl_xor(s2, 16, 64);
-    s += __shfl_xor(s, 32, 64);
-    s2 += __shfl_xor(s2, 32, 64);
-    const float mean = s * (1.0f / kD);
-    const float var = fmaxf(s2 * (1.0f / kD) - mean * mean, 0.0f);
-    rstd = rsqrtf(var + 1e-5f);
-    shift = -mean * rstd;
-}
-
-// Normalised rows of both own slots into X_j (LDS, row-major); the
-// LayerNorm's scale and shift are folded into the next product's weights.
-template <bool kF8>
-__device__ __forceinline__ void normalize_rows_t(const Tile32 &h, typename Op<kF8>::T *X0, typename Op<kF8>::T *X1) {
-    const int l = threadIdx.x & 63;
-    const int c16 = l & 15, r0 = 4 * (l >> 4);
-#pragma unroll
-    for (int j = 0; j < 2; j++) {
-        float rstd, sh;
-        row_stats_t(h, j, rstd, sh);
-        typename Op<kF8>::T *X = (j ? X1 : X0) + c16 * Op<kF8>::ld + r0;
-#pragma unroll
-        for (int db = 0; db < 4; db++) {
-            f32x4 y;
-#pragma unroll
-            for (int i = 0; i < 4; i++) y[i] = fmaf(h.t[j * 4 + db][i], rstd, sh);
-            store4<kF8>(X + db * 16, y);
-        }
-    }
-}
-
-__device__ __forceinline__ f32x4 ld4(const float *p) {
-    const float4 v = *reinterpret_cast<const float4 *>(p);
-    return f32x4{v.x, v.y, v.z, v.w};
-}
-
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-__device__ __forceinline__ bf16x4 cvt4(const f32x4 &v) {
-    bf16x4 o;
-#pragma unroll
-    for (int i = 0; i < 4; i++) o[i] = (__bf16)v[i];
-    return o;
-}
-
-// Where the keys and values of one configuration's key blocks live for
-// one head: blocks < sb in the sample's cache (global), the others in the
-// tile's slots (LDS).
-struct KvSrc {
-    const __bf16 *kc, *vc;  // cached K [64][16] and V^T [16][64] of this head (blocks < sb)
-    const __bf16 *ks, *vt;  // LDS slot arrays of the tile
-    int cls, c, sb;
-};
-
-// Causal attention of query block QB (a slot of configuration c) for one
-// head: S^T[key][query] = K Q^T (the lane owns query c16 + 16 QB and keys
-// 16 kb + r0 + i), softmax over keys in base 2 (scale and log2(e) are folded
-// into Q): unnormalised P[query][key] -> Pb, then O^T[c][query] = V^T P^T
-// divided by the row sums 1^T P^T (the same MFMA with an all-ones operand)
-// into Oq[query][16 hh + c].
-template <int QB, bool kF8>
-__device__ __forceinline__ void attend_block(const __bf16 *Qq, const KvSrc &S, __bf16 *Pb, typename Op<kF8>::T *Oq,
-                                             int hh) {
-    const int l = threadIdx.x & 63;
-    const int c16 = l & 15, r0 = 4 * (l >> 4), kq = 8 * (l >> 4);
-    const bf16x8 zero8 = {};
-    const bf16x8 bqf = l < 32 ? lds_frag(Qq, c16, kQLd, kq) : zero8;
-    f32x4 st[4];
-#pragma unroll
-    for (int kb = 0; kb < 4; kb++) {
-        st[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (kb <= QB) {
-            bf16x8 akf = zero8;
-            if (l < 32) {
-                if (kb < S.sb) akf = *reinterpret_cast<const bf16x8 *>(S.kc + (kb * 16 + c16) * kDh + kq);
-                else akf = lds_frag(S.ks + slot_of(S.cls, S.c, kb) * (16 * kQLd), c16, kQLd, kq);
-            }
-            st[kb] = mfma16(akf, bqf, st[kb]);
-        }
-    }
-    // key 16 kb + r0 + i is visible to query 16 QB + c16 when kb < QB, or
-    // kb == QB and r0 + i <= c16
-    float mx = -INFINITY;
-#pragma unroll
-    for (int kb = 0; kb <= QB; kb++)
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-            if (kb < QB || r0 + i <= c16) mx = fmaxf(mx, st[kb][i]);
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-    // unnormalised weights p = 2^(s - max) in BF16; the denominator of each
-    // query is the sum of the same BF16 values, taken by one more MFMA with an
-    // all-ones operand, and divides the output (four values per lane)
-#pragma unroll
-    for (int kb = 0; kb < 4; kb++) {
-        bf16x4 pk;
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-            pk[i] = (__bf16)((kb < QB || (kb == QB && r0 + i <= c16)) ? __builtin_amdgcn_exp2f(st[kb][i] - mx) : 0.f);
-        *reinterpret_cast<bf16x4 *>(Pb + c16 * kLd + kb * 16 + r0) = pk;
-    }
-    wave_lds_sync();
-    bf16x8 ones;
-#pragma unroll
-    for (int e = 0; e < 8; e++) ones[e] = (__bf16)1.0f;
-    f32x4 ot = {0.f, 0.f, 0.f, 0.f}, den = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int ks = 0; ks < 64; ks += 32) {
-        if (ks <= QB * 16 + 15) {
-            const int kb = (ks >> 4) + (kq >> 4);  // key block of this lane's eight keys
-            bf16x8 av;
-            if (kb < S.sb) av = *reinterpret_cast<const bf16x8 *>(S.vc + c16 * 64 + ks + kq);
-            else av = *reinterpret_cast<const bf16x8 *>(S.vt + slot_of(S.cls, S.c, kb) * (kDh * kVLd) + c16 * kVLd + (kq & 15));
-            const bf16x8 bp = lds_frag(Pb, c16, kLd, ks + kq);
-            ot = mfma16(av, bp, ot);
-            den = mfma16(ones, bp, den);
-        }
-    }
-    ot *= __builtin_amdgcn_rcpf(den[0]);
-    if constexpr (kF8)
-        *reinterpret_cast<uint32_t *>(Oq + c16 * Op<true>::ld + hh * kDh + r0) = fp8x4(ot);
-    else
-        *reinterpret_cast<bf16x4 *>(Oq + c16 * kLd + hh * kDh + r0) = cvt4(ot);
-    wave_lds_sync();  // Pb is rewritten by the next block
-}
-
-template <bool kF8>
-__device__ __forceinline__ void attend(int QB, const __bf16 *Qq, const KvSrc &S, __bf16 *Pb, typename Op<kF8>::T *Oq,
-                                       int hh) {
-    switch (QB) {
-        case 0: attend_block<0, kF8>(Qq, S, Pb, Oq, hh); break;
-        case 1: attend_block<1, kF8>(Qq, S, Pb, Oq, hh); break;
-        case 2: attend_block<2, kF8>(Qq, S, Pb, Oq, hh); break;
-        default: attend_block<3, kF8>(Qq, S, Pb, Oq, hh); break;
-    }
-}
-
-// One item of a batched list-mode launch: a system's model and work.
-struct TfItem {
-    Bf16View M;
-    TfArgs A;
-};
-constexpr int kMaxTfItems = 64;
-
-template <bool kList, bool kF8, bool kBatch>
-__device__ __forceinline__ void transformer_bf16(const Bf16View &M0, const TfArgs &A0, const TfItem *items,
-                                                 int n_items) {
-    typedef Op<kF8> OP;
-    typedef typename OP::T AT;
-    constexpr int kLdA = OP::ld;
-    __shared__ __align__(16) AT wbuf[192 * kLdA];
-    __shared__ __align__(16) float2 gtab[kGeluN];
-    __shared__ __align__(16) AT xs[kSlots][16 * kLdA];
-    __shared__ __align__(16) AT os[kSlots][16 * kLdA];
-    __shared__ __align__(16) __bf16 qs[kSlots][16 * kQLd];
-    __shared__ __align__(16) __bf16 ks_[kSlots][16 * kQLd];
-    __shared__ __align__(16) __bf16 vt[kSlots][kDh * kVLd];
-    __shared__ __align__(16) __bf16 ps[8][16 * kLd];
-    __shared__ double slot_lp[kSlots];
-    __shared__ int64_t sh_hdr[8];
-    // batched launch: first global tile of every (item, class), in item-major order
-    __shared__ int64_t sh_tile0[kBatch ? 4 * kMaxTfItems + 1 : 1];
-
-    const int l = threadIdx.x & 63;
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int c16 = l & 15, r0 = 4 * (l >> 4), kq = 8 * (l >> 4);
-    __bf16 *Pb = ps[w];
-    for (int i = threadIdx.x; i < kGeluN; i += blockDim.x)  // the same table in every model
-        gtab[i] = make_float2(M0.wf[M0.fl.gelu + 2 * i], M0.wf[M0.fl.gelu + 2 * i + 1]);
-    if (!kBatch && kList && threadIdx.x < 8) sh_hdr[threadIdx.x] = A0.hdr[threadIdx.x];
-    if constexpr (kBatch) {
-        if (threadIdx.x == 0) {
-            int64_t acc = 0;
-            for (int it = 0; it < n_items; it++)
-                for (int c = 0; c < 4; c++) {
-                    sh_tile0[4 * it + c] = acc;
-                    acc += (items[it].A.hdr[c] + cls_cpt(c) - 1) / cls_cpt(c);
-                }
-            sh_tile0[4 * n_items] = acc;
-        }
-    }
-    __syncthreads();
-    int64_t tiles[4] = {0, 0, 0, 0}, T;
-    if (kBatch) {
-        T = sh_tile0[4 * n_items];
-    } else if (kList) {
-        T = 0;
-        for (int c = 0; c < 4; c++) {
-            tiles[c] = (sh_hdr[c] + cls_cpt(c) - 1) / cls_cpt(c);
-            T += tiles[c];
-        }
-    } else {
-        T = (A0.n + 3) / 4;
-    }
-
-    for (int64_t tile = blockIdx.x; tile < T; tile += gridDim.x) {
-        int cls = 0;
-        int64_t tb = tile * 4, cnt = A0.n, lbase = 0;
-        Bf16View M = M0;
-        TfArgs A = A0;
-        if constexpr (kBatch) {
-            int q = 0;  // the last (item, class) whose first tile is at or before `tile`
-            for (int step = 4 * kMaxTfItems; step >= 1; step >>= 1)
-                if (q + step < 4 * n_items && sh_tile0[q + step] <= tile) q += step;
-            const int it = q >> 2;
-            cls = q & 3;
-            M = items[it].M;
-            A = items[it].A;
-            tb = (tile - sh_tile0[q]) * cls_cpt(cls);
-            cnt = A.hdr[cls];
-            lbase = A.hdr[4 + cls];
-        } else if (kList) {
-            int64_t tt = tile;
-            cls = 3;
-            for (int c = 0; c < 3; c++) {
-                if (tt < tiles[c]) {
-                    cls = c;
-                    break;
-                }
-                tt -= tiles[c];
-            }
-            tb = tt * cls_cpt(cls);
-            cnt = sh_hdr[cls];
-            lbase = sh_hdr[4 + cls];
-        }
-        const int K = M.K;
-        const float *wf = M.wf;
-        const int64_t kv_cfg = (int64_t)M.L * kH * kKvPerHead;  // cache elements per configuration
-        const int cpt = cls_cpt(cls);
-        // the wave's two slots: configuration, row block, key, sample
-        int sc[2], srb[2];
-        uint64_t upm[2], dnm[2];
-        int64_t ssmp[2];
-#pragma unroll
-        for (int j = 0; j < 2; j++) {
-            slot_info(cls, 2 * w + j, sc[j], srb[j]);
-            const bool valid = sc[j] < cpt && tb + sc[j] < cnt;
-            Key x{0ull, 0ull};
-            ssmp[j] = 0;
-            if (valid) {
-                if (kList) {
-                    const int64_t e = A.list[lbase + tb + sc[j]];
-                    x.lo = A.xkeys[2 * e];
-                    x.hi = A.xkeys[2 * e + 1];
-                    ssmp[j] = e / A.C;
-                } else {
-                    x.lo = A.keys[2 * (tb + sc[j])];
-                    x.hi = A.keys[2 * (tb + sc[j]) + 1];
-                }
-            }
-            // token of position q (orbital K-1-q) = up bit + 2 down bit, as
-            // two wave-uniform 64-bit masks over positions
-            const bool inq = l < K;
-            upm[j] = __ballot(inq && key_bit(x, 2 * (K - 1 - l)));
-            dnm[j] = __ballot(inq && key_bit(x, 2 * (K - 1 - l) + 1));
-        }
-        auto token = [&](int j, int q) -> int {
-            return (int)((upm[j] >> q) & 1ull) | ((int)((dnm[j] >> q) & 1ull) << 1);
-        };
-        AT *X0 = xs[2 * w], *X1 = xs[2 * w + 1], *O0 = os[2 * w], *O1 = os[2 * w + 1];
-        // embeddings of the own rows (transposed layout): h[s][c] = tok_emb[prev token][c] +
-        // pos_emb[s][c], padding rows 0
-        Tile32 h;
-#pragma unroll
-        for (int j = 0; j < 2; j++) {
-            const int s = srb[j] * 16 + c16;
-            const int prev = s == 0 ? 4 : (s < K ? token(j, s - 1) : 0);
-#pragma unroll
-            for (int db = 0; db < 4; db++) {
-                const int c = db * 16 + r0;
-                h.t[j * 4 + db] = s < K ? ld4(wf + M.fl.tok_emb + prev * kD + c) + ld4(wf + M.fl.pos_emb + s * kD + c)
-                                        : f32x4{0.f, 0.f, 0.f, 0.f};
-            }
-        }
-
-        for (int layer = 0; layer < M.L; layer++) {
-            const float *lv = wf + M.fl.layer0 + layer * M.fl.layer_stride;
-            const AT *lw = (kF8 ? reinterpret_cast<const AT *>(M.w8) : reinterpret_cast<const AT *>(M.wb)) +
-                           M.bl.layer0 + layer * M.bl.layer_stride;
-            // FP8: power-of-two scale s of each weight matrix and 1/s
-            const float *f8 = lv + kV_f8;
-            normalize_rows_t<kF8>(h, X0, X1);
-            __syncthreads();  // previous users of wbuf are done
-            stage_rows_t(wbuf, kLdA, lw, 64, 192, 64);
-            __syncthreads();
-            for (int hh = 0; hh < kH; hh++) {
-                // Q^T and K^T (dims x positions) and V (positions x dims) of the
-                // own slots, biases in the accumulators
-                f32x4 qt[2], kt[2], v[2];
-                const float bv = lv[kV_bqkv + 128 + hh * kDh + c16] * (kF8 ? f8[4] : 1.0f);
-                f32x4 bq, bk;
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    bq[i] = lv[kV_bqkv + hh * kDh + r0 + i] * (kF8 ? f8[0] : 1.0f);
-                    bk[i] = lv[kV_bqkv + 64 + hh * kDh + r0 + i] * (kF8 ? f8[2] : 1.0f);
-                }
-#pragma unroll
-                for (int j = 0; j < 2; j++) {
-                    qt[j] = bq;
-                    kt[j] = bk;
-                    v[j] = f32x4{bv, bv, bv, bv};
-                }
-#pragma unroll
-                for (int ks = 0; ks < 64; ks += 32) {
-                    const typename OP::Frag wq = OP::frag(wbuf, hh * kDh + c16, ks + kq);
-                    const typename OP::Frag wk = OP::frag(wbuf, 64 + hh * kDh + c16, ks + kq);
-                    const typename OP::Frag wv = OP::frag(wbuf, 128 + hh * kDh + c16, ks + kq);
-#pragma unroll
-                    for (int j = 0; j < 2; j++) {
-                        const typename OP::Frag a = OP::frag(j ? X1 : X0, c16, ks + kq);
-                        qt[j] = OP::mma(wq, a, qt[j]);
-                        kt[j] = OP::mma(wk, a, kt[j]);
-                        v[j] = OP::mma(a, wv, v[j]);
-                    }
-                }
-                if constexpr (kF8) {
-#pragma unroll
-                    for (int j = 0; j < 2; j++) {
-                        qt[j] *= f8[1];
-                        kt[j] *= f8[3];
-                        v[j] *= f8[5];
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < 2; j++) {
-                    const int q = 2 * w + j;
-                    const bf16x4 k4 = cvt4(kt[j]), v4 = cvt4(v[j]);
-                    *reinterpret_cast<bf16x4 *>(qs[q] + c16 * kQLd + r0) = cvt4(qt[j]);
-                    *reinterpret_cast<bf16x4 *>(ks_[q] + c16 * kQLd + r0) = k4;
-                    *reinterpret_cast<bf16x4 *>(vt[q] + c16 * kVLd + r0) = v4;
-                    if (A.kv_out && sc[j] < cpt && tb + sc[j] < cnt) {  // sample mode: keep them for list mode
-                        __bf16 *kc = A.kv_out + (tb + sc[j]) * kv_cfg + ((int64_t)layer * kH + hh) * kKvPerHead;
-                        *reinterpret_cast<bf16x4 *>(kc + (srb[j] * 16 + c16) * kDh + r0) = k4;
-                        *reinterpret_cast<bf16x4 *>(kc + 64 * kDh + c16 * 64 + srb[j] * 16 + r0) = v4;
-                    }
-                }
-                __syncthreads();  // K and V of every slot written
-#pragma unroll
-                for (int j = 0; j < 2; j++) {
-                    KvSrc S;
-                    const __bf16 *kc = A.kv_in ? A.kv_in + ssmp[j] * kv_cfg + ((int64_t)layer * kH + hh) * kKvPerHead : nullptr;
-                    S.kc = kc;
-                    S.vc = kc + 64 * kDh;
-                    S.ks = &ks_[0][0];
-                    S.vt = &vt[0][0];
-                    S.cls = cls;
-                    S.c = sc[j];
-                    S.sb = kList ? cls : 0;
-                    attend<kF8>(srb[j], qs[2 * w + j], S, Pb, j ? O1 : O0, hh);
-                }
-                __syncthreads();  // every slot done with this head's K and V (and the QKV weights)
-            }
-            stage_rows_t(wbuf, kLdA, lw + 192 * 64, 64, 64, 64);
-            __syncthreads();
-#pragma unroll
-            for (int db = 0; db < 4; db++) {
-                const f32x4 bo = ld4(lv + kV_bo + db * 16 + r0);
-#pragma unroll
-                for (int j = 0; j < 2; j++) h.t[j * 4 + db] += bo;
-            }
-            // FP8: the products come out scaled by the matrix's power of two s;
-            // the residual is scaled by s around them (exact)
-            if constexpr (kF8) {
-#pragma unroll
-                for (int q = 0; q < 8; q++) h.t[q] *= f8[6];
-            }
-            gemm_slots_t<kF8>(h, O0, O1, wbuf, 64);
-            if constexpr (kF8) {
-#pragma unroll
-                for (int q = 0; q < 8; q++) h.t[q] *= f8[7];
-            }
-            normalize_rows_t<kF8>(h, X0, X1);
-            if constexpr (kF8) {
-#pragma unroll
-                for (int q = 0; q < 8; q++) h.t[q] *= f8[10];
-            }
-            // FFN in four hidden chunks of 64
-            for (int chunk = 0; chunk < 4; chunk++) {
-                __syncthreads();
-                stage_rows_t(wbuf, kLdA, lw + 192 * 64 + 64 * 64 + chunk * 64 * 64, 64, 64, 64);  // w1T rows
-                stage_rows_t(wbuf + 64 * kLdA, kLdA, lw + 192 * 64 + 64 * 64 + 256 * 64 + chunk * 64, 256, 64, 64);
-                __syncthreads();
-                // f^T: lane (row c16, hidden units 16 hb + r0 + i) of the chunk
-                Tile32 f;
-#pragma unroll
-                for (int hb = 0; hb < 4; hb++) {
-                    f32x4 b1 = ld4(lv + kV_b1 + chunk * 64 + hb * 16 + r0);
-                    if constexpr (kF8) b1 *= f8[8];
-#pragma unroll
-                    for (int j = 0; j < 2; j++) f.t[j * 4 + hb] = b1;
-                }
-                gemm_slots_t<kF8>(f, X0, X1, wbuf, 64);
-#pragma unroll
-                for (int j = 0; j < 2; j++) {
-                    AT *O = (j ? O1 : O0) + c16 * kLdA + r0;
-#pragma unroll
-                    for (int hb = 0; hb < 4; hb++) {
-                        f32x4 g;
-#pragma unroll
-                        for (int i = 0; i < 4; i++) g[i] = gelu_tab(gtab, kF8 ? f.t[j * 4 + hb][i] * f8[9] : f.t[j * 4 + hb][i]);
-                        store4<kF8>(O + hb * 16, g);
-                    }
-                }
-                wave_lds_sync();
-                gemm_slots_t<kF8>(h, O0, O1, wbuf + 64 * kLdA, 64);
-            }
-            if constexpr (kF8) {
-#pragma unroll
-                for (int q = 0; q < 8; q++) h.t[q] *= f8[11];
-            }
-#pragma unroll
-            for (int db = 0; db < 4; db++) {
-                const f32x4 b2 = ld4(lv + kV_b2 + db * 16 + r0);
-#pragma unroll
-                for (int j = 0; j < 2; j++) h.t[j * 4 + db] += b2;
-            }
-        }
-        // final LayerNorm (scale folded into the head), head, mask and the
-        // log-probability of the actual token, per own slot: lane l's group of
-        // four lanes holds row c16; lanes 0..15 finish it
-#pragma unroll
-        for (int j = 0; j < 2; j++) {
-            float rstd, sh;
-            row_stats_t(h, j, rstd, sh);
-            float z[4] = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int db = 0; db < 4; db++)
-#pragma unroll
-                for (int i = 0; i < 4; i++) {
-                    const float y = fmaf(h.t[j * 4 + db][i], rstd, sh);
-                    const f32x4 hw4 = ld4(wf + M.fl.head_w + (db * 16 + r0 + i) * 4);
-#pragma unroll
-                    for (int t = 0; t < 4; t++) z[t] = fmaf(y, hw4[t], z[t]);
-                }
-#pragma unroll
-            for (int t = 0; t < 4; t++) {
-                z[t] += __shfl_xor(z[t], 16, 64);
-                z[t] += __shfl_xor(z[t], 32, 64);
-            }
-            float lsum = 0.f;
-            const int s = srb[j] * 16 + c16;
-            if (l < 16 && s < K) {
-                const uint64_t below = (1ull << s) - 1ull;  // s < K <= 64
-                const int up = __popcll(upm[j] & below), dn = __popcll(dnm[j] & below);
-                const int rem = K - 1 - s, orb = K - 1 - s;
-                float mx = -INFINITY;
-                bool ok[4];
-#pragma unroll
-                for (int t = 0; t < 4; t++) {
-                    z[t] += wf[M.fl.head_b + t] + wf[M.fl.bias + orb * 4 + t];
-                    const int bu = t & 1, bd = t >> 1;
-                    ok[t] = (up + bu <= M.n_up) && (dn + bd <= M.n_dn) && (M.n_up - up - bu <= rem) &&
-                            (M.n_dn - dn - bd <= rem);
-                    if (ok[t]) mx = fmaxf(mx, z[t]);
-                }
-                float den = 0.f;
-#pragma unroll
-                for (int t = 0; t < 4; t++)
-                    if (ok[t]) den += __expf(z[t] - mx);
-                const int ts = token(j, s);
-                const float lden = __logf(den);
-                lsum = ok[ts] ? (z[ts] - mx) - lden : -INFINITY;
-                if (!kList && A.cond_out && s == A.cond_pos && sc[j] < cpt && tb + sc[j] < cnt)
-#pragma unroll
-                    for (int t = 0; t < 4; t++)
-                        A.cond_out[(tb + sc[j]) * 4 + t] = ok[t] ? (double)((z[t] - mx) - lden) : -INFINITY;
-            }
-            // the slot's rows live in lanes 0..15
-            lsum = dpp_row_sum(lsum);
-            if (l == 0) slot_lp[2 * w + j] = (double)lsum;
-        }
-        __syncthreads();
-        // per configuration: sum of its row blocks in block order
-        if ((int)threadIdx.x < cpt && tb + (int)threadIdx.x < cnt) {
-            const int c = threadIdx.x;
-            if (kList) {
-                const int64_t e = A.list[lbase + tb + c];
-                double acc = A.pre_in[(e / A.C) * 4 + cls];
-                for (int kb = cls; kb < 4; kb++) acc += slot_lp[slot_of(cls, c, kb)];
-                A.xla[e] = 0.5 * acc;
-            } else {
-                double acc = 0.0;
-                for (int kb = 0; kb < 4; kb++) {
-                    if (A.pre_out) A.pre_out[(tb + c) * 4 + kb] = acc;
-                    acc += slot_lp[slot_of(0, c, kb)];
-                }
-                A.logabs[tb + c] = 0.5 * acc;
-            }
-        }
-        __syncthreads();  // slot_lp and the slots are reused by the next tile
-    }
-}
-
-__global__ void __launch_bounds__(512) k_transformer_bf16(Bf16View M, TfArgs A) {
-    transformer_bf16<false, false, false>(M, A, nullptr, 0);
-}
-
-__global__ void __launch_bounds__(512) k_transformer_bf16_list(Bf16View M, TfArgs A) {
-    transformer_bf16<true, false, false>(M, A, nullptr, 0);
-}
-
-__global__ void __launch_bounds__(512) k_transformer_fp8(Bf16View M, TfArgs A) {
-    transformer_bf16<false, true, false>(M, A, nullptr, 0);
-}
-
-__global__ void __launch_bounds__(512) k_transformer_fp8_list(Bf16View M, TfArgs A) {
-    transformer_bf16<true, true, false>(M, A, nullptr, 0);
-}
-
-// Many systems in one persistent launch: the list-mode work of every item
-// (its four class lists, hdr on the device) as one tile space; each block
-// takes tiles in turn and runs them with that item's model.
-__global__ void __launch_bounds__(512) k_transformer_bf16_batch(Bf16View M0, const TfItem *items, int n_items) {
-    transformer_bf16<true, false, true>(M0, items[0].A, items, n_items);
 }
 
 // Phase MLP (Section 4.1): phi = b3 + w3 . GELU(GELU(bits W1 + b1) W2 + b2)
@@ -1086,9 +236,24 @@ nnqs_status bf16_model_init(nnqs_model *m, const float *weights) {
         for (int k = 0; k < kdim; k++)
             for (int nn = 0; nn < ndim; nn++) wb[dst + (int64_t)(row0 + nn) * dst_ld + k] = to_bf16_bits(src[k * ndim + nn]);
     };
-    // FP8 copy of a [kdim][ndim] matrix, transposed like put_t, with the power
-    // of two s that brings its largest magnitude to at most 448; stores s, 1/s
-    auto put_t8 = [&](int64_t dst, int dst_ld, const float *src, int kdim, int ndim, int row0, float *sc) {
+    // Element (output n, inner k) of a transformer matrix in operand order: 16 x
+    // 32 fragments, row block major, lane (k % 32) / 8 * 16 + n % 16 of a
+    // fragment holding its eight k one after another.
+    auto frag_at = [](int kdim, int n, int k) -> int64_t {
+        return ((int64_t)((n >> 4) * (kdim / 32) + (k >> 5)) * 64 + ((k >> 3) & 3) * 16 + (n & 15)) * 8 + (k & 7);
+    };
+    // Output n's place among the rows with `pair`: output 32 p + 8 q + 4 t + i
+    // in row 4 q + i of block 2 p + t, so that the eight outputs a lane (row
+    // group q) holds of two blocks are one operand of the next product.
+    auto paired = [](int n) { return (n & ~31) | (n & 4) << 2 | (n & 24) >> 1 | (n & 3); };
+    auto put_frag = [&](int64_t dst, const float *src, int kdim, int ndim, int row0, bool pair) {
+        for (int k = 0; k < kdim; k++)
+            for (int nn = 0; nn < ndim; nn++)
+                wb[dst + frag_at(kdim, row0 + (pair ? paired(nn) : nn), k)] = to_bf16_bits(src[k * ndim + nn]);
+    };
+    // FP8 copy in the same order, with the power of two s that brings the
+    // matrix's largest magnitude to at most 448; stores s, 1/s
+    auto put_f8 = [&](int64_t dst, const float *src, int kdim, int ndim, int row0, bool pair, float *sc) {
         double mx = 0.0;
         for (int64_t e = 0; e < (int64_t)kdim * ndim; e++) mx = std::max(mx, std::fabs((double)src[e]));
         int k2 = mx > 0.0 ? (int)std::floor(std::log2(448.0 / mx)) : 0;
@@ -1096,7 +261,7 @@ nnqs_status bf16_model_init(nnqs_model *m, const float *weights) {
         const double s = std::ldexp(1.0, k2);
         for (int k = 0; k < kdim; k++)
             for (int nn = 0; nn < ndim; nn++)
-                w8[dst + (int64_t)(row0 + nn) * dst_ld + k] = to_e4m3((float)(s * src[k * ndim + nn]));
+                w8[dst + frag_at(kdim, row0 + (pair ? paired(nn) : nn), k)] = to_e4m3((float)(s * src[k * ndim + nn]));
         sc[0] = (float)s;
         sc[1] = (float)(1.0 / s);
     };
@@ -1130,25 +295,25 @@ nnqs_status bf16_model_init(nnqs_model *m, const float *weights) {
                     *b1 = w1 + kD * kF, *w2 = b1 + kF, *b2 = w2 + kF * kD;
         float *lv = wf.data() + fl.layer0 + l * fl.layer_stride;
         fold(wq, bq, ln1g, ln1b, kD, kD, qscale, fw, fb);
-        put_t(base, 64, fw.data(), kD, kD, 0);
-        put_t8(base, 64, fw.data(), kD, kD, 0, lv + kV_f8 + 0);
+        put_frag(base, fw.data(), kD, kD, 0, true);
+        put_f8(base, fw.data(), kD, kD, 0, true, lv + kV_f8 + 0);
         std::memcpy(lv + kV_bqkv, fb.data(), kD * 4);
         fold(wk, bk, ln1g, ln1b, kD, kD, 1.0, fw, fb);
-        put_t(base, 64, fw.data(), kD, kD, 64);
-        put_t8(base, 64, fw.data(), kD, kD, 64, lv + kV_f8 + 2);
+        put_frag(base, fw.data(), kD, kD, 64, true);
+        put_f8(base, fw.data(), kD, kD, 64, true, lv + kV_f8 + 2);
         std::memcpy(lv + kV_bqkv + 64, fb.data(), kD * 4);
         fold(wv, bv, ln1g, ln1b, kD, kD, 1.0, fw, fb);
-        put_t(base, 64, fw.data(), kD, kD, 128);
-        put_t8(base, 64, fw.data(), kD, kD, 128, lv + kV_f8 + 4);
+        put_frag(base, fw.data(), kD, kD, 128, false);
+        put_f8(base, fw.data(), kD, kD, 128, false, lv + kV_f8 + 4);
         std::memcpy(lv + kV_bqkv + 128, fb.data(), kD * 4);
-        put_t(base + 192 * 64, 64, wo, kD, kD, 0);
-        put_t8(base + 192 * 64, 64, wo, kD, kD, 0, lv + kV_f8 + 6);
+        put_frag(base + 192 * 64, wo, kD, kD, 0, false);
+        put_f8(base + 192 * 64, wo, kD, kD, 0, false, lv + kV_f8 + 6);
         fold(w1, b1, ln2g, ln2b, kD, kF, 1.0, fw, fb);
-        put_t(base + 192 * 64 + 64 * 64, 64, fw.data(), kD, kF, 0);
-        put_t8(base + 192 * 64 + 64 * 64, 64, fw.data(), kD, kF, 0, lv + kV_f8 + 8);
+        put_frag(base + 192 * 64 + 64 * 64, fw.data(), kD, kF, 0, true);
+        put_f8(base + 192 * 64 + 64 * 64, fw.data(), kD, kF, 0, true, lv + kV_f8 + 8);
         std::memcpy(lv + kV_b1, fb.data(), kF * 4);
-        put_t(base + 192 * 64 + 64 * 64 + 256 * 64, 256, w2, kF, kD, 0);
-        put_t8(base + 192 * 64 + 64 * 64 + 256 * 64, 256, w2, kF, kD, 0, lv + kV_f8 + 10);
+        put_frag(base + 192 * 64 + 64 * 64 + 256 * 64, w2, kF, kD, 0, false);
+        put_f8(base + 192 * 64 + 64 * 64 + 256 * 64, w2, kF, kD, 0, false, lv + kV_f8 + 10);
         std::memcpy(lv + kV_ln1_g, ln1g, kD * 4);
         std::memcpy(lv + kV_ln1_b, ln1b, kD * 4);
         std::memcpy(lv + kV_bo, bo, kD * 4);
@@ -1203,11 +368,11 @@ static int cu_count() {
     return cus;
 }
 
-// One block per CU is resident (the slots take 157 KB of LDS); blocks loop
-// over tiles.
-static unsigned tf_grid(int64_t tiles) {
+// One block per CU is resident (the weights take 108 KB of LDS); blocks loop
+// over tiles, of at least one configuration each.
+static unsigned tf_grid(int64_t n) {
     const int64_t cap = cu_count();
-    return (unsigned)(tiles < 1 ? 1 : tiles < cap ? tiles : cap);
+    return (unsigned)(n < 1 ? 1 : n < cap ? n : cap);
 }
 
 static unsigned phase_grid(int64_t n) {
@@ -1226,10 +391,10 @@ nnqs_status enqueue_logpsi_bf16(const nnqs_model *m, const uint64_t *keys, int64
     A.logabs = logabs;
     if (fp8) {
         TimedRegion tr("k_transformer_fp8", st);
-        hipLaunchKernelGGL(k_transformer_fp8, dim3(tf_grid((n + 3) / 4)), dim3(512), 0, st, v, A);
+        tf_launch_sample(true, tf_grid(n), st, v, A);
     } else {
         TimedRegion tr("k_transformer_bf16", st);
-        hipLaunchKernelGGL(k_transformer_bf16, dim3(tf_grid((n + 3) / 4)), dim3(512), 0, st, v, A);
+        tf_launch_sample(false, tf_grid(n), st, v, A);
     }
     {
         TimedRegion tr("k_phase_bf16", st);
@@ -1249,12 +414,12 @@ nnqs_status enqueue_bf16_cond(const nnqs_model *m, const uint64_t *keys, int64_t
     A.cond_pos = cpos;
     A.cond_out = cond;
     TimedRegion tr("k_transformer_bf16", st);
-    hipLaunchKernelGGL(k_transformer_bf16, dim3(tf_grid((n + 3) / 4)), dim3(512), 0, st, bf16_view(m), A);
+    tf_launch_sample(false, tf_grid(n), st, bf16_view(m), A);
     NNQS_HIP_CHECK(hipGetLastError());
     return NNQS_OK;
 }
 
-int64_t bf16_cache_elems(const nnqs_model *m) { return (int64_t)m->desc.n_layers * kH * kKvPerHead; }
+int64_t bf16_cache_elems(const nnqs_model *m) { return (int64_t)m->desc.n_layers * (kH / 2) * kKvPerPair; }
 
 nnqs_status enqueue_bf16_cached(const nnqs_model *m, const uint64_t *keys, int64_t n, double *logabs, __bf16 *kv,
                                 double *pre, hipStream_t st, bool fp8) {
@@ -1267,10 +432,10 @@ nnqs_status enqueue_bf16_cached(const nnqs_model *m, const uint64_t *keys, int64
     A.pre_out = pre;
     if (fp8) {
         TimedRegion tr("k_transformer_fp8", st);
-        hipLaunchKernelGGL(k_transformer_fp8, dim3(tf_grid((n + 3) / 4)), dim3(512), 0, st, bf16_view(m), A);
+        tf_launch_sample(true, tf_grid(n), st, bf16_view(m), A);
     } else {
         TimedRegion tr("k_transformer_bf16", st);
-        hipLaunchKernelGGL(k_transformer_bf16, dim3(tf_grid((n + 3) / 4)), dim3(512), 0, st, bf16_view(m), A);
+        tf_launch_sample(false, tf_grid(n), st, bf16_view(m), A);
     }
     NNQS_HIP_CHECK(hipGetLastError());
     return NNQS_OK;
@@ -1292,10 +457,10 @@ nnqs_status enqueue_bf16_list(const nnqs_model *m, const uint64_t *xkeys, int64_
     A.list_mode = 1;  // kv_out / pre_out stay null: list mode only reads the cache
     if (fp8) {
         TimedRegion tr("k_transformer_fp8_list", st);
-        hipLaunchKernelGGL(k_transformer_fp8_list, dim3(tf_grid((max_entries + 3) / 4)), dim3(512), 0, st, v, A);
+        tf_launch_list(true, tf_grid(max_entries), st, v, A);
     } else {
         TimedRegion tr("k_transformer_bf16_list", st);
-        hipLaunchKernelGGL(k_transformer_bf16_list, dim3(tf_grid((max_entries + 3) / 4)), dim3(512), 0, st, v, A);
+        tf_launch_list(false, tf_grid(max_entries), st, v, A);
     }
     {
         TimedRegion tr("k_phase_bf16", st);
@@ -1339,8 +504,7 @@ nnqs_status enqueue_bf16_phase_list(const nnqs_model *m, const uint64_t *xkeys, 
 
 nnqs_status enqueue_bf16_batch(const nnqs_model *m0, const void *d_items, int n_items, hipStream_t st) {
     TimedRegion tr("k_transformer_bf16_batch", st);
-    hipLaunchKernelGGL(k_transformer_bf16_batch, dim3((unsigned)cu_count()), dim3(512), 0, st, bf16_view(m0),
-                       static_cast<const TfItem *>(d_items), n_items);
+    tf_launch_batch((unsigned)cu_count(), st, bf16_view(m0), static_cast<const TfItem *>(d_items), n_items);
     NNQS_HIP_CHECK(hipGetLastError());
     return NNQS_OK;
 }
