@@ -219,7 +219,7 @@ extern "C" nnqs_status nnqs_bas(nnqs_model *model, int32_t precision, uint64_t s
     hipLaunchKernelGGL(k_bas_init, dim3(1), dim3(1), 0, st, S.pk, S.pc, S.pl, (uint64_t)n_samples);
     int64_t n = 1;
     for (int s = 0; s < K; s++) {
-        nnqs_status r = precision == NNQS_FP64 ? enqueue_logpsi_f64(model, S.pk, n, S.la, S.ph, st, s, S.cond)
+        nnqs_status r = precision == NNQS_FP64 ? enqueue_logpsi_f64(model, S.pk, n, S.la, nullptr, st, s, S.cond)
                                                : enqueue_bf16_cond(model, S.pk, n, s, S.cond, S.la, st);
         if (r != NNQS_OK) return r;
         hipLaunchKernelGGL((k_bas_scan<uint64_t, CountOf>), dim3(1), dim3(1024), 0, st, n, CountOf{S.pc}, S.offs);

@@ -684,7 +684,7 @@ extern "C" nnqs_status nnqs_eloc_model(const nnqs_system *sys, nnqs_model *model
             grow(reinterpret_cast<void **>(&model->d_kv64), (size_t)chunk * f64_cache_doubles(model) * sizeof(double));
         if (s1 == NNQS_OK)
             s1 = grow(reinterpret_cast<void **>(&model->d_pre64),
-                      (size_t)chunk * (sys->view.K + 1) * sizeof(double));
+                      (size_t)chunk * 4 * sizeof(double));
         if (s1 != NNQS_OK) {
             eloc_model_free(model);
             return s1;
@@ -868,8 +868,8 @@ extern "C" nnqs_status nnqs_eloc_model(const nnqs_system *sys, nnqs_model *model
             NNQS_HIP_CHECK(hipStreamSynchronize(st));
             const int64_t nref = rh[0] + rh[1] + rh[2] + rh[3];
             refined += nref;
-            s1 = enqueue_f64_list(model, model->d_xkeys, C, rlist, nref, keys + 2 * s0, model->d_kv64,
-                                  model->d_pre64, model->d_xla, model->d_xph, st);
+            s1 = enqueue_f64_list(model, model->d_xkeys, C, rlist, d_rhdr, nref, model->d_kv64, model->d_pre64,
+                                  model->d_xla, model->d_xph, st);
             if (s1 != NNQS_OK) return s1;
             if (dedup) {
                 hipLaunchKernelGGL(k_dd_scatter, dim3((unsigned)((n_kept + 255) / 256)), dim3(256), 0, st,

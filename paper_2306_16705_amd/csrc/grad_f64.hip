@@ -648,7 +648,9 @@ nnqs_status nnqs_model_adamw_step(nnqs_model *m, const double *grad, int64_t ste
     hipLaunchKernelGGL(kg_adamw, dim3(nblocks(nw)), dim3(256), 0, st, m->d_w64, grad, mom1, mom2, nw, m->off.bias,
                        m->off.bias + 4 * (int64_t)m->desc.n_orb, lr, beta1, beta2, eps, weight_decay, bc1, bc2);
     NNQS_HIP_CHECK(hipGetLastError());
-    // the reduced-precision copies follow the FP64 master weights
+    // the packed and reduced-precision copies follow the FP64 master weights
+    const nnqs_status ps = f64_model_pack(m, st);
+    if (ps != NNQS_OK) return ps;
     NNQS_HIP_CHECK(hipStreamSynchronize(st));
     std::vector<double> w64((size_t)nw);
     NNQS_HIP_CHECK(hipMemcpy(w64.data(), m->d_w64, nw * sizeof(double), hipMemcpyDeviceToHost));

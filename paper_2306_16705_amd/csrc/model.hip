@@ -260,7 +260,9 @@ nnqs_status nnqs_model_create(nnqs_model **out, const nnqs_model_desc *desc, con
         nnqs_model_destroy(m);
         return fail(NNQS_EHIP, "copy of the model weights failed");
     }
-    nnqs_status st = bf16_model_init(m, weights);
+    nnqs_status st = f64_model_pack(m, nullptr);
+    if (st == NNQS_OK && hipStreamSynchronize(nullptr) != hipSuccess) st = fail(NNQS_EHIP, "packing of the model weights failed");
+    if (st == NNQS_OK) st = bf16_model_init(m, weights);
     if (st != NNQS_OK) {
         nnqs_model_destroy(m);
         return st;
@@ -272,6 +274,7 @@ nnqs_status nnqs_model_create(nnqs_model **out, const nnqs_model_desc *desc, con
 nnqs_status nnqs_model_destroy(nnqs_model *m) {
     if (!m) return NNQS_OK;
     hipFree(m->d_w64);
+    hipFree(m->d_w64p);
     hipFree(m->d_f64s);
     hipFree(m->d_grads);
     bf16_model_free(m);

@@ -52,6 +52,7 @@ struct nnqs_model {
     nnqs_model_desc desc{};
     nnqs::ModelOffsets off{};
     double *d_w64 = nullptr;
+    double *d_w64p = nullptr;  // the layers' weights in the FP64 transformer's operand order (transformer_f64.hip)
     int max_lds = 0;
     // scratch of the layer-batched FP64 forward (model_f64.hip), grown on demand
     void *d_f64s = nullptr;
@@ -139,6 +140,8 @@ nnqs_status enqueue_bf16_list(const nnqs_model *m, const uint64_t *xkeys, int64_
                               double *xla, double *xph, hipStream_t st, bool fp8);
 void eloc_model_free(nnqs_model *m);
 bool f64_shape_ok(const nnqs_model_desc &m);
+// Allocates (first call) and fills the packed copy of the FP64 weights from the master weights.
+nnqs_status f64_model_pack(nnqs_model *m, hipStream_t st);
 // FP64 forward; with cond, also the masked conditionals of position cpos
 // into cond[n][4] (batch sampling).
 nnqs_status enqueue_logpsi_f64(const nnqs_model *m, const uint64_t *keys, int64_t n, double *logabs, double *phase,
@@ -154,9 +157,9 @@ int64_t f64_cache_doubles(const nnqs_model *m);
 // sk[2 i + 1] (word 1 major) with 32-bit payloads si[i] as the final
 // tie-break, in place (nnqs_core.hip).
 void bitonic_sort128(uint64_t *sk, uint32_t *si, int64_t P, hipStream_t st);
-nnqs_status enqueue_f64_list(const nnqs_model *m, const uint64_t *xkeys, int64_t C, const int32_t *list, int64_t n,
-                             const uint64_t *keys, const double *kvc, const double *pre, double *xla, double *xph,
-                             hipStream_t st);
+nnqs_status enqueue_f64_list(const nnqs_model *m, const uint64_t *xkeys, int64_t C, const int32_t *list,
+                             const int64_t *hdr, int64_t n, const double *kvc, const double *pre, double *xla,
+                             double *xph, hipStream_t st);
 nnqs_status screen_infer(nnqs_screen *s, const uint64_t *keys, const uint8_t *exc, int64_t n, float *pred,
                          hipStream_t st, bool fp8);
 }  // namespace nnqs

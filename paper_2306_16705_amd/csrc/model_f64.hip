@@ -1,12 +1,10 @@
-// FP64 network forward, layer by layer over batches of configurations (the
-// ansatz of Section 3.1, Eq. 11 and Fig. 2, with the Eq. 12 mask and the
-// phase MLP of Section 4.1).  Every step is a plain kernel over the rows of
-// a whole batch: LayerNorm one wave per row, the dense layers an LDS-tiled
-// FP64 MFMA product (64 x 64 output tile per block) with bias, GELU or
-// residual-add epilogues, causal attention on FP64 MFMA one wave per
-// (configuration, head).  Activations live in model-owned scratch between steps.
-// The arithmetic is the FP64 definition of the network; only the summation
-// order differs from a one-configuration-at-a-time evaluation.
+// The FP64 network: entry points (the transformer in one launch,
+// transformer_f64.hip; the phase MLP of Section 4.1 here), and the layer-wise
+// kernels of the gradient's forward, which keeps every activation: LayerNorm
+// one wave per row, the dense layers an LDS-tiled FP64 MFMA product (64 x 64
+// output tile per block) with bias, GELU or residual-add epilogues, causal
+// attention on FP64 MFMA one wave per (configuration, head).  Only the
+// summation order differs from a one-configuration-at-a-time evaluation.
 #include <cmath>
 #include <climits>
 #include <vector>
@@ -416,20 +414,37 @@ __global__ void __launch_bounds__(256) k64_head(ModelView M, const double *__res
 }
 
 // First phase layer from the occupation bits: z1[b][j] = GELU(b1[j] + sum
-// over set bits p of W1[p][j]).
-__global__ void k64_phase1(ModelView M, const uint64_t *__restrict__ keys, int64_t B, double *__restrict__ z1) {
+// over set bits p of W1[p][j]); configuration b is keys[b], or keys[list[b]].
+__global__ void k64_phase1(ModelView M, const uint64_t *__restrict__ keys, const int32_t *__restrict__ list, int64_t B,
+                           double *__restrict__ z1) {
     const int P = M.P;
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= B * P) return;
     const int64_t b = e / P;
     const int j = (int)(e - b * P);
+    const int64_t kb = list ? list[b] : b;
     Key x;
-    x.lo = keys[2 * b];
-    x.hi = keys[2 * b + 1];
+    x.lo = keys[2 * kb];
+    x.hi = keys[2 * kb + 1];
     double acc = M.w64[M.off.ph_b1 + j];
     for (int p = 0; p < 2 * M.K; p++)
         if (key_bit(x, p)) acc += M.w64[M.off.ph_w1 + (int64_t)p * P + j];
     z1[e] = gelu_f64(acc);
+}
+
+// Phase of each configuration, b3 + z2 . w3 (one wave each, fixed-order lane
+// sums), to phase[b] or phase[list[b]].
+__global__ void __launch_bounds__(256) k64_phase_out(ModelView M, const double *__restrict__ z2,
+                                                     const int32_t *__restrict__ list, int64_t B,
+                                                     double *__restrict__ phase) {
+    const int lane = threadIdx.x & 63;
+    const int64_t b = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    if (b >= B) return;
+    double ph = 0.0;
+    for (int i = lane; i < M.P; i += 64) ph += z2[b * M.P + i] * M.w64[M.off.ph_w3 + i];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) ph += __shfl_xor(ph, off, 64);
+    if (lane == 0) phase[list ? list[b] : b] = M.w64[M.off.ph_b3] + ph;
 }
 
 // Per configuration: log|psi| = 1/2 sum_s lp, phase = b3 + z2 . w3 (one wave
@@ -453,99 +468,6 @@ __global__ void __launch_bounds__(256) k64_finish(ModelView M, const double *__r
         logabs[b] = 0.5 * s;
         phase[b] = M.w64[M.off.ph_b3] + ph;
     }
-}
-
-// ------------------------------------------------ prefix reuse in FP64
-// Cache of a configuration's forward for the prefix-reusing evaluation of its
-// connections: per configuration [L][2][K][64] doubles, every layer's keys
-// then values (all heads, as the attention used them), and pre[K + 1] with
-// pre[s] = sum_{t < s} log pi_t.  By causality of the attention and of the
-// autoregressive product of Eq. 8, a connected x' whose first changed
-// position is s0 has the same rows s <= s0 as its sample, so its forward can
-// start at row s0 from the cache.
-__global__ void k64_cache_kv(const double *__restrict__ kk, const double *__restrict__ v, int64_t B, int K, int l,
-                             int L, double *__restrict__ kvc) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t per = (int64_t)K * 64;
-    if (e >= B * per) return;
-    const int64_t b = e / per, r = e - b * per;
-    double *dst = kvc + ((b * L + l) * 2) * per + r;
-    dst[0] = kk[e];
-    dst[per] = v[e];
-}
-
-__global__ void k64_prefix(const double *__restrict__ lp, int64_t B, int K, double *__restrict__ pre) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    double s = 0.0;
-    for (int t = 0; t < K; t++) {
-        pre[b * (K + 1) + t] = s;
-        s += lp[b * K + t];
-    }
-    pre[b * (K + 1) + K] = s;
-}
-
-// First changed sequence position of x' against its sample x (position s
-// holds orbital K-1-s); the sample itself restarts at the last position.
-__device__ __forceinline__ int first_change(int K, const uint64_t *x, const uint64_t *xp) {
-    const uint64_t d0 = x[0] ^ xp[0], d1 = x[1] ^ xp[1];
-    if (!d0 && !d1) return K - 1;
-    const int p = d1 ? 127 - __clzll(d1) : 63 - __clzll(d0);
-    return K - 1 - (p >> 1);
-}
-
-// Per listed connection i (x' = xkeys[list[i]], sample list[i] / C of the
-// chunk): its start s0 and row count K - s0.
-__global__ void k64x_count(const uint64_t *__restrict__ xkeys, const int32_t *__restrict__ list, int64_t n,
-                           const uint64_t *__restrict__ keys, int64_t C, int K, int32_t *__restrict__ s0v,
-                           int32_t *__restrict__ rows) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int64_t e = list[i];
-    const int s0 = first_change(K, keys + 2 * (e / C), xkeys + 2 * e);
-    s0v[i] = s0;
-    rows[i] = K - s0;
-}
-
-// Row maps of one batch of B listed connections: rows off[i] - off0 ..
-// + K - s0[i] belong to connection i, position s0[i] + j; and the batch's
-// keys gathered into ckeys.
-__global__ void k64x_rowmap(const uint64_t *__restrict__ xkeys, const int32_t *__restrict__ list,
-                            const int32_t *__restrict__ s0v, const int32_t *__restrict__ off, int32_t off0, int64_t B,
-                            int K, int32_t *__restrict__ row_cfg, int32_t *__restrict__ row_pos,
-                            uint64_t *__restrict__ ckeys) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B) return;
-    const int s0 = s0v[i];
-    const int r0 = off[i] - off0;
-    for (int j = 0; j < K - s0; j++) {
-        row_cfg[r0 + j] = (int32_t)i;
-        row_pos[r0 + j] = s0 + j;
-    }
-    const int64_t e = list[i];
-    ckeys[2 * i] = xkeys[2 * e];
-    ckeys[2 * i + 1] = xkeys[2 * e + 1];
-}
-
-// Embeddings of the mapped rows: h[r][c] = tok_emb[token at s-1][c] + pos_emb[s][c].
-__global__ void k64x_embed(ModelView M, const uint64_t *__restrict__ ckeys, const int32_t *__restrict__ row_cfg,
-                           const int32_t *__restrict__ row_pos, int64_t R, double *__restrict__ h) {
-    const int K = M.K, d = M.d;
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= R * d) return;
-    const int64_t row = e / d;
-    const int c = (int)(e - row * d);
-    const int64_t i = row_cfg[row];
-    const int s = row_pos[row];
-    Key x;
-    x.lo = ckeys[2 * i];
-    x.hi = ckeys[2 * i + 1];
-    int prev = 4;
-    if (s > 0) {
-        const int o = K - s;  // orbital of position s - 1
-        prev = key_bit(x, 2 * o) + 2 * key_bit(x, 2 * o + 1);
-    }
-    h[e] = M.w64[M.off.tok_emb + prev * d + c] + M.w64[M.off.pos_emb + (int64_t)s * d + c];
 }
 
 // Causal attention of the mapped rows on FP64 MFMA (the tiling of
@@ -645,252 +567,74 @@ k64x_attention(const double *__restrict__ q, const double *__restrict__ k, const
     }
 }
 
-// Output head of the mapped rows (as k64_head): one wave per row; the
-// electrons placed before position s are counted from the key.
-__global__ void __launch_bounds__(256) k64x_head(ModelView M, const double *__restrict__ a,
-                                                 const uint64_t *__restrict__ ckeys,
-                                                 const int32_t *__restrict__ row_cfg,
-                                                 const int32_t *__restrict__ row_pos, int64_t R,
-                                                 double *__restrict__ lp) {
-    const int K = M.K;
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (row >= R) return;  // wave-uniform
-    const int64_t i = row_cfg[row];
-    const int s = row_pos[row];
-    Key x;
-    x.lo = ckeys[2 * i];
-    x.hi = ckeys[2 * i + 1];
-    auto token = [&](int pos) {
-        const int oo = K - 1 - pos;
-        return key_bit(x, 2 * oo) + 2 * key_bit(x, 2 * oo + 1);
-    };
-    const int tr = lane < s ? token(lane) : 0;
-    const int up = __popcll(__ballot(tr & 1)), dn = __popcll(__ballot(tr >> 1));
-    const double *W = M.w64;
-    const double av = a[row * 64 + lane];
-    double z[4];
-#pragma unroll
-    for (int t = 0; t < 4; t++) {
-        double vv = av * W[M.off.head_w + lane * 4 + t];
-#pragma unroll
-        for (int off2 = 32; off2 >= 1; off2 >>= 1) vv += __shfl_xor(vv, off2, 64);
-        z[t] = vv;
-    }
-    if (lane != 0) return;
-    const int rem = K - 1 - s, orb = K - 1 - s;
-    bool ok[4];
-    double mx = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < 4; t++) {
-        z[t] += W[M.off.head_b + t] + W[M.off.bias + orb * 4 + t];
-        const int bu = t & 1, bd = t >> 1;
-        ok[t] = (up + bu <= M.n_up) && (dn + bd <= M.n_dn) && (M.n_up - up - bu <= rem) && (M.n_dn - dn - bd <= rem);
-        if (ok[t] && z[t] > mx) mx = z[t];
-    }
-    double den = 0.0;
-#pragma unroll
-    for (int t = 0; t < 4; t++)
-        if (ok[t]) den += exp(z[t] - mx);
-    const int ts = token(s);
-    lp[row] = ok[ts] ? (z[ts] - mx) - log(den) : -INFINITY;
-}
-
-// Per listed connection: log|psi| = 1/2 (pre[sample][s0] + sum of its rows'
-// log pi), phase = b3 + z2 . w3, written to xla / xph at list[i] (one wave each).
-__global__ void __launch_bounds__(256) k64x_finish(ModelView M, const double *__restrict__ lp,
-                                                   const double *__restrict__ z2, const double *__restrict__ pre,
-                                                   const int32_t *__restrict__ list,
-                                                   const int32_t *__restrict__ s0v,
-                                                   const int32_t *__restrict__ off, int32_t off0, int64_t C,
-                                                   int64_t B, double *__restrict__ xla, double *__restrict__ xph) {
-    const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (i >= B) return;
-    const int K = M.K, s0 = s0v[i];
-    const int64_t r0 = off[i] - off0;
-    double s = 0.0;
-    for (int t = lane; t < K - s0; t += 64) s += lp[r0 + t];
-    double ph = 0.0;
-    for (int j = lane; j < M.P; j += 64) ph += z2[i * M.P + j] * M.w64[M.off.ph_w3 + j];
-#pragma unroll
-    for (int off2 = 32; off2 >= 1; off2 >>= 1) {
-        s += __shfl_xor(s, off2, 64);
-        ph += __shfl_xor(ph, off2, 64);
-    }
-    if (lane == 0) {
-        const int64_t e = list[i];
-        xla[e] = 0.5 * (pre[(e / C) * (K + 1) + s0] + s);
-        xph[e] = M.w64[M.off.ph_b3] + ph;
-    }
-}
-
 static unsigned blocks_for(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
-int64_t f64_cache_doubles(const nnqs_model *m) { return (int64_t)m->desc.n_layers * 2 * m->desc.n_orb * 64; }
-
 bool f64_shape_ok(const nnqs_model_desc &m) { return m.d_model == 64 && m.n_heads == 4 && m.d_ff % 64 == 0; }
+
+nnqs_status f64_model_pack(nnqs_model *m, hipStream_t st) {
+    if (!f64_shape_ok(m->desc)) return NNQS_OK;
+    if (!m->d_w64p && hipMalloc(&m->d_w64p, f64_packed_bytes(m->desc)) != hipSuccess)
+        return fail(NNQS_ENOMEM, "device allocation of the packed model failed");
+    f64_pack(model_view(m), m->d_w64p, st);
+    NNQS_HIP_CHECK(hipGetLastError());
+    return NNQS_OK;
+}
+
+// Phase MLP of n configurations (keys, or keys[list]) in passes of kF64Batch.
+static nnqs_status enqueue_phase_f64(nnqs_model *m, const uint64_t *keys, const int32_t *list, int64_t n, double *phase,
+                                     hipStream_t st) {
+    const ModelView M = model_view(m);
+    const int P = M.P;
+    const int64_t Bmax = n < kF64Batch ? n : kF64Batch;
+    const size_t need = (size_t)Bmax * 2 * P * sizeof(double);
+    if (m->f64cap < need) {
+        NNQS_HIP_CHECK(hipStreamSynchronize(st));
+        hipFree(m->d_f64s);
+        m->d_f64s = nullptr;
+        m->f64cap = 0;
+        if (hipMalloc(&m->d_f64s, need) != hipSuccess) return fail(NNQS_ENOMEM, "FP64 forward scratch (%zu bytes)", need);
+        m->f64cap = need;
+    }
+    double *z1 = reinterpret_cast<double *>(m->d_f64s), *z2 = z1 + (size_t)Bmax * P;
+    const double *W = m->d_w64;
+    for (int64_t b0 = 0; b0 < n; b0 += kF64Batch) {
+        const int64_t B = n - b0 < kF64Batch ? n - b0 : kF64Batch;
+        const uint64_t *kb = list ? keys : keys + 2 * b0;
+        const int32_t *lb = list ? list + b0 : nullptr;
+        hipLaunchKernelGGL(k64_phase1, dim3(blocks_for(B * P)), dim3(256), 0, st, M, kb, lb, B, z1);
+        hipLaunchKernelGGL(k64_gemm<2>, dim3((unsigned)((P + 63) / 64), (unsigned)((B + 63) / 64)), dim3(256), 0, st,
+                           z1, P, W + M.off.ph_w2, P, W + M.off.ph_b2, B, P, P, z2, P);
+        hipLaunchKernelGGL(k64_phase_out, dim3(blocks_for(B, 4)), dim3(256), 0, st, M, z2, lb, B,
+                           list ? phase : phase + b0);
+    }
+    NNQS_HIP_CHECK(hipGetLastError());
+    return NNQS_OK;
+}
 
 nnqs_status enqueue_logpsi_f64(const nnqs_model *cm, const uint64_t *keys, int64_t n, double *logabs,
                                double *phase, hipStream_t st, int cpos, double *cond, double *kvc, double *pre) {
     nnqs_model *m = const_cast<nnqs_model *>(cm);  // owns its scratch (one call at a time per model)
-    const ModelView M = model_view(m);
-    const int K = M.K, d = M.d, F = M.F, P = M.P;
-    const int64_t Bmax = n < kF64Batch ? n : kF64Batch;
-    const int64_t rows_max = Bmax * K;
-    // h, a, q, k, v [rows][64]; f [rows][F] (also z1, z2 [B][P]); lp [rows]; LayerNorm statistics [rows][2];
-    // tok [rows]
-    const size_t need = (size_t)rows_max * (5 * d + (F > 2 * P / K + 1 ? F : 2 * P / K + 1) + 3) * 8 + rows_max + 256;
-    if (m->f64cap < need) {
-        NNQS_HIP_CHECK(hipStreamSynchronize(st));
-        hipFree(m->d_f64s);
-        m->d_f64s = nullptr;
-        m->f64cap = 0;
-        if (hipMalloc(&m->d_f64s, need) != hipSuccess) return fail(NNQS_ENOMEM, "FP64 forward scratch (%zu bytes)", need);
-        m->f64cap = need;
-    }
-    const size_t fcols = (size_t)(F > 2 * P / K + 1 ? F : 2 * P / K + 1);
-    double *h = reinterpret_cast<double *>(m->d_f64s);
-    double *a = h + rows_max * d, *q = a + rows_max * d, *kk = q + rows_max * d, *v = kk + rows_max * d;
-    double *f = v + rows_max * d;
-    double *lp = f + rows_max * fcols, *lst = lp + rows_max;
-    int8_t *tok = reinterpret_cast<int8_t *>(lst + 2 * rows_max);
-    const LayerOffsets LO = layer_offsets(d, F);
-    const double *W = m->d_w64;
-    const double scale = 1.0 / sqrt((double)(d / M.H));
-    for (int64_t b0 = 0; b0 < n; b0 += kF64Batch) {
-        const int64_t B = n - b0 < kF64Batch ? n - b0 : kF64Batch;
-        const int64_t R = B * K;
-        const unsigned gy = (unsigned)((R + 63) / 64);
-        hipLaunchKernelGGL(k64_embed, dim3(blocks_for(R * d)), dim3(256), 0, st, M, keys + 2 * b0, B, tok, h);
-        for (int l = 0; l < M.L; l++) {
-            const double *Lw = W + M.off.layer0 + (int64_t)l * M.off.layer_stride;
-            if (l == 0)  // later layers: the statistics come with the previous FFN output
-                hipLaunchKernelGGL(k64_ln_stats, dim3(blocks_for(R, 4)), dim3(256), 0, st, h, R, lst);
-            hipLaunchKernelGGL(k64_gemm_qkv, dim3(3, gy), dim3(256), 0, st, h, Lw + LO.wq, Lw + LO.bq,
-                               LO.wk - LO.wq, R, q, (int64_t)(kk - q), lst, Lw + LO.ln1_g, Lw + LO.ln1_b);
-            if (kvc)
-                hipLaunchKernelGGL(k64_cache_kv, dim3(blocks_for(R * 64)), dim3(256), 0, st, kk, v, B, K, l, M.L,
-                                   kvc + b0 * M.L * 2 * K * 64);
-            hipLaunchKernelGGL(k64_attention, dim3((unsigned)B), dim3(256), 0, st, q, kk, v, B, K, scale, a);
-            hipLaunchKernelGGL(k64_gemm_res<64>, dim3(1, gy), dim3(256), 0, st, a, 64, Lw + LO.wo, Lw + LO.bo, R, h,
-                               lst);
-            hipLaunchKernelGGL(k64_gemm_ln<2>, dim3((unsigned)((F + 63) / 64), gy), dim3(256), 0, st, h, Lw + LO.w1, F,
-                               Lw + LO.b1, R, F, f, (int)fcols, lst, Lw + LO.ln2_g, Lw + LO.ln2_b);
-            ffn_out(f, (int)fcols, Lw + LO.w2, Lw + LO.b2, R, F, h, lst, st);
-        }
-        hipLaunchKernelGGL(k64_layernorm, dim3(blocks_for(R, 4)), dim3(256), 0, st, h, W + M.off.lnf_g,
-                           W + M.off.lnf_b, R, a);
-        hipLaunchKernelGGL(k64_head, dim3(blocks_for(R, 4)), dim3(256), 0, st, M, a, tok, B, lp, cpos,
-                           cond ? cond + 4 * b0 : (double *)nullptr);
-        if (pre)
-            hipLaunchKernelGGL(k64_prefix, dim3(blocks_for(B)), dim3(256), 0, st, lp, B, K,
-                               pre + (int64_t)(K + 1) * b0);
-        double *z1 = f, *z2 = f + (size_t)B * P;
-        hipLaunchKernelGGL(k64_phase1, dim3(blocks_for(B * P)), dim3(256), 0, st, M, keys + 2 * b0, B, z1);
-        hipLaunchKernelGGL(k64_gemm<2>, dim3((unsigned)((P + 63) / 64), (unsigned)((B + 63) / 64)), dim3(256), 0, st,
-                           z1, P, W + M.off.ph_w2, P, W + M.off.ph_b2, B, P, P, z2, P);
-        hipLaunchKernelGGL(k64_finish, dim3(blocks_for(B, 4)), dim3(256), 0, st, M, lp, z2, B, logabs + b0,
-                           phase + b0);
-        NNQS_HIP_CHECK(hipGetLastError());
-    }
-    return NNQS_OK;
+    transformer_f64_sample(model_view(m), m->d_w64p, keys, n, logabs, cpos, cond, kvc, pre, st);
+    NNQS_HIP_CHECK(hipGetLastError());
+    return phase ? enqueue_phase_f64(m, keys, nullptr, n, phase, st) : NNQS_OK;
 }
 
-// FP64 forward of n listed connections with prefix reuse (see k64_cache_kv):
-// each x' runs only its rows from its first changed position s0 on (the
-// sample itself: the last row), in batches of up to kF64Batch connections
-// whose rows are packed one after another; kvc / pre: the cache of the
-// chunk's samples (keys [m][2]), indexed by list entry / C.  Results go to
-// xla / xph.  Synchronises `st` once (the row counts set the batches).
-nnqs_status enqueue_f64_list(const nnqs_model *cm, const uint64_t *xkeys, int64_t C, const int32_t *list, int64_t n,
-                             const uint64_t *keys, const double *kvc, const double *pre, double *xla, double *xph,
-                             hipStream_t st) {
+// FP64 forward of n listed connections (sorted by first changed row block,
+// hdr on the device) with prefix reuse from the cache kvc / pre of the
+// chunk's samples, indexed by list entry / C.  Results go to xla / xph.
+nnqs_status enqueue_f64_list(const nnqs_model *cm, const uint64_t *xkeys, int64_t C, const int32_t *list,
+                             const int64_t *hdr, int64_t n, const double *kvc, const double *pre, double *xla,
+                             double *xph, hipStream_t st) {
     if (n <= 0) return NNQS_OK;
     nnqs_model *m = const_cast<nnqs_model *>(cm);
-    const ModelView M = model_view(m);
-    const int K = M.K, d = M.d, F = M.F, P = M.P;
-    // per-connection starts and row counts, then their offsets (host scan);
-    // offsets are 32-bit (a chunk holds at most 2^24 connections of <= 64 rows)
-    if (n * K > (int64_t)INT32_MAX)
-        return fail(NNQS_EINVAL, "%lld refined connections exceed 32-bit row offsets", (long long)n);
-    const size_t rag_need = (size_t)(3 * n + 1) * sizeof(int32_t);
-    if (m->ragcap < rag_need) {
-        NNQS_HIP_CHECK(hipStreamSynchronize(st));
-        hipFree(m->d_rag);
-        m->d_rag = nullptr;
-        m->ragcap = 0;
-        if (hipMalloc(&m->d_rag, rag_need) != hipSuccess) return fail(NNQS_ENOMEM, "row maps (%zu bytes)", rag_need);
-        m->ragcap = rag_need;
-    }
-    int32_t *s0v = reinterpret_cast<int32_t *>(m->d_rag), *rows = s0v + n, *off = rows + n;
-    hipLaunchKernelGGL(k64x_count, dim3(blocks_for(n)), dim3(256), 0, st, xkeys, list, n, keys, C, K, s0v, rows);
+    transformer_f64_list(model_view(m), m->d_w64p, xkeys, C, list, hdr, n, kvc, pre, xla, st);
     NNQS_HIP_CHECK(hipGetLastError());
-    std::vector<int32_t> h_rows((size_t)n), h_off((size_t)n + 1);
-    NNQS_HIP_CHECK(hipMemcpyAsync(h_rows.data(), rows, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    NNQS_HIP_CHECK(hipStreamSynchronize(st));
-    h_off[0] = 0;
-    for (int64_t i = 0; i < n; i++) h_off[(size_t)i + 1] = h_off[(size_t)i] + h_rows[(size_t)i];
-    NNQS_HIP_CHECK(hipMemcpyAsync(off, h_off.data(), (size_t)(n + 1) * sizeof(int32_t), hipMemcpyHostToDevice, st));
-    const int64_t Bmax = n < kF64Batch ? n : kF64Batch;
-    const int64_t Rmax = Bmax * K;
-    // h, a, q, k, v [rows][64]; f [rows][F]; z1, z2 [B][P]; lp [rows]; LayerNorm statistics [rows][2];
-    // ckeys [B][2]; row maps [rows][2]
-    const size_t need = ((size_t)Rmax * (5 * d + F + 3) + (size_t)Bmax * (2 * P + 2)) * 8 + (size_t)Rmax * 8 + 256;
-    if (m->f64cap < need) {
-        NNQS_HIP_CHECK(hipStreamSynchronize(st));
-        hipFree(m->d_f64s);
-        m->d_f64s = nullptr;
-        m->f64cap = 0;
-        if (hipMalloc(&m->d_f64s, need) != hipSuccess) return fail(NNQS_ENOMEM, "FP64 forward scratch (%zu bytes)", need);
-        m->f64cap = need;
-    }
-    double *h = reinterpret_cast<double *>(m->d_f64s);
-    double *a = h + Rmax * d, *qb = a + Rmax * d, *kk = qb + Rmax * d, *v = kk + Rmax * d;
-    double *f = v + Rmax * d, *z1 = f + Rmax * F, *z2 = z1 + Bmax * P, *lp = z2 + Bmax * P;
-    double *lst = lp + Rmax;  // LayerNorm statistics [rows][2]
-    uint64_t *ckeys = reinterpret_cast<uint64_t *>(lst + 2 * Rmax);
-    int32_t *row_cfg = reinterpret_cast<int32_t *>(ckeys + 2 * Bmax), *row_pos = row_cfg + Rmax;
-    const LayerOffsets LO = layer_offsets(d, F);
-    const double *W = m->d_w64;
-    const double scale = 1.0 / sqrt((double)(d / M.H));
-    for (int64_t b0 = 0; b0 < n; b0 += kF64Batch) {
-        const int64_t B = n - b0 < kF64Batch ? n - b0 : kF64Batch;
-        const int32_t off0 = h_off[(size_t)b0];
-        const int64_t R = h_off[(size_t)(b0 + B)] - off0;
-        const unsigned gy = (unsigned)((R + 63) / 64);
-        const int32_t *lq = list + b0, *sq = s0v + b0, *oq = off + b0;
-        hipLaunchKernelGGL(k64x_rowmap, dim3(blocks_for(B)), dim3(256), 0, st, xkeys, lq, sq, oq, off0, B, K, row_cfg,
-                           row_pos, ckeys);
-        hipLaunchKernelGGL(k64x_embed, dim3(blocks_for(R * d)), dim3(256), 0, st, M, ckeys, row_cfg, row_pos, R, h);
-        for (int l = 0; l < M.L; l++) {
-            const double *Lw = W + M.off.layer0 + (int64_t)l * M.off.layer_stride;
-            if (l == 0)  // later layers: the statistics come with the previous FFN output
-                hipLaunchKernelGGL(k64_ln_stats, dim3(blocks_for(R, 4)), dim3(256), 0, st, h, R, lst);
-            hipLaunchKernelGGL(k64_gemm_qkv, dim3(3, gy), dim3(256), 0, st, h, Lw + LO.wq, Lw + LO.bq,
-                               LO.wk - LO.wq, R, qb, (int64_t)(kk - qb), lst, Lw + LO.ln1_g, Lw + LO.ln1_b);
-            hipLaunchKernelGGL(k64x_attention, dim3((unsigned)B), dim3(256), 0, st, qb, kk, v, kvc, lq, sq, oq, off0,
-                               C, B, K, M.L, l, scale, a);
-            hipLaunchKernelGGL(k64_gemm_res<64>, dim3(1, gy), dim3(256), 0, st, a, 64, Lw + LO.wo, Lw + LO.bo, R, h,
-                               lst);
-            hipLaunchKernelGGL(k64_gemm_ln<2>, dim3((unsigned)((F + 63) / 64), gy), dim3(256), 0, st, h, Lw + LO.w1, F,
-                               Lw + LO.b1, R, F, f, F, lst, Lw + LO.ln2_g, Lw + LO.ln2_b);
-            ffn_out(f, F, Lw + LO.w2, Lw + LO.b2, R, F, h, lst, st);
-        }
-        hipLaunchKernelGGL(k64_layernorm, dim3(blocks_for(R, 4)), dim3(256), 0, st, h, W + M.off.lnf_g,
-                           W + M.off.lnf_b, R, a);
-        hipLaunchKernelGGL(k64x_head, dim3(blocks_for(R, 4)), dim3(256), 0, st, M, a, ckeys, row_cfg, row_pos, R, lp);
-        hipLaunchKernelGGL(k64_phase1, dim3(blocks_for(B * P)), dim3(256), 0, st, M, ckeys, B, z1);
-        hipLaunchKernelGGL(k64_gemm<2>, dim3((unsigned)((P + 63) / 64), (unsigned)((B + 63) / 64)), dim3(256), 0, st,
-                           z1, P, W + M.off.ph_w2, P, W + M.off.ph_b2, B, P, P, z2, P);
-        hipLaunchKernelGGL(k64x_finish, dim3(blocks_for(B, 4)), dim3(256), 0, st, M, lp, z2, pre, lq, sq, oq, off0, C,
-                           B, xla, xph);
-        NNQS_HIP_CHECK(hipGetLastError());
-    }
-    return NNQS_OK;
+    return enqueue_phase_f64(m, xkeys, list, n, xph, st);
 }
 
 // Instances launched from other files (the FP64 backward).
+template __global__ void k64_gemm_res<64>(const double *, int, const double *, const double *, int64_t, double *,
+                                          double *);
 template __global__ void k64_gemm<0, false>(const double *, int, const double *, int, const double *, int64_t, int,
                                             int, double *, int);
 template __global__ void k64_gemm<1, false>(const double *, int, const double *, int, const double *, int64_t, int,
