@@ -15,14 +15,30 @@ __global__ void k64_embed(ModelView M, const uint64_t *__restrict__ keys, int64_
 __global__ void k64_layernorm(const double *__restrict__ in, const double *__restrict__ g,
                               const double *__restrict__ b, int64_t rows, double *__restrict__ out);
 // C[r][j] = epi(bias[j] + sum_k A[r][k] B[k][j]); B[k][j] = W[k*ldw + j], or
-// W[j*ldw + k] with TB (the transposed weight, y W^T); EPI 0 stores, 1 adds
-// to C, 2 stores GELU.
-template <int EPI, bool TB = false>
-__global__ void k64_gemm(const double *__restrict__ A, int lda, const double *__restrict__ W, int ldw,
-                         const double *__restrict__ bias, int64_t M, int N, int Kd, double *__restrict__ C, int ldc);
-// Causal attention of [B*K][64] rows, one wave per (configuration, head).
+// W[j*ldw + k] with TB (the transposed weight, y W^T).  EPI 0 stores, 2
+// stores GELU, 3 stores GELU' and, in E.C2, GELU (u Phi(u), Phi(u) + u phi(u)),
+// 4 stores the sum times E.U, 5 stores E.src + the sum.
+struct GemmEpi {
+    const double *U = nullptr;    // EPI 4
+    const double *src = nullptr;  // EPI 5
+    double *C2 = nullptr;         // EPI 3
+};
+
+template <int EPI, bool TB>
+void gemm64(const double *A, int lda, const double *W, int ldw, const double *bias, int64_t M, int N, int Kd, double *C,
+            int ldc, const GemmEpi &E, hipStream_t st);
+// C + x cs = a W_x + b_x (x = 0, 1, 2; weights and biases ws apart), and C = sum_x A_x W_x^T.
+void gemm64_qkv(const double *a, const double *W, const double *bias, int64_t ws, int64_t M, double *C, int64_t cs,
+                hipStream_t st);
+void gemm64_qkv_back(const double *A, int64_t as, const double *W, int64_t ws, int64_t M, double *C, hipStream_t st);
+// Attention backward of [B*K][64] rows, one block per (configuration, head).
+__global__ void k64x_attention_back(const double *__restrict__ q, const double *__restrict__ k,
+                                    const double *__restrict__ v, const double *__restrict__ o,
+                                    const double *__restrict__ dout, int K, double scale,
+                                    double *__restrict__ dq, double *__restrict__ dk, double *__restrict__ dv);
+// Causal attention of [B*K][64] rows, one block per (configuration, head).
 __global__ void k64_attention(const double *__restrict__ q, const double *__restrict__ k,
-                              const double *__restrict__ v, int64_t B, int K, double scale, double *__restrict__ o);
+                              const double *__restrict__ v, int K, double scale, double *__restrict__ o);
 // Output head: log-probability of each row's token (and the conditionals of position cpos).
 __global__ void k64_head(ModelView M, const double *__restrict__ a, const int8_t *__restrict__ tok, int64_t B,
                          double *__restrict__ lp, int cpos, double *__restrict__ cond);

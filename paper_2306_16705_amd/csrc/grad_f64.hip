@@ -3,54 +3,28 @@
 // the gradient estimator of Eq. 7 (Section 2.1), AdamW and the warm-up
 // learning rate of Eq. 13 (Section 4.1).
 //
-// The forward runs layer by layer over passes of kGradBatch configurations
-// with the kernels of the FP64 forward, keeping every activation the backward
-// needs (about 33 KB per sequence row at d 64, F 256, four layers).  The
-// backward walks the layers in reverse with one kernel per step: row kernels
-// (one wave per row) for the head and LayerNorm, one wave per (configuration,
-// head) for attention, FP64 MFMA products with the transposed weight for the
-// input gradients, and a split-k FP64 MFMA product X^T dY for every weight
-// gradient whose per-split partials are added in a fixed order, so results
-// are reproducible bit for bit.  The token and position embeddings take their
-// gradients through the same product with one-hot row matrices.
+// The forward runs layer by layer over passes of kGradBatch configurations,
+// keeping every activation the backward needs; the backward walks the layers
+// in reverse with row kernels (one wave per row) for the head and LayerNorm,
+// one block per (configuration, head) for attention and FP64 MFMA products with
+// the transposed weights, and keeps the gradient of every product's output.
+// All weight and bias gradients then come from one grouped launch of X^T dY
+// products (kg_gemm_tn): its tiles fill the chip where one product's do not.
+// Rows are split so that the launch has about two blocks per CU; each split
+// writes the gradient's own layout, and one launch adds the splits in a fixed
+// order (kg_reduce), so results are reproducible bit for bit.
+// 128 configurations at K = 60, one MI355X: the gradient and an
+// optimiser step 10.49 ms before (76 weight-gradient launches of a few blocks,
+// 4.6 ms; 4.1 ms of host work), 1.08 ms now, of which the grouped products 124 us,
+// the 22 layer products 0.45 ms, attention 0.16 ms.
+#include <algorithm>
 #include <cmath>
-#include <vector>
 
 #include "f64_kernels.hpp"
 
 namespace nnqs {
 
 constexpr int64_t kGradBatch = 256;  // configurations per pass
-constexpr int64_t kTnRows = 512;     // rows per split of the weight-gradient products
-constexpr int kTnMaxSplits = (int)((kGradBatch * 64 + kTnRows - 1) / kTnRows);
-
-__device__ __forceinline__ double gelu_grad_f64(double u) {
-    // d/du [u Phi(u)] = Phi(u) + u phi(u)
-    const double cdf = 0.5 * (1.0 + erf(u * 0.70710678118654752440));
-    const double pdf = 0.39894228040143267794 * exp(-0.5 * u * u);
-    return cdf + u * pdf;
-}
-
-__global__ void kg_fill(double *__restrict__ p, int64_t n, double v) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) p[e] = v;
-}
-
-__global__ void kg_copy(const double *__restrict__ src, int64_t n, double *__restrict__ dst) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) dst[e] = src[e];
-}
-
-__global__ void kg_gelu(const double *__restrict__ u, int64_t n, double *__restrict__ out) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) out[e] = gelu_f64(u[e]);
-}
-
-// d[e] *= GELU'(u[e])
-__global__ void kg_gelu_back(const double *__restrict__ u, int64_t n, double *__restrict__ d) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n) d[e] *= gelu_grad_f64(u[e]);
-}
 
 // Occupation bits as a [B][N2] matrix of 0 / 1 (the phase MLP's input).
 __global__ void kg_bits(const uint64_t *__restrict__ keys, int64_t B, int N2, double *__restrict__ bits) {
@@ -62,18 +36,6 @@ __global__ void kg_bits(const uint64_t *__restrict__ keys, int64_t B, int N2, do
     x.lo = keys[2 * b];
     x.hi = keys[2 * b + 1];
     bits[e] = (double)key_bit(x, p);
-}
-
-// One-hot rows of the input token (previous token, begin token 4 at s = 0)
-// [R][5] and of the position [R][K], for the embedding gradients.
-__global__ void kg_onehots(const int8_t *__restrict__ tok, int64_t B, int K, double *__restrict__ oh_tok,
-                           double *__restrict__ oh_pos) {
-    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (row >= B * K) return;
-    const int s = (int)(row % K);
-    const int prev = s == 0 ? 4 : tok[row - 1];
-    for (int t = 0; t < 5; t++) oh_tok[row * 5 + t] = t == prev ? 1.0 : 0.0;
-    for (int j = 0; j < K; j++) oh_pos[row * K + j] = j == s ? 1.0 : 0.0;
 }
 
 // Output head backward, one wave per row (lane = model column, d = 64).  The
@@ -165,153 +127,153 @@ __global__ void __launch_bounds__(256) kg_layernorm_back(const double *__restric
     prod[e] = d * xh;
 }
 
-// Causal attention backward, one wave per (configuration, head), lane i =
-// query row i (K <= 64): recompute P = softmax(scale Q K^T) row by row, then
-// dV = P^T dO, dS = P o (dO V^T - D) with D_i = dO_i . O_i, dQ = scale dS K,
-// dK = scale dS^T Q.  q, k, v, o, dout and the outputs are [B*K][64] with head
-// hh in columns 16 hh .. 16 hh + 15.
-__global__ void __launch_bounds__(64) kg_attention_back(const double *__restrict__ q, const double *__restrict__ k,
-                                                        const double *__restrict__ v, const double *__restrict__ o,
-                                                        const double *__restrict__ dout, int64_t B, int K,
-                                                        double scale, double *__restrict__ dq,
-                                                        double *__restrict__ dk, double *__restrict__ dv) {
-    __shared__ double Qs[64][17], Ks[64][17], Vs[64][17], Gs[64][17];
-    __shared__ double P[64][65];
-    const int i = threadIdx.x;
-    const int64_t b = blockIdx.x >> 2;
-    const int hh = (int)(blockIdx.x & 3);
-    if (b >= B) return;  // block-uniform
-    const int64_t base = (b * K + i) * 64 + hh * 16;
-    double Di = 0.0;
-    for (int c = 0; c < 16; c++) {
-        const bool in = i < K;
-        Qs[i][c] = in ? q[base + c] : 0.0;
-        Ks[i][c] = in ? k[base + c] : 0.0;
-        Vs[i][c] = in ? v[base + c] : 0.0;
-        const double gd = in ? dout[base + c] : 0.0;
-        Gs[i][c] = gd;
-        Di += gd * (in ? o[base + c] : 0.0);
-    }
-    __syncthreads();
-    if (i < K) {
-        double mx = -INFINITY;
-        for (int j = 0; j <= i; j++) {
-            double sc = 0.0;
-            for (int c = 0; c < 16; c++) sc += Qs[i][c] * Ks[j][c];
-            P[i][j] = sc;
-            mx = fmax(mx, sc);
-        }
-        double den = 0.0;
-        for (int j = 0; j <= i; j++) {
-            const double p = exp((P[i][j] - mx) * scale);
-            P[i][j] = p;
-            den += p;
-        }
-        const double inv = 1.0 / den;
-        for (int j = 0; j <= i; j++) P[i][j] *= inv;
-    }
-    __syncthreads();
-    double acc[16];
-    // dV[j] = sum_{i >= j} P[i][j] dO[i]   (lane = key j)
-    for (int c = 0; c < 16; c++) acc[c] = 0.0;
-    for (int r = i; r < K; r++) {
-        const double p = P[r][i];
-        for (int c = 0; c < 16; c++) acc[c] += p * Gs[r][c];
-    }
-    if (i < K)
-        for (int c = 0; c < 16; c++) dv[base + c] = acc[c];
-    __syncthreads();  // every column of P is read before rows become dS
-    if (i < K) {
-        for (int j = 0; j <= i; j++) {
-            double dp = 0.0;
-            for (int c = 0; c < 16; c++) dp += Gs[i][c] * Vs[j][c];
-            P[i][j] = P[i][j] * (dp - Di);
-        }
-        for (int c = 0; c < 16; c++) acc[c] = 0.0;
-        for (int j = 0; j <= i; j++) {
-            const double ds = P[i][j];
-            for (int c = 0; c < 16; c++) acc[c] += ds * Ks[j][c];
-        }
-        for (int c = 0; c < 16; c++) dq[base + c] = scale * acc[c];
-    }
-    __syncthreads();
-    // dK[j] = scale sum_{i >= j} dS[i][j] Q[i]   (lane = key j)
-    for (int c = 0; c < 16; c++) acc[c] = 0.0;
-    for (int r = i; r < K; r++) {
-        const double ds = P[r][i];
-        for (int c = 0; c < 16; c++) acc[c] += ds * Qs[r][c];
-    }
-    if (i < K)
-        for (int c = 0; c < 16; c++) dk[base + c] = scale * acc[c];
-}
-
-// Phase MLP output layer backward: du2[b][i] = cp[b] w3[i] GELU'(u2[b][i]).
-__global__ void kg_phase_top(const double *__restrict__ u2, const double *__restrict__ w3,
+// Phase MLP output layer backward: du2[b][i] = cp[b] w3[i] d2[b][i], d2 =
+// GELU'(u2).
+__global__ void kg_phase_top(const double *__restrict__ d2, const double *__restrict__ w3,
                              const double *__restrict__ cp, int64_t B, int P, double *__restrict__ du2) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (e >= B * P) return;
     const int64_t b = e / P;
     const int j = (int)(e - b * P);
-    du2[e] = cp[b] * w3[j] * gelu_grad_f64(u2[e]);
+    du2[e] = cp[b] * w3[j] * d2[e];
 }
 
-// Weight-gradient partials on FP64 MFMA: part[z][i][j] = sum over rows r of
-// split z of X[r][i] D[r][j] for i < M, j < N (X null: a column of ones, M = 1,
-// the bias gradients).  Block: 64 x 64 tile of the [M][N] result, four waves
-// of 16 rows; rows in slices of 32 through LDS (the MFMA layout as in k64_gemm).
-__global__ void __launch_bounds__(256) kg_gemm_tn(const double *__restrict__ X, int ldx,
-                                                  const double *__restrict__ D, int ldd, int64_t R, int M, int N,
-                                                  int64_t rows_per_split, double *__restrict__ part) {
-    constexpr int KS = 32;
-    __shared__ double Xs[KS][64 + 1];
-    __shared__ double Ds[KS][64 + 1];
+// One weight-gradient product of the grouped launch: out[goff + i N + j] =
+// sum over rows r of X[r][i] D[r][j] (i < M, j < N), and out[boff + j] = sum of
+// D[r][j] where boff >= 0 (M = 0: only that).
+struct TnProblem {
+    const double *X, *D;
+    int ldx, ldd, M, N;
+    int64_t R, goff, boff;
+    int tile0, splits;  // first block; row splits of each of its tiles
+};
+constexpr int kTnMax = 48;  // 3.5 KB of kernel arguments; four layers in one launch
+struct TnGroup {
+    TnProblem p[kTnMax];
+    int n;
+};
+
+// Block: one 64 x 64 tile of one product over one split's rows, four waves of
+// 16 rows of the tile; rows r in slices of 32 through LDS, the next slice's
+// loads in flight.  The blocks of a product's first tile row also add up D's
+// columns.  Split z writes part + z total.
+__global__ void __launch_bounds__(256) kg_gemm_tn(TnGroup G, int64_t total, double *__restrict__ part) {
+    __shared__ double Xs[32][80];
+    __shared__ double Ds[32][80];
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int lr = l & 15, lk = l >> 4;
-    const int i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
-    const int64_t rs = (int64_t)blockIdx.z * rows_per_split;
-    const int64_t re = rs + rows_per_split < R ? rs + rows_per_split : R;
+    int q = 0;
+    while (q + 1 < G.n && (int)blockIdx.x >= G.p[q + 1].tile0) q++;
+    const TnProblem &P = G.p[q];
+    const int b = (int)blockIdx.x - P.tile0, z = b % P.splits, t = b / P.splits;
+    const int nt = (P.N + 63) / 64;
+    const int i0 = t / nt * 64, j0 = t % nt * 64;
+    const int64_t per = (((P.R + P.splits - 1) / P.splits) + 31) & ~(int64_t)31;
+    const int64_t rs = z * per, re = rs + per < P.R ? rs + per : P.R;
     const int tc = threadIdx.x & 63, tr = threadIdx.x >> 6;
-    f64x4 acc[4];
-#pragma unroll
-    for (int cb = 0; cb < 4; cb++) acc[cb] = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int64_t k0 = rs; k0 < re; k0 += KS) {
-        __syncthreads();
+    const bool xin = i0 + tc < P.M, din = j0 + tc < P.N;
+    const double *X = P.X + i0 + tc, *D = P.D + j0 + tc;
+    const bool product = P.M > 0, colsum = P.boff >= 0 && i0 == 0;
+    double px[8], pd[8], cs = 0.0;
+    auto load = [&](int64_t k0) {
 #pragma unroll
         for (int e = 0; e < 8; e++) {
-            const int kk = tr + 4 * e;
-            const int64_t r = k0 + kk;
-            const bool rin = r < re;
-            Xs[kk][tc] = (rin && i0 + tc < M) ? (X ? X[r * ldx + i0 + tc] : 1.0) : 0.0;
-            Ds[kk][tc] = (rin && j0 + tc < N) ? D[r * ldd + j0 + tc] : 0.0;
+            const int64_t r = k0 + tr + 4 * e;
+            px[e] = (r < re && xin) ? X[r * P.ldx] : 0.0;
+            pd[e] = (r < re && din) ? D[r * P.ldd] : 0.0;
+        }
+    };
+    f64x4 acc[4] = {};
+    load(rs);
+    for (int64_t k0 = rs; k0 < re; k0 += 32) {
+        if (!product) {  // column sums only
+#pragma unroll
+            for (int e = 0; e < 8; e++) cs += pd[e];
+            load(k0 + 32);
+            continue;
         }
         __syncthreads();
 #pragma unroll
-        for (int k4 = 0; k4 < KS; k4 += 4) {
+        for (int e = 0; e < 8; e++) {
+            Xs[tr + 4 * e][tc] = px[e];
+            Ds[tr + 4 * e][tc] = pd[e];
+            cs += pd[e];
+        }
+        __syncthreads();
+        load(k0 + 32);
+#pragma unroll
+        for (int k4 = 0; k4 < 32; k4 += 4) {
             const double a = Xs[k4 + lk][16 * w + lr];
 #pragma unroll
             for (int cb = 0; cb < 4; cb++)
                 acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Ds[k4 + lk][cb * 16 + lr], acc[cb], 0, 0, 0);
         }
     }
+    double *out = part + z * total;
+    if (product)
 #pragma unroll
-    for (int cb = 0; cb < 4; cb++) {
-        const int j = j0 + cb * 16 + lr;
-        if (j >= N) continue;
+        for (int cb = 0; cb < 4; cb++) {
+            const int j = j0 + cb * 16 + lr;
+            if (j >= P.N) continue;
 #pragma unroll
-        for (int ii = 0; ii < 4; ii++) {
-            const int i = i0 + 16 * w + lk + 4 * ii;
-            if (i < M) part[((int64_t)blockIdx.z * M + i) * N + j] = acc[cb][ii];
+            for (int ii = 0; ii < 4; ii++) {
+                const int i = i0 + 16 * w + lk + 4 * ii;
+                if (i < P.M) out[P.goff + (int64_t)i * P.N + j] = acc[cb][ii];
+            }
         }
+    if (colsum) {  // block-uniform: the four row phases of each column in order
+        __syncthreads();
+        Ds[tr][tc] = cs;
+        __syncthreads();
+        if (tr == 0 && din) out[P.boff + j0 + tc] = ((Ds[0][tc] + Ds[1][tc]) + Ds[2][tc]) + Ds[3][tc];
     }
 }
 
-// grad[e] += sum_{z < S} part[z][e], in order of z.
-__global__ void kg_reduce_add(const double *__restrict__ part, int S, int64_t MN, double *__restrict__ grad) {
+// Embedding gradients: h0[b, s] = tok_emb[token at s-1] + pos_emb[s].  Block =
+// position: the position's sum over b to pos[s], and the sums by input token
+// to tokp[s][5] (each of four row phases in order of b, then the phases).
+__global__ void __launch_bounds__(256) kg_embed_back(const double *__restrict__ dh, const int8_t *__restrict__ tok,
+                                                     int64_t B, int K, double *__restrict__ pos,
+                                                     double *__restrict__ tokp) {
+    __shared__ double sh[4][6][64];
+    const int s = blockIdx.x, c = threadIdx.x & 63, ph = threadIdx.x >> 6;
+    double a[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};  // tokens 0 .. 4, all
+    for (int64_t b = ph; b < B; b += 4) {
+        const int64_t row = b * K + s;
+        const int prev = s == 0 ? 4 : tok[row - 1];
+        const double v = dh[row * 64 + c];
+        a[5] += v;
+#pragma unroll
+        for (int t = 0; t < 5; t++) a[t] += t == prev ? v : 0.0;
+    }
+#pragma unroll
+    for (int t = 0; t < 6; t++) sh[ph][t][c] = a[t];
+    __syncthreads();
+    for (int t = ph; t < 6; t += 4) {
+        const double v = ((sh[0][t][c] + sh[1][t][c]) + sh[2][t][c]) + sh[3][t][c];
+        if (t == 5) pos[s * 64 + c] = v;
+        else tokp[(s * 5 + t) * 64 + c] = v;
+    }
+}
+
+// grad[e] = (add ? grad[e] : 0) + the splits of part in order: `splits` of the
+// transformer's weights (from layer0 up to the logit bias), one of the phase
+// MLP's and the position embedding; the token embedding from its K position
+// sums; the fixed logit-bias table has none.
+__global__ void kg_reduce(ModelOffsets O, int K, const double *__restrict__ part, int splits,
+                          const double *__restrict__ tokp, bool add, double *__restrict__ grad) {
     const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= MN) return;
+    if (e >= O.total) return;
     double s = 0.0;
-    for (int z = 0; z < S; z++) s += part[(int64_t)z * MN + e];
-    grad[e] += s;
+    if (e >= O.bias && e < O.ph_w1) {
+        s = 0.0;
+    } else if (e < O.pos_emb) {
+        for (int p = 0; p < K; p++) s += tokp[(int64_t)p * 320 + (e - O.tok_emb)];
+    } else {
+        const int n = e >= O.layer0 && e < O.bias ? splits : 1;
+        for (int z = 0; z < n; z++) s += part[(int64_t)z * O.total + e];
+    }
+    grad[e] = (add ? grad[e] : 0.0) + s;
 }
 
 // Eq. 7 cotangents: with p = c / sum c and E = energy[0] + i energy[1],
@@ -350,36 +312,79 @@ __global__ void kg_adamw(double *__restrict__ w, const double *__restrict__ g, d
 static unsigned nblocks(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
 // Device scratch of one pass (doubles unless noted), carved from one buffer.
+// Per layer: the forward's activations (Hin: L + 1; U: GELU' of the hidden
+// layer, G: its GELU) and the gradients of the
+// products' outputs (dH: L + 1, dH[l] at the input of layer l).
 struct GradScratch {
-    double *Hin, *A1, *Q, *Kb, *V, *O, *Hmid, *A2, *U, *G;  // per layer (Hin: L + 1)
-    double *AF, *LP, *bits, *U1, *Z1, *U2, *Z2, *la, *ph;
-    double *dH, *dA, *dO, *dQ, *dK, *dV, *dU, *prod, *dz, *ohtok, *ohpos, *dP1, *dP2;
+    double *Hin, *A1, *Q, *O, *Hmid, *A2, *U, *G;  // Q: Q, K, V one after another
+    double *dH, *dU, *dA2, *prod2, *dHm, *dQ, *dA1, *prod1;
+    double *AF, *LP, *bits, *U1, *Z1, *U2, *Z2, *dO, *dAF, *prodf, *dz, *dP1, *dP2, *tokp;
     double *part, *epart, *energy, *cl, *cp;
     int8_t *tok;
 };
 
-static size_t grad_scratch_doubles(const nnqs_model_desc &m, int64_t Bmax, int64_t nmax, size_t &part_elems) {
-    const int64_t K = m.n_orb, d = m.d_model, F = m.d_ff, P = m.phase_hidden, L = m.n_layers;
-    const int64_t R = Bmax * K;
-    int64_t mn = d * F;
-    if (P * P > mn) mn = P * P;
-    if (2 * K * P > mn) mn = 2 * K * P;
-    part_elems = (size_t)kTnMaxSplits * (size_t)mn;
-    size_t n = 0;
-    n += (size_t)(L + 1) * R * d + (size_t)7 * L * R * d + (size_t)2 * L * R * F;  // saved layers
-    n += (size_t)R * d + R + (size_t)Bmax * 2 * K + (size_t)4 * Bmax * P + 2 * Bmax;
-    n += (size_t)7 * R * d + (size_t)R * F + (size_t)R * 4 + (size_t)R * 5 + (size_t)R * K + (size_t)2 * Bmax * P;
-    n += part_elems + (size_t)kPartialBlocks * 8 + 8 + (size_t)2 * nmax;
-    n += (size_t)(R + 7) / 8 + 1;  // tokens (bytes)
-    return n;
+// Rows per split: K = 60, 128 configurations take 10 splits (1.08 ms a step; 384
+// rows the same, 1,536 rows 1.13 ms).
+constexpr int64_t kTnSplitRows = 768;
+
+static int tn_splits(int64_t R) { return (int)std::max<int64_t>(1, (R + kTnSplitRows - 1) / kTnSplitRows); }
+
+// Carves the scratch of passes of Bmax configurations (and cotangents of n)
+// from `at`; returns the doubles used.
+static size_t grad_carve(const nnqs_model *m, int64_t Bmax, int64_t n, double *base, GradScratch &S) {
+    const nnqs_model_desc &md = m->desc;
+    const size_t K = md.n_orb, d = md.d_model, F = md.d_ff, P = md.phase_hidden, L = md.n_layers;
+    const size_t R = (size_t)Bmax * K, B = (size_t)Bmax, Rd = R * d;
+    size_t at = 0;
+    auto take = [&](size_t cnt) {
+        double *p = base ? base + at : nullptr;
+        at += cnt;
+        return p;
+    };
+    S.Hin = take((L + 1) * Rd);
+    S.A1 = take(L * Rd);
+    S.Q = take(3 * L * Rd);
+    S.O = take(L * Rd);
+    S.Hmid = take(L * Rd);
+    S.A2 = take(L * Rd);
+    S.U = take(L * R * F);
+    S.G = take(L * R * F);
+    S.dH = take((L + 1) * Rd);
+    S.dU = take(L * R * F);
+    S.dA2 = take(L * Rd);
+    S.prod2 = take(L * Rd);
+    S.dHm = take(L * Rd);
+    S.dQ = take(3 * L * Rd);
+    S.dA1 = take(L * Rd);
+    S.prod1 = take(L * Rd);
+    S.AF = take(Rd);
+    S.LP = take(R);
+    S.bits = take(B * 2 * K);
+    S.U1 = take(B * P);
+    S.Z1 = take(B * P);
+    S.U2 = take(B * P);
+    S.Z2 = take(B * P);
+    S.dO = take(Rd);
+    S.dAF = take(Rd);
+    S.prodf = take(Rd);
+    S.dz = take(R * 4);
+    S.dP1 = take(B * P);
+    S.dP2 = take(B * P);
+    S.tokp = take(K * 5 * d);
+    S.part = take((size_t)tn_splits((int64_t)R) * (size_t)m->off.total);
+    S.epart = take((size_t)kPartialBlocks * 8);
+    S.energy = take(8);
+    S.cl = take((size_t)n);
+    S.cp = take((size_t)n);
+    S.tok = reinterpret_cast<int8_t *>(take((R + 7) / 8 + 1));
+    return at;
 }
 
-static nnqs_status grad_scratch(nnqs_model *m, int64_t n, GradScratch &S) {
-    const nnqs_model_desc &md = m->desc;
+static nnqs_status grad_scratch(nnqs_model *m, int64_t n, GradScratch &S, hipStream_t st) {
     const int64_t Bmax = n < kGradBatch ? n : kGradBatch;
-    size_t part_elems = 0;
-    const size_t need = grad_scratch_doubles(md, kGradBatch, n, part_elems) * sizeof(double);
+    const size_t need = grad_carve(m, Bmax, n, nullptr, S) * sizeof(double);
     if (m->gradcap < need) {
+        NNQS_HIP_CHECK(hipStreamSynchronize(st));
         (void)hipFree(m->d_grads);
         m->d_grads = nullptr;
         m->gradcap = 0;
@@ -387,85 +392,29 @@ static nnqs_status grad_scratch(nnqs_model *m, int64_t n, GradScratch &S) {
             return fail(NNQS_ENOMEM, "FP64 gradient scratch (%zu bytes)", need);
         m->gradcap = need;
     }
-    (void)Bmax;
-    const int64_t K = md.n_orb, d = md.d_model, F = md.d_ff, P = md.phase_hidden, L = md.n_layers;
-    const int64_t R = kGradBatch * K, B = kGradBatch;
-    double *at = reinterpret_cast<double *>(m->d_grads);
-    auto take = [&](size_t cnt) {
-        double *p = at;
-        at += cnt;
-        return p;
-    };
-    S.Hin = take((size_t)(L + 1) * R * d);
-    S.A1 = take((size_t)L * R * d);
-    S.Q = take((size_t)L * R * d);
-    S.Kb = take((size_t)L * R * d);
-    S.V = take((size_t)L * R * d);
-    S.O = take((size_t)L * R * d);
-    S.Hmid = take((size_t)L * R * d);
-    S.A2 = take((size_t)L * R * d);
-    S.U = take((size_t)L * R * F);
-    S.G = take((size_t)L * R * F);
-    S.AF = take((size_t)R * d);
-    S.LP = take((size_t)R);
-    S.bits = take((size_t)B * 2 * K);
-    S.U1 = take((size_t)B * P);
-    S.Z1 = take((size_t)B * P);
-    S.U2 = take((size_t)B * P);
-    S.Z2 = take((size_t)B * P);
-    S.la = take((size_t)B);
-    S.ph = take((size_t)B);
-    S.dH = take((size_t)R * d);
-    S.dA = take((size_t)R * d);
-    S.dO = take((size_t)R * d);
-    S.dQ = take((size_t)R * d);
-    S.dK = take((size_t)R * d);
-    S.dV = take((size_t)R * d);
-    S.prod = take((size_t)R * d);
-    S.dU = take((size_t)R * F);
-    S.dz = take((size_t)R * 4);
-    S.ohtok = take((size_t)R * 5);
-    S.ohpos = take((size_t)R * K);
-    S.dP1 = take((size_t)B * P);
-    S.dP2 = take((size_t)B * P);
-    S.part = take(part_elems);
-    S.epart = take((size_t)kPartialBlocks * 8);
-    S.energy = take(8);
-    S.cl = take((size_t)n);
-    S.cp = take((size_t)n);
-    S.tok = reinterpret_cast<int8_t *>(at);
+    grad_carve(m, Bmax, n, reinterpret_cast<double *>(m->d_grads), S);
     return NNQS_OK;
 }
 
-// grad[goff ..] += X^T D over R rows (X null: column sums of D).
-static void tn_add(const double *X, int ldx, const double *D, int ldd, int64_t R, int M, int N, double *part,
-                   double *grad, hipStream_t st) {
-    const int S = (int)((R + kTnRows - 1) / kTnRows);
-    hipLaunchKernelGGL(kg_gemm_tn, dim3((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64), (unsigned)S), dim3(256),
-                       0, st, X, ldx, D, ldd, R, M, N, (int64_t)kTnRows, part);
-    const int64_t MN = (int64_t)M * N;
-    hipLaunchKernelGGL(kg_reduce_add, dim3(nblocks(MN)), dim3(256), 0, st, part, S, MN, grad);
-}
-
-// C = A W^T (EPI 0) or C += A W^T (EPI 1) for a weight W [in][out]: A [M][out], C [M][in].
-template <int EPI>
-static void gemm_wt(const double *A, const double *W, int in, int out, int64_t M, double *C, hipStream_t st) {
-    hipLaunchKernelGGL((k64_gemm<EPI, true>), dim3((unsigned)((in + 63) / 64), (unsigned)((M + 63) / 64)), dim3(256),
-                       0, st, A, out, W, out, (const double *)nullptr, M, in, out, C, in);
-}
-
-// C = A W + b for a weight W [in][out]: A [M][in], C [M][out].
-static void gemm_w(const double *A, const double *W, const double *b, int in, int out, int64_t M, double *C,
-                   hipStream_t st) {
-    hipLaunchKernelGGL((k64_gemm<0, false>), dim3((unsigned)((out + 63) / 64), (unsigned)((M + 63) / 64)),
-                       dim3(256), 0, st, A, in, W, out, b, M, out, in, C, out);
-}
-
-static void gemm_w_add(const double *A, const double *W, const double *b, int in, int out, int64_t M, double *C,
-                       hipStream_t st) {
-    hipLaunchKernelGGL((k64_gemm<1, false>), dim3((unsigned)((out + 63) / 64), (unsigned)((M + 63) / 64)),
-                       dim3(256), 0, st, A, in, W, out, b, M, out, in, C, out);
-}
+// Collects the products of a pass and launches them in groups.
+struct TnLauncher {
+    TnGroup G{};
+    int blocks = 0;
+    int64_t total;
+    double *part;
+    hipStream_t st;
+    void add(const double *X, int ldx, const double *D, int ldd, int64_t R, int M, int N, int64_t goff, int64_t boff,
+             int splits) {
+        G.p[G.n] = TnProblem{X, D, ldx, ldd, M, N, R, goff, boff, blocks, splits};
+        G.n++;
+        blocks += splits * std::max(1, (M + 63) / 64) * ((N + 63) / 64);
+        if (G.n == kTnMax) flush();
+    }
+    void flush() {
+        if (G.n) hipLaunchKernelGGL(kg_gemm_tn, dim3((unsigned)blocks), dim3(256), 0, st, G, total, part);
+        G.n = blocks = 0;
+    }
+};
 
 bool grad_shape_ok(const nnqs_model_desc &m) { return f64_shape_ok(m) && m.n_orb <= 64; }
 
@@ -476,7 +425,7 @@ nnqs_status enqueue_model_grad(nnqs_model *m, const uint64_t *keys, int64_t n, c
     if (!grad_shape_ok(m->desc))
         return fail(NNQS_EUNSUPPORTED, "gradients need d_model 64, 4 heads, d_ff a multiple of 64 and n_orb <= 64");
     GradScratch S{};
-    nnqs_status rc = grad_scratch(m, n, S);
+    nnqs_status rc = grad_scratch(m, n, S, st);
     if (rc != NNQS_OK) return rc;
     const ModelView M = model_view(m);
     const int K = M.K, d = M.d, F = M.F, P = M.P, L = M.L;
@@ -484,109 +433,108 @@ nnqs_status enqueue_model_grad(nnqs_model *m, const uint64_t *keys, int64_t n, c
     const ModelOffsets &OF = m->off;
     double *W = m->d_w64;
     const double scale = 1.0 / sqrt((double)(d / M.H));
-    hipLaunchKernelGGL(kg_fill, dim3(nblocks(OF.total)), dim3(256), 0, st, grad, OF.total, 0.0);
+    const GemmEpi none{};
+    const int64_t Rs = (n < kGradBatch ? n : kGradBatch) * K;  // layer stride in the saved buffers
     for (int64_t b0 = 0; b0 < n; b0 += kGradBatch) {
         const int64_t B = n - b0 < kGradBatch ? n - b0 : kGradBatch;
-        const int64_t R = B * K, Rd = R * d, RF = R * F;
-        const int64_t Rs = (int64_t)kGradBatch * K;  // layer stride in the saved buffers
-        auto hin = [&](int l) { return S.Hin + (size_t)l * Rs * d; };
+        const int64_t R = B * K, Rd = R * d;
         auto lay = [&](double *base, int l, int w) { return base + (size_t)l * Rs * w; };
         // ---------------------------------------------------------- forward
-        hipLaunchKernelGGL(k64_embed, dim3(nblocks(Rd)), dim3(256), 0, st, M, keys + 2 * b0, B, S.tok, hin(0));
+        hipLaunchKernelGGL(k64_embed, dim3(nblocks(Rd)), dim3(256), 0, st, M, keys + 2 * b0, B, S.tok, S.Hin);
         for (int l = 0; l < L; l++) {
             const double *Lw = W + OF.layer0 + (int64_t)l * OF.layer_stride;
-            double *a1 = lay(S.A1, l, d), *q = lay(S.Q, l, d), *kk = lay(S.Kb, l, d), *v = lay(S.V, l, d);
-            double *o = lay(S.O, l, d), *hm = lay(S.Hmid, l, d), *a2 = lay(S.A2, l, d);
-            double *u = lay(S.U, l, F), *g = lay(S.G, l, F);
-            hipLaunchKernelGGL(k64_layernorm, dim3(nblocks(R, 4)), dim3(256), 0, st, hin(l), Lw + LO.ln1_g,
-                               Lw + LO.ln1_b, R, a1);
-            gemm_w(a1, Lw + LO.wq, Lw + LO.bq, d, d, R, q, st);
-            gemm_w(a1, Lw + LO.wk, Lw + LO.bk, d, d, R, kk, st);
-            gemm_w(a1, Lw + LO.wv, Lw + LO.bv, d, d, R, v, st);
-            hipLaunchKernelGGL(k64_attention, dim3((unsigned)B), dim3(256), 0, st, q, kk, v, B, K, scale, o);
-            hipLaunchKernelGGL(kg_copy, dim3(nblocks(Rd)), dim3(256), 0, st, hin(l), Rd, hm);
-            gemm_w_add(o, Lw + LO.wo, Lw + LO.bo, d, d, R, hm, st);
-            hipLaunchKernelGGL(k64_layernorm, dim3(nblocks(R, 4)), dim3(256), 0, st, hm, Lw + LO.ln2_g,
-                               Lw + LO.ln2_b, R, a2);
-            gemm_w(a2, Lw + LO.w1, Lw + LO.b1, d, F, R, u, st);
-            hipLaunchKernelGGL(kg_gelu, dim3(nblocks(RF)), dim3(256), 0, st, u, RF, g);
-            hipLaunchKernelGGL(kg_copy, dim3(nblocks(Rd)), dim3(256), 0, st, hm, Rd, hin(l + 1));
-            gemm_w_add(g, Lw + LO.w2, Lw + LO.b2, F, d, R, hin(l + 1), st);
+            double *hin = lay(S.Hin, l, d), *a1 = lay(S.A1, l, d), *q = lay(S.Q, l, 3 * d), *o = lay(S.O, l, d);
+            double *hm = lay(S.Hmid, l, d), *a2 = lay(S.A2, l, d), *u = lay(S.U, l, F), *g = lay(S.G, l, F);
+            hipLaunchKernelGGL(k64_layernorm, dim3(nblocks(R, 4)), dim3(256), 0, st, hin, Lw + LO.ln1_g, Lw + LO.ln1_b,
+                               R, a1);
+            gemm64_qkv(a1, Lw + LO.wq, Lw + LO.bq, LO.wk - LO.wq, R, q, Rs * d, st);
+            hipLaunchKernelGGL(k64_attention, dim3((unsigned)(4 * B)), dim3(256), 0, st, q, q + Rs * d, q + 2 * Rs * d, K,
+                               scale, o);
+            GemmEpi res{};
+            res.src = hin;
+            gemm64<5, false>(o, d, Lw + LO.wo, d, Lw + LO.bo, R, d, d, hm, d, res, st);
+            hipLaunchKernelGGL(k64_layernorm, dim3(nblocks(R, 4)), dim3(256), 0, st, hm, Lw + LO.ln2_g, Lw + LO.ln2_b, R,
+                               a2);
+            GemmEpi both{};
+            both.C2 = g;
+            gemm64<3, false>(a2, d, Lw + LO.w1, F, Lw + LO.b1, R, F, d, u, F, both, st);
+            res.src = hm;
+            gemm64<5, false>(g, F, Lw + LO.w2, d, Lw + LO.b2, R, d, F, lay(S.Hin, l + 1, d), d, res, st);
         }
-        hipLaunchKernelGGL(k64_layernorm, dim3(nblocks(R, 4)), dim3(256), 0, st, hin(L), W + OF.lnf_g, W + OF.lnf_b,
-                           R, S.AF);
-        hipLaunchKernelGGL(k64_head, dim3(nblocks(R, 4)), dim3(256), 0, st, M, S.AF, S.tok, B, S.LP, -1,
-                           (double *)nullptr);
+        double *hl = lay(S.Hin, L, d);
+        hipLaunchKernelGGL(k64_layernorm, dim3(nblocks(R, 4)), dim3(256), 0, st, hl, W + OF.lnf_g, W + OF.lnf_b, R, S.AF);
         hipLaunchKernelGGL(kg_bits, dim3(nblocks(B * 2 * K)), dim3(256), 0, st, keys + 2 * b0, B, 2 * K, S.bits);
-        gemm_w(S.bits, W + OF.ph_w1, W + OF.ph_b1, 2 * K, P, B, S.U1, st);
-        hipLaunchKernelGGL(kg_gelu, dim3(nblocks(B * P)), dim3(256), 0, st, S.U1, B * P, S.Z1);
-        gemm_w(S.Z1, W + OF.ph_w2, W + OF.ph_b2, P, P, B, S.U2, st);
-        hipLaunchKernelGGL(kg_gelu, dim3(nblocks(B * P)), dim3(256), 0, st, S.U2, B * P, S.Z2);
-        if (la_out && ph_out)
+        GemmEpi ph{};
+        ph.C2 = S.Z1;
+        gemm64<3, false>(S.bits, 2 * K, W + OF.ph_w1, P, W + OF.ph_b1, B, P, 2 * K, S.U1, P, ph, st);
+        ph.C2 = S.Z2;
+        gemm64<3, false>(S.Z1, P, W + OF.ph_w2, P, W + OF.ph_b2, B, P, P, S.U2, P, ph, st);
+        if (la_out && ph_out) {
+            hipLaunchKernelGGL(k64_head, dim3(nblocks(R, 4)), dim3(256), 0, st, M, S.AF, S.tok, B, S.LP, -1,
+                               (double *)nullptr);
             hipLaunchKernelGGL(k64_finish, dim3(nblocks(B, 4)), dim3(256), 0, st, M, S.LP, S.Z2, B, la_out + b0,
                                ph_out + b0);
+        }
         // --------------------------------------------------------- backward
+        TnLauncher T{};
+        T.total = OF.total;
+        T.part = S.part;
+        T.st = st;
+        const int sp = tn_splits(R);
         hipLaunchKernelGGL(kg_head_back, dim3(nblocks(R, 4)), dim3(256), 0, st, M, S.AF, S.tok, B, cl + b0, S.dz,
-                           S.dA);
-        tn_add(S.AF, d, S.dz, 4, R, d, 4, S.part, grad + OF.head_w, st);
-        tn_add(nullptr, 0, S.dz, 4, R, 1, 4, S.part, grad + OF.head_b, st);
-        hipLaunchKernelGGL(kg_layernorm_back, dim3(nblocks(R, 4)), dim3(256), 0, st, hin(L), W + OF.lnf_g, S.dA, R,
-                           (const double *)nullptr, S.dH, S.prod);
-        tn_add(nullptr, 0, S.prod, d, R, 1, d, S.part, grad + OF.lnf_g, st);
-        tn_add(nullptr, 0, S.dA, d, R, 1, d, S.part, grad + OF.lnf_b, st);
+                           S.dAF);
+        double *dtop = lay(S.dH, L, d);
+        hipLaunchKernelGGL(kg_layernorm_back, dim3(nblocks(R, 4)), dim3(256), 0, st, hl, W + OF.lnf_g, S.dAF, R,
+                           (const double *)nullptr, dtop, S.prodf);
+        T.add(S.AF, d, S.dz, 4, R, d, 4, OF.head_w, OF.head_b, sp);
+        T.add(nullptr, 0, S.prodf, d, R, 0, d, 0, OF.lnf_g, sp);
+        T.add(nullptr, 0, S.dAF, d, R, 0, d, 0, OF.lnf_b, sp);
         for (int l = L - 1; l >= 0; l--) {
             const double *Lw = W + OF.layer0 + (int64_t)l * OF.layer_stride;
-            double *Gl = grad + OF.layer0 + (int64_t)l * OF.layer_stride;
-            double *a1 = lay(S.A1, l, d), *q = lay(S.Q, l, d), *kk = lay(S.Kb, l, d), *v = lay(S.V, l, d);
-            double *o = lay(S.O, l, d), *hm = lay(S.Hmid, l, d), *a2 = lay(S.A2, l, d);
-            double *u = lay(S.U, l, F), *g = lay(S.G, l, F);
+            const int64_t gl = OF.layer0 + (int64_t)l * OF.layer_stride;
+            double *a1 = lay(S.A1, l, d), *q = lay(S.Q, l, 3 * d), *o = lay(S.O, l, d), *hm = lay(S.Hmid, l, d);
+            double *a2 = lay(S.A2, l, d), *u = lay(S.U, l, F), *g = lay(S.G, l, F);
+            double *dout = lay(S.dH, l + 1, d), *dU = lay(S.dU, l, F), *dA2 = lay(S.dA2, l, d), *dHm = lay(S.dHm, l, d);
+            double *dQ = lay(S.dQ, l, 3 * d), *dA1 = lay(S.dA1, l, d), *p1 = lay(S.prod1, l, d), *p2 = lay(S.prod2, l, d);
             // feed-forward block: out = hm + GELU(LN2(hm) W1 + b1) W2 + b2
-            tn_add(g, F, S.dH, d, R, F, d, S.part, Gl + LO.w2, st);
-            tn_add(nullptr, 0, S.dH, d, R, 1, d, S.part, Gl + LO.b2, st);
-            gemm_wt<0>(S.dH, Lw + LO.w2, F, d, R, S.dU, st);
-            hipLaunchKernelGGL(kg_gelu_back, dim3(nblocks(RF)), dim3(256), 0, st, u, RF, S.dU);
-            tn_add(a2, d, S.dU, F, R, d, F, S.part, Gl + LO.w1, st);
-            tn_add(nullptr, 0, S.dU, F, R, 1, F, S.part, Gl + LO.b1, st);
-            gemm_wt<0>(S.dU, Lw + LO.w1, d, F, R, S.dA, st);
-            hipLaunchKernelGGL(kg_layernorm_back, dim3(nblocks(R, 4)), dim3(256), 0, st, hm, Lw + LO.ln2_g, S.dA, R,
-                               S.dH, S.dH, S.prod);
-            tn_add(nullptr, 0, S.prod, d, R, 1, d, S.part, Gl + LO.ln2_g, st);
-            tn_add(nullptr, 0, S.dA, d, R, 1, d, S.part, Gl + LO.ln2_b, st);
+            GemmEpi gb{};
+            gb.U = u;
+            gemm64<4, true>(dout, d, Lw + LO.w2, d, nullptr, R, F, d, dU, F, gb, st);
+            gemm64<0, true>(dU, F, Lw + LO.w1, F, nullptr, R, d, F, dA2, d, none, st);
+            hipLaunchKernelGGL(kg_layernorm_back, dim3(nblocks(R, 4)), dim3(256), 0, st, hm, Lw + LO.ln2_g, dA2, R,
+                               (const double *)dout, dHm, p2);
+            T.add(g, F, dout, d, R, F, d, gl + LO.w2, gl + LO.b2, sp);
+            T.add(a2, d, dU, F, R, d, F, gl + LO.w1, gl + LO.b1, sp);
+            T.add(nullptr, 0, p2, d, R, 0, d, 0, gl + LO.ln2_g, sp);
+            T.add(nullptr, 0, dA2, d, R, 0, d, 0, gl + LO.ln2_b, sp);
             // attention block: hm = h + Attn(LN1(h)) Wo + bo
-            tn_add(o, d, S.dH, d, R, d, d, S.part, Gl + LO.wo, st);
-            tn_add(nullptr, 0, S.dH, d, R, 1, d, S.part, Gl + LO.bo, st);
-            gemm_wt<0>(S.dH, Lw + LO.wo, d, d, R, S.dO, st);
-            hipLaunchKernelGGL(kg_attention_back, dim3((unsigned)(B * 4)), dim3(64), 0, st, q, kk, v, o, S.dO, B, K,
-                               scale, S.dQ, S.dK, S.dV);
-            tn_add(a1, d, S.dQ, d, R, d, d, S.part, Gl + LO.wq, st);
-            tn_add(nullptr, 0, S.dQ, d, R, 1, d, S.part, Gl + LO.bq, st);
-            tn_add(a1, d, S.dK, d, R, d, d, S.part, Gl + LO.wk, st);
-            tn_add(nullptr, 0, S.dK, d, R, 1, d, S.part, Gl + LO.bk, st);
-            tn_add(a1, d, S.dV, d, R, d, d, S.part, Gl + LO.wv, st);
-            tn_add(nullptr, 0, S.dV, d, R, 1, d, S.part, Gl + LO.bv, st);
-            gemm_wt<0>(S.dQ, Lw + LO.wq, d, d, R, S.dA, st);
-            gemm_wt<1>(S.dK, Lw + LO.wk, d, d, R, S.dA, st);
-            gemm_wt<1>(S.dV, Lw + LO.wv, d, d, R, S.dA, st);
-            hipLaunchKernelGGL(kg_layernorm_back, dim3(nblocks(R, 4)), dim3(256), 0, st, hin(l), Lw + LO.ln1_g, S.dA,
-                               R, S.dH, S.dH, S.prod);
-            tn_add(nullptr, 0, S.prod, d, R, 1, d, S.part, Gl + LO.ln1_g, st);
-            tn_add(nullptr, 0, S.dA, d, R, 1, d, S.part, Gl + LO.ln1_b, st);
+            gemm64<0, true>(dHm, d, Lw + LO.wo, d, nullptr, R, d, d, S.dO, d, none, st);
+            hipLaunchKernelGGL(k64x_attention_back, dim3((unsigned)(4 * B)), dim3(256), 0, st, q, q + Rs * d, q + 2 * Rs * d,
+                               o, S.dO, K, scale, dQ, dQ + Rs * d, dQ + 2 * Rs * d);
+            gemm64_qkv_back(dQ, Rs * d, Lw + LO.wq, LO.wk - LO.wq, R, dA1, st);
+            hipLaunchKernelGGL(kg_layernorm_back, dim3(nblocks(R, 4)), dim3(256), 0, st, lay(S.Hin, l, d),
+                               Lw + LO.ln1_g, dA1, R, (const double *)dHm, lay(S.dH, l, d), p1);
+            T.add(o, d, dHm, d, R, d, d, gl + LO.wo, gl + LO.bo, sp);
+            T.add(a1, d, dQ, d, R, d, d, gl + LO.wq, gl + LO.bq, sp);
+            T.add(a1, d, dQ + Rs * d, d, R, d, d, gl + LO.wk, gl + LO.bk, sp);
+            T.add(a1, d, dQ + 2 * Rs * d, d, R, d, d, gl + LO.wv, gl + LO.bv, sp);
+            T.add(nullptr, 0, p1, d, R, 0, d, 0, gl + LO.ln1_g, sp);
+            T.add(nullptr, 0, dA1, d, R, 0, d, 0, gl + LO.ln1_b, sp);
         }
-        // embeddings: h0[b, s] = tok_emb[token at s-1] + pos_emb[s]
-        hipLaunchKernelGGL(kg_onehots, dim3(nblocks(R)), dim3(256), 0, st, S.tok, B, K, S.ohtok, S.ohpos);
-        tn_add(S.ohtok, 5, S.dH, d, R, 5, d, S.part, grad + OF.tok_emb, st);
-        tn_add(S.ohpos, K, S.dH, d, R, K, d, S.part, grad + OF.pos_emb, st);
+        hipLaunchKernelGGL(kg_embed_back, dim3((unsigned)K), dim3(256), 0, st, S.dH, S.tok, B, K, S.part + OF.pos_emb,
+                           S.tokp);
         // phase MLP: phi = b3 + GELU(GELU(bits W1 + b1) W2 + b2) w3
-        tn_add(S.Z2, P, cp + b0, 1, B, P, 1, S.part, grad + OF.ph_w3, st);
-        tn_add(nullptr, 0, cp + b0, 1, B, 1, 1, S.part, grad + OF.ph_b3, st);
         hipLaunchKernelGGL(kg_phase_top, dim3(nblocks(B * P)), dim3(256), 0, st, S.U2, W + OF.ph_w3, cp + b0, B, P,
                            S.dP2);
-        tn_add(S.Z1, P, S.dP2, P, B, P, P, S.part, grad + OF.ph_w2, st);
-        tn_add(nullptr, 0, S.dP2, P, B, 1, P, S.part, grad + OF.ph_b2, st);
-        gemm_wt<0>(S.dP2, W + OF.ph_w2, P, P, B, S.dP1, st);
-        hipLaunchKernelGGL(kg_gelu_back, dim3(nblocks(B * P)), dim3(256), 0, st, S.U1, B * P, S.dP1);
-        tn_add(S.bits, 2 * K, S.dP1, P, B, 2 * K, P, S.part, grad + OF.ph_w1, st);
-        tn_add(nullptr, 0, S.dP1, P, B, 1, P, S.part, grad + OF.ph_b1, st);
+        GemmEpi gb{};
+        gb.U = S.U1;
+        gemm64<4, true>(S.dP2, P, W + OF.ph_w2, P, nullptr, B, P, P, S.dP1, P, gb, st);
+        T.add(S.Z1, P, S.dP2, P, B, P, P, OF.ph_w2, OF.ph_b2, 1);
+        T.add(S.bits, 2 * K, S.dP1, P, B, 2 * K, P, OF.ph_w1, OF.ph_b1, 1);
+        T.add(S.Z2, P, cp + b0, 1, B, P, 1, OF.ph_w3, OF.ph_b3, 1);
+        T.flush();
+        hipLaunchKernelGGL(kg_reduce, dim3(nblocks(OF.total)), dim3(256), 0, st, OF, K, (const double *)S.part, sp,
+                           (const double *)S.tokp, b0 > 0, grad);
         NNQS_HIP_CHECK(hipGetLastError());
     }
     return NNQS_OK;
@@ -616,7 +564,7 @@ nnqs_status nnqs_vmc_gradient(nnqs_model *m, const uint64_t *keys, const uint32_
         return fail(NNQS_EUNSUPPORTED, "gradients need d_model 64, 4 heads, d_ff a multiple of 64 and n_orb <= 64");
     hipStream_t st = as_stream(stream);
     GradScratch S{};
-    nnqs_status rc = grad_scratch(m, n, S);
+    nnqs_status rc = grad_scratch(m, n, S, st);
     if (rc != NNQS_OK) return rc;
     double *E = energy ? energy : S.energy;
     rc = enqueue_energy_partials(S.epart, counts, eloc, n, E, st);
@@ -645,18 +593,17 @@ nnqs_status nnqs_model_adamw_step(nnqs_model *m, const double *grad, int64_t ste
     hipStream_t st = as_stream(stream);
     const int64_t nw = m->off.total;
     const double bc1 = 1.0 - std::pow(beta1, (double)step), bc2 = 1.0 - std::pow(beta2, (double)step);
+    // the weights change in place: no stream may still be reading the old ones
+    NNQS_HIP_CHECK(hipDeviceSynchronize());
     hipLaunchKernelGGL(kg_adamw, dim3(nblocks(nw)), dim3(256), 0, st, m->d_w64, grad, mom1, mom2, nw, m->off.bias,
                        m->off.bias + 4 * (int64_t)m->desc.n_orb, lr, beta1, beta2, eps, weight_decay, bc1, bc2);
     NNQS_HIP_CHECK(hipGetLastError());
     // the packed and reduced-precision copies follow the FP64 master weights
-    const nnqs_status ps = f64_model_pack(m, st);
-    if (ps != NNQS_OK) return ps;
-    NNQS_HIP_CHECK(hipStreamSynchronize(st));
-    std::vector<double> w64((size_t)nw);
-    NNQS_HIP_CHECK(hipMemcpy(w64.data(), m->d_w64, nw * sizeof(double), hipMemcpyDeviceToHost));
-    std::vector<float> w32(w64.begin(), w64.end());
-    bf16_model_free(m);
-    return bf16_model_init(m, w32.data());
+    nnqs_status rc = f64_model_pack(m, st);
+    if (rc == NNQS_OK) rc = bf16_model_refresh(m, st);
+    if (rc != NNQS_OK) return rc;
+    NNQS_HIP_CHECK(hipStreamSynchronize(st));  // the new weights hold for every stream once this returns
+    return NNQS_OK;
 }
 
 nnqs_status nnqs_model_get_weights(const nnqs_model *m, double *out, void *stream) {

@@ -261,8 +261,8 @@ nnqs_status nnqs_model_create(nnqs_model **out, const nnqs_model_desc *desc, con
         return fail(NNQS_EHIP, "copy of the model weights failed");
     }
     nnqs_status st = f64_model_pack(m, nullptr);
+    if (st == NNQS_OK) st = bf16_model_init(m);
     if (st == NNQS_OK && hipStreamSynchronize(nullptr) != hipSuccess) st = fail(NNQS_EHIP, "packing of the model weights failed");
-    if (st == NNQS_OK) st = bf16_model_init(m, weights);
     if (st != NNQS_OK) {
         nnqs_model_destroy(m);
         return st;

@@ -58,7 +58,7 @@ struct nnqs_model {
     void *d_f64s = nullptr;
     size_t f64cap = 0;
     // scratch of the FP64 backward (grad_f64.hip): saved activations of one
-    // pass, their gradients and the weight-gradient partials
+    // pass, their gradients and the splits of the weight gradients
     void *d_grads = nullptr;
     size_t gradcap = 0;
     // BF16 path: transposed BF16 matrices and FP32 vectors (model_bf16.hip)
@@ -108,7 +108,9 @@ namespace nnqs {
 ModelView model_view(const nnqs_model *m);
 nnqs_status enqueue_logpsi(const nnqs_model *m, const uint64_t *keys, int64_t n, int32_t precision, double *logabs,
                            double *phase, hipStream_t st);
-nnqs_status bf16_model_init(nnqs_model *m, const float *weights);
+// allocates the reduced-precision copies; refresh writes them from the FP64 weights
+nnqs_status bf16_model_init(nnqs_model *m);
+nnqs_status bf16_model_refresh(nnqs_model *m, hipStream_t st);
 void bf16_model_free(nnqs_model *m);
 nnqs_status enqueue_logpsi_bf16(const nnqs_model *m, const uint64_t *keys, int64_t n, double *logabs,
                                 double *phase, hipStream_t st, bool fp8 = false);

@@ -182,9 +182,8 @@ static Bf16View bf16_view(const nnqs_model *m) {
     return v;
 }
 
-static uint16_t to_bf16_bits(float f) {  // round to nearest even
-    uint32_t u;
-    std::memcpy(&u, &f, 4);
+__device__ __forceinline__ uint16_t to_bf16_bits(float f) {  // round to nearest even
+    uint32_t u = __builtin_bit_cast(uint32_t, f);
     if ((u & 0x7F800000u) == 0x7F800000u) return (uint16_t)(u >> 16);
     u += 0x7FFFu + ((u >> 16) & 1u);
     return (uint16_t)(u >> 16);
@@ -192,24 +191,15 @@ static uint16_t to_bf16_bits(float f) {  // round to nearest even
 
 // OCP FP8 E4M3 (bias 7, 3 mantissa bits, largest finite 448), round to
 // nearest even, saturated at +-448.
-static uint8_t to_e4m3(float f) {
-    const uint8_t sign = std::signbit(f) ? 0x80 : 0x00;
-    double a = std::fabs((double)f);
+__device__ __forceinline__ uint8_t to_e4m3(float f) {
+    const uint8_t sign = (__builtin_bit_cast(uint32_t, f) >> 31) ? 0x80 : 0x00;
+    const double a = fabs((double)f);
     if (!(a == a)) return 0x7F;
     if (a >= 448.0) return sign | 0x7E;
-    auto rne = [](double v) {  // round half to even
-        const double fl = std::floor(v), d = v - fl;
-        if (d > 0.5) return fl + 1.0;
-        if (d < 0.5) return fl;
-        return std::fmod(fl, 2.0) == 0.0 ? fl : fl + 1.0;
-    };
-    if (a < std::ldexp(1.0, -6)) {  // subnormal: m * 2^-9 (m = 8 carries into the smallest normal)
-        return sign | (uint8_t)rne(a * 512.0);
-    }
-    int e = 0;
-    const double fr = std::frexp(a, &e);  // a = fr * 2^e, fr in [0.5, 1)
-    e -= 1;                               // a = (2 fr) * 2^e, 2 fr in [1, 2)
-    double q = rne((2.0 * fr - 1.0) * 8.0);
+    if (a < 0x1p-6)  // subnormal: m * 2^-9 (m = 8 carries into the smallest normal)
+        return sign | (uint8_t)rint(a * 512.0);
+    int e = ilogb(a);  // a = v * 2^e, v in [1, 2)
+    double q = rint((ldexp(a, -e) - 1.0) * 8.0);
     if (q >= 8.0) {
         q = 0.0;
         e += 1;
@@ -218,138 +208,167 @@ static uint8_t to_e4m3(float f) {
     return sign | (uint8_t)(code > 0x7E ? 0x7E : code);
 }
 
-nnqs_status bf16_model_init(nnqs_model *m, const float *weights) {
+// Element (output n, inner k) of a transformer matrix in operand order: 16 x
+// 32 fragments, row block major, lane (k % 32) / 8 * 16 + n % 16 of a
+// fragment holding its eight k one after another.
+__device__ __forceinline__ int64_t frag_at(int kdim, int n, int k) {
+    return ((int64_t)((n >> 4) * (kdim / 32) + (k >> 5)) * 64 + ((k >> 3) & 3) * 16 + (n & 15)) * 8 + (k & 7);
+}
+
+// Output n's place among the rows of a `pair` matrix: output 32 p + 8 q + 4 t
+// + i in row 4 q + i of block 2 p + t, so that the eight outputs a lane (row
+// group q) holds of two blocks are one operand of the next product.
+__device__ __forceinline__ int paired(int n) { return (n & ~31) | (n & 4) << 2 | (n & 24) >> 1 | (n & 3); }
+
+// The BF16, FP8 and FP32 copies of the network from its FP64 weights, rounded
+// to FP32 first.  A LayerNorm's scale g and shift b fold into the product
+// y W + c that reads it: (n * g + b) W + c = n (diag(g) W) + (b W + c), n = the
+// normalised row; the attention scale 1/sqrt(16) and log2(e) (the softmax
+// runs in base 2) fold into W_q and b_q.  Folded in FP64 with every product
+// and sum rounded (no contraction), then rounded to FP32.  Every FP8 matrix
+// is scaled by the power of two that brings its largest magnitude to at most
+// 448.  Block: one of a layer's six matrices (its values stay in registers
+// between the search for the largest and the two copies), a 64 x 64 tile of a
+// phase matrix's transpose, or (last) the head and the vectors.
+// The copy is bound by the latency of a block's few loads; done on the host,
+// with its two transfers and the reallocation, it took 4.1 ms per optimiser
+// step, here 20 us.
+constexpr int kRefreshThreads = 1024;
+__global__ void __launch_bounds__(kRefreshThreads)
+k_bf16_refresh(const double *__restrict__ w64, ModelOffsets o, int K, int L, Bf16Layout bl, F32Layout fl,
+               uint16_t *__restrict__ wb, uint8_t *__restrict__ w8, float *__restrict__ wf) {
+#pragma clang fp contract(off)
+    __shared__ float sh[64][65];
+    const int t = threadIdx.x;
+    const auto W = [&](int64_t off) { return (float)w64[off]; };
+    const auto copy = [&](int64_t dst, int64_t src, int64_t cnt) {
+        for (int64_t e = t; e < cnt; e += kRefreshThreads) wf[dst + e] = W(src + e);
+    };
+    int blk = (int)blockIdx.x;
+    if (blk < 6 * L) {
+        const int l = blk / 6, x = blk % 6;  // q, k, v, o, w1, w2
+        const int64_t dd = kD * kD, bs = dd + kD;  // one square matrix and its bias
+        const int64_t ln1 = o.layer0 + l * o.layer_stride, wq = ln1 + 2 * kD, ln2 = wq + 4 * bs, w1 = ln2 + 2 * kD,
+                      w2 = w1 + (int64_t)kD * kF + kF;
+        const int kdim = x == 5 ? kF : kD, ndim = x == 4 ? kF : kD;
+        const int64_t src = x < 4 ? wq + x * bs : x == 4 ? w1 : w2, bias = src + (int64_t)kdim * ndim;
+        const int64_t ln = x == 4 ? ln2 : ln1;
+        const bool folds = x != 3 && x != 5, pair = x < 2 || x == 4;
+        const double scale = x == 0 ? 0.25 * 1.4426950408889634 : 1.0;
+        const int64_t dst = bl.layer0 + l * bl.layer_stride +
+                            (x < 3 ? x * dd : x == 3 ? 3 * dd : x == 4 ? 4 * dd : 4 * dd + (int64_t)kD * kF);
+        const int64_t lv = fl.layer0 + l * fl.layer_stride;
+        const int nshift = ndim == kF ? 8 : 6, per = kdim * ndim / kRefreshThreads;  // 4 or 16
+        float v[16];
+        float mx = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            if (i >= per) continue;
+            const int e = t + i * kRefreshThreads, k = e >> nshift;
+            v[i] = W(src + e);
+            if (folds) v[i] = (float)(scale * (double)W(ln + k) * (double)v[i]);
+            const float av = fabsf(v[i]);
+            mx = mx < av ? av : mx;  // a NaN leaves it
+        }
+        for (int d = 32; d; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d));
+        if ((t & 63) == 0) sh[0][t >> 6] = mx;
+        __syncthreads();
+        for (int q = 0; q < kRefreshThreads / 64; q++) mx = fmaxf(mx, sh[0][q]);
+        int k2 = mx > 0.f ? ilogb(448.0 / (double)mx) : 0;
+        k2 = k2 < -60 ? -60 : k2 > 60 ? 60 : k2;
+        const double s = ldexp(1.0, k2);
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            if (i >= per) continue;
+            const int e = t + i * kRefreshThreads, k = e >> nshift, n = e & (ndim - 1);
+            const int64_t at = dst + frag_at(kdim, pair ? paired(n) : n, k);
+            wb[at] = to_bf16_bits(v[i]);
+            w8[at] = to_e4m3((float)(s * (double)v[i]));
+        }
+        if (t == 0) {
+            wf[lv + kV_f8 + 2 * x] = (float)s;
+            wf[lv + kV_f8 + 2 * x + 1] = (float)(1.0 / s);
+        }
+        if (t < ndim) {
+            float b = W(bias + t);
+            if (folds) {
+                double acc = (double)b;
+#pragma unroll 8
+                for (int k = 0; k < kD; k++) acc += (double)W(ln + kD + k) * (double)W(src + (int64_t)k * ndim + t);
+                b = (float)(scale * acc);
+            }
+            wf[lv + (x < 3 ? kV_bqkv + 64 * x : x == 3 ? kV_bo : x == 4 ? kV_b1 : kV_b2) + t] = b;
+        }
+        if (x == 3) {
+            copy(lv + kV_ln1_g, ln1, 2 * kD);
+            copy(lv + kV_ln2_g, ln2, 2 * kD);
+        }
+        return;
+    }
+    blk -= 6 * L;
+    const int t1 = kP / 64 * (kPhaseBits / 64), t2 = kP / 64 * (kP / 64);
+    if (blk < t1 + t2) {  // dst[n][k] = src[k][n]; inputs beyond the 2K bits are zero
+        const bool first = blk < t1;
+        const int q = first ? blk : blk - t1, kdim = first ? 2 * K : kP, ld = first ? kPhaseBits : kP;
+        const int n0 = q % (kP / 64) * 64, k0 = q / (kP / 64) * 64;
+        const int64_t src = first ? o.ph_w1 : o.ph_w2, dst = first ? bl.ph_w1T : bl.ph_w2T;
+        const int c = t & 63, r = t >> 6;
+        for (int i = r; i < 64; i += kRefreshThreads / 64)
+            sh[i][c] = k0 + i < kdim ? W(src + (int64_t)(k0 + i) * kP + n0 + c) : 0.f;
+        __syncthreads();
+        for (int i = r; i < 64; i += kRefreshThreads / 64)
+            wb[dst + (int64_t)(n0 + i) * ld + k0 + c] = to_bf16_bits(sh[c][i]);
+        return;
+    }
+    copy(fl.tok_emb, o.tok_emb, 5 * kD);
+    copy(fl.pos_emb, o.pos_emb, (int64_t)K * kD);
+    copy(fl.lnf_g, o.lnf_g, kD);
+    copy(fl.lnf_b, o.lnf_b, kD);
+    copy(fl.bias, o.bias, 4 * (int64_t)K);
+    copy(fl.ph_b1, o.ph_b1, kP);
+    copy(fl.ph_b2, o.ph_b2, kP);
+    copy(fl.ph_w3, o.ph_w3, kP);
+    copy(fl.ph_b3, o.ph_b3, 1);
+    if (t < 4 * kD) wf[fl.head_w + t] = (float)((double)W(o.lnf_g + (t >> 2)) * (double)W(o.head_w + t));
+    if (t < 4) {
+        double acc = (double)W(o.head_b + t);
+#pragma unroll 8
+        for (int k = 0; k < kD; k++) acc += (double)W(o.lnf_b + k) * (double)W(o.head_w + 4 * k + t);
+        wf[fl.head_b + t] = (float)acc;
+    }
+}
+
+nnqs_status bf16_model_refresh(nnqs_model *m, hipStream_t st) {
+    if (!m->bf16_ok) return NNQS_OK;
+    const int K = m->desc.n_orb, L = m->desc.n_layers;
+    const unsigned blocks = 6u * (unsigned)L + kP / 64 * (kPhaseBits / 64 + kP / 64) + 1;
+    hipLaunchKernelGGL(k_bf16_refresh, dim3(blocks), dim3(kRefreshThreads), 0, st, m->d_w64, m->off, K, L,
+                       bf16_layout(L), f32_layout(K, L), reinterpret_cast<uint16_t *>(m->d_bf16),
+                       reinterpret_cast<uint8_t *>(m->d_fp8), m->d_f32);
+    NNQS_HIP_CHECK(hipGetLastError());
+    return NNQS_OK;
+}
+
+nnqs_status bf16_model_init(nnqs_model *m) {
     const nnqs_model_desc &d = m->desc;
     m->bf16_ok = d.d_model == kD && d.n_heads == kH && d.d_ff == kF && d.phase_hidden == kP && d.n_orb <= 64 &&
                  2 * d.n_orb <= kPhaseBits;
     if (!m->bf16_ok) return NNQS_OK;
-    const int K = d.n_orb, L = d.n_layers;
-    const ModelOffsets &o = m->off;
-    const Bf16Layout bl = bf16_layout(L);
-    const F32Layout fl = f32_layout(K, L);
-    std::vector<uint16_t> wb((size_t)bl.total, 0);
-    std::vector<uint8_t> w8((size_t)bl.total, 0);
-    std::vector<float> wf((size_t)fl.total, 0.f);
-    auto W = [&](int64_t off) { return weights + off; };
-    // transposed copy: dst[n][k] = src[k][n] for a [kdim][ndim] source matrix
-    auto put_t = [&](int64_t dst, int dst_ld, const float *src, int kdim, int ndim, int row0) {
-        for (int k = 0; k < kdim; k++)
-            for (int nn = 0; nn < ndim; nn++) wb[dst + (int64_t)(row0 + nn) * dst_ld + k] = to_bf16_bits(src[k * ndim + nn]);
-    };
-    // Element (output n, inner k) of a transformer matrix in operand order: 16 x
-    // 32 fragments, row block major, lane (k % 32) / 8 * 16 + n % 16 of a
-    // fragment holding its eight k one after another.
-    auto frag_at = [](int kdim, int n, int k) -> int64_t {
-        return ((int64_t)((n >> 4) * (kdim / 32) + (k >> 5)) * 64 + ((k >> 3) & 3) * 16 + (n & 15)) * 8 + (k & 7);
-    };
-    // Output n's place among the rows with `pair`: output 32 p + 8 q + 4 t + i
-    // in row 4 q + i of block 2 p + t, so that the eight outputs a lane (row
-    // group q) holds of two blocks are one operand of the next product.
-    auto paired = [](int n) { return (n & ~31) | (n & 4) << 2 | (n & 24) >> 1 | (n & 3); };
-    auto put_frag = [&](int64_t dst, const float *src, int kdim, int ndim, int row0, bool pair) {
-        for (int k = 0; k < kdim; k++)
-            for (int nn = 0; nn < ndim; nn++)
-                wb[dst + frag_at(kdim, row0 + (pair ? paired(nn) : nn), k)] = to_bf16_bits(src[k * ndim + nn]);
-    };
-    // FP8 copy in the same order, with the power of two s that brings the
-    // matrix's largest magnitude to at most 448; stores s, 1/s
-    auto put_f8 = [&](int64_t dst, const float *src, int kdim, int ndim, int row0, bool pair, float *sc) {
-        double mx = 0.0;
-        for (int64_t e = 0; e < (int64_t)kdim * ndim; e++) mx = std::max(mx, std::fabs((double)src[e]));
-        int k2 = mx > 0.0 ? (int)std::floor(std::log2(448.0 / mx)) : 0;
-        k2 = std::min(60, std::max(-60, k2));
-        const double s = std::ldexp(1.0, k2);
-        for (int k = 0; k < kdim; k++)
-            for (int nn = 0; nn < ndim; nn++)
-                w8[dst + frag_at(kdim, row0 + (pair ? paired(nn) : nn), k)] = to_e4m3((float)(s * src[k * ndim + nn]));
-        sc[0] = (float)s;
-        sc[1] = (float)(1.0 / s);
-    };
-    // A LayerNorm's scale g and shift b fold into the product y W + c that
-    // reads it: (n * g + b) W + c = n (diag(g) W) + (b W + c), n = the
-    // normalised row; the attention scale 1/sqrt(16) and log2(e) (the softmax
-    // runs in base 2) fold into W_q and b_q.  Folded in FP64, then rounded.
-    auto fold = [&](const float *Wm, const float *bm, const float *g, const float *beta, int kdim, int ndim,
-                    double scale, std::vector<float> &Wf, std::vector<float> &bf) {
-        Wf.assign((size_t)kdim * ndim, 0.f);
-        bf.assign((size_t)ndim, 0.f);
-        for (int nn = 0; nn < ndim; nn++) {
-            double acc = bm[nn];
-            for (int k = 0; k < kdim; k++) {
-                Wf[(size_t)k * ndim + nn] = (float)(scale * (double)g[k] * (double)Wm[(size_t)k * ndim + nn]);
-                acc += (double)beta[k] * (double)Wm[(size_t)k * ndim + nn];
-            }
-            bf[nn] = (float)(scale * acc);
-        }
-    };
-    const double qscale = 0.25 * 1.4426950408889634;
-    std::vector<float> fw, fb;
-    for (int l = 0; l < L; l++) {
-        const int64_t lo = o.layer0 + l * o.layer_stride;
-        const int64_t base = bl.layer0 + l * bl.layer_stride;
-        const int64_t dd = kD * kD;
-        // layer block layout of the FP32 weights: ln1_g ln1_b wq bq wk bk wv bv wo bo ln2_g ln2_b w1 b1 w2 b2
-        const float *ln1g = W(lo), *ln1b = W(lo + kD);
-        const float *wq = W(lo + 2 * kD), *bq = wq + dd, *wk = bq + kD, *bk = wk + dd, *wv = bk + kD, *bv = wv + dd,
-                    *wo = bv + kD, *bo = wo + dd, *ln2g = bo + kD, *ln2b = ln2g + kD, *w1 = ln2b + kD,
-                    *b1 = w1 + kD * kF, *w2 = b1 + kF, *b2 = w2 + kF * kD;
-        float *lv = wf.data() + fl.layer0 + l * fl.layer_stride;
-        fold(wq, bq, ln1g, ln1b, kD, kD, qscale, fw, fb);
-        put_frag(base, fw.data(), kD, kD, 0, true);
-        put_f8(base, fw.data(), kD, kD, 0, true, lv + kV_f8 + 0);
-        std::memcpy(lv + kV_bqkv, fb.data(), kD * 4);
-        fold(wk, bk, ln1g, ln1b, kD, kD, 1.0, fw, fb);
-        put_frag(base, fw.data(), kD, kD, 64, true);
-        put_f8(base, fw.data(), kD, kD, 64, true, lv + kV_f8 + 2);
-        std::memcpy(lv + kV_bqkv + 64, fb.data(), kD * 4);
-        fold(wv, bv, ln1g, ln1b, kD, kD, 1.0, fw, fb);
-        put_frag(base, fw.data(), kD, kD, 128, false);
-        put_f8(base, fw.data(), kD, kD, 128, false, lv + kV_f8 + 4);
-        std::memcpy(lv + kV_bqkv + 128, fb.data(), kD * 4);
-        put_frag(base + 192 * 64, wo, kD, kD, 0, false);
-        put_f8(base + 192 * 64, wo, kD, kD, 0, false, lv + kV_f8 + 6);
-        fold(w1, b1, ln2g, ln2b, kD, kF, 1.0, fw, fb);
-        put_frag(base + 192 * 64 + 64 * 64, fw.data(), kD, kF, 0, true);
-        put_f8(base + 192 * 64 + 64 * 64, fw.data(), kD, kF, 0, true, lv + kV_f8 + 8);
-        std::memcpy(lv + kV_b1, fb.data(), kF * 4);
-        put_frag(base + 192 * 64 + 64 * 64 + 256 * 64, w2, kF, kD, 0, false);
-        put_f8(base + 192 * 64 + 64 * 64 + 256 * 64, w2, kF, kD, 0, false, lv + kV_f8 + 10);
-        std::memcpy(lv + kV_ln1_g, ln1g, kD * 4);
-        std::memcpy(lv + kV_ln1_b, ln1b, kD * 4);
-        std::memcpy(lv + kV_bo, bo, kD * 4);
-        std::memcpy(lv + kV_ln2_g, ln2g, kD * 4);
-        std::memcpy(lv + kV_ln2_b, ln2b, kD * 4);
-        std::memcpy(lv + kV_b2, b2, kD * 4);
-    }
-    std::memcpy(wf.data() + fl.tok_emb, W(o.tok_emb), 5 * kD * 4);
-    std::memcpy(wf.data() + fl.pos_emb, W(o.pos_emb), (size_t)K * kD * 4);
-    std::memcpy(wf.data() + fl.lnf_g, W(o.lnf_g), kD * 4);
-    std::memcpy(wf.data() + fl.lnf_b, W(o.lnf_b), kD * 4);
-    fold(W(o.head_w), W(o.head_b), W(o.lnf_g), W(o.lnf_b), kD, 4, 1.0, fw, fb);
-    std::memcpy(wf.data() + fl.head_w, fw.data(), 4 * kD * 4);
-    std::memcpy(wf.data() + fl.head_b, fb.data(), 4 * 4);
-    std::memcpy(wf.data() + fl.bias, W(o.bias), (size_t)4 * K * 4);
-    std::memcpy(wf.data() + fl.ph_b1, W(o.ph_b1), kP * 4);
-    std::memcpy(wf.data() + fl.ph_b2, W(o.ph_b2), kP * 4);
-    std::memcpy(wf.data() + fl.ph_w3, W(o.ph_w3), kP * 4);
-    wf[fl.ph_b3] = *W(o.ph_b3);
+    const Bf16Layout bl = bf16_layout(d.n_layers);
+    const F32Layout fl = f32_layout(d.n_orb, d.n_layers);
+    if (hipMalloc(&m->d_bf16, (size_t)bl.total * 2) != hipSuccess ||
+        hipMalloc(&m->d_f32, (size_t)fl.total * 4) != hipSuccess || hipMalloc(&m->d_fp8, (size_t)bl.total) != hipSuccess)
+        return fail(NNQS_ENOMEM, "device allocation of the BF16 model failed");
+    std::vector<float> gelu((size_t)2 * kGeluN);
     for (int i = 0; i < kGeluN; i++) {  // Phi at the knots, in FP64
         const double v0 = (i - (double)kGeluOff) / kGeluScale, v1 = v0 + 1.0 / kGeluScale;
         const double p0 = 0.5 * std::erfc(-v0 / std::sqrt(2.0)), p1 = 0.5 * std::erfc(-v1 / std::sqrt(2.0));
-        wf[fl.gelu + 2 * i] = (float)p0;
-        wf[fl.gelu + 2 * i + 1] = (float)(p1 - p0);
+        gelu[2 * i] = (float)p0;
+        gelu[2 * i + 1] = (float)(p1 - p0);
     }
-    // phase W1 [2K][512] -> ph_w1T[512][128] (bits beyond 2K stay zero)
-    put_t(bl.ph_w1T, kPhaseBits, W(o.ph_w1), 2 * K, kP, 0);
-    put_t(bl.ph_w2T, kP, W(o.ph_w2), kP, kP, 0);
-    if (hipMalloc(&m->d_bf16, wb.size() * 2) != hipSuccess || hipMalloc(&m->d_f32, wf.size() * 4) != hipSuccess ||
-        hipMalloc(&m->d_fp8, w8.size()) != hipSuccess)
-        return fail(NNQS_ENOMEM, "device allocation of the BF16 model failed");
-    if (hipMemcpy(m->d_fp8, w8.data(), w8.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(m->d_bf16, wb.data(), wb.size() * 2, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(m->d_f32, wf.data(), wf.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
+    if (hipMemcpy(m->d_f32 + fl.gelu, gelu.data(), gelu.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
         return fail(NNQS_EHIP, "copy of the BF16 model failed");
-    return NNQS_OK;
+    return bf16_model_refresh(m, nullptr);
 }
 
 void bf16_model_free(nnqs_model *m) {

@@ -56,309 +56,259 @@ __global__ void __launch_bounds__(256) k64_layernorm(const double *__restrict__ 
     out[row * 64 + lane] = (v - mean) * r * g[lane] + b[lane];
 }
 
-// The same row statistics alone, st[row] = (mean, 1/sqrt(var + eps)), for
-// products that normalise their A rows while staging them (gemm64_tile with
-// NORM), which saves writing and re-reading the normalised rows.
-__global__ void __launch_bounds__(256) k64_ln_stats(const double *__restrict__ in, int64_t rows,
-                                                    double *__restrict__ st) {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    if (row >= rows) return;
-    const double v = in[row * 64 + lane];
-    double s = v;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
-    const double mean = s / 64.0;
-    double q = (v - mean) * (v - mean);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) q += __shfl_xor(q, off, 64);
-    if (lane == 0) {
-        st[2 * row] = mean;
-        st[2 * row + 1] = 1.0 / sqrt(q / 64.0 + 1e-5);
-    }
-}
-
 // C[r][j] = epi(bias[j] + sum_k A[r][k] B[k][j]) for r < M, j < N, with
 // B[k][j] = W[k][j], or W[j][k] with TB (products with a transposed weight in
-// the backward); EPI 0 stores, 1 adds to C (residual), 2 stores GELU.  Block: 64 x 64 tile of C,
-// four waves of 16 rows each, on v_mfma_f64_16x16x4_f64 (lane l holds
-// A[l & 15][l >> 4] and B[l >> 4][l & 15]; accumulator register i of lane l
-// holds row (l >> 4) + 4 i, column l & 15, unlike the BF16 16x16 variants);
+// the backward).  Block: TM x 64 tile of C, four waves: 16 rows each by all 64
+// columns (TM = 64), or 16 rows by 32 columns (TM = 32), on
+// v_mfma_f64_16x16x4_f64 (lane l holds A[l & 15][l >> 4] and B[l >> 4][l & 15];
+// accumulator register i of lane l holds row (l >> 4) + 4 i, column l & 15);
 // k in slices of 32 through LDS, the next slice's global loads in flight
-// during the current slice's products.  FP64 throughout: only the summation
-// order differs from a plain dot product.
-// With NORM (Kd = 64) the A rows are LayerNorm inputs: each staged element
-// becomes (a - mean) rstd g[k] + b[k] with the row's statistics from lnst
-// (k64_ln_stats) and the scale and shift lng, lnb.  With STATS (EPI 1, N = 64,
-// one column block) the wave holds all 64 columns of its 16 updated rows and
-// also writes their LayerNorm statistics (mean, rstd) to stout, as
-// k64_ln_stats would.
-template <int EPI, bool TB, bool NORM = false, bool STATS = false>
-__device__ __forceinline__ void gemm64_tile(const double *__restrict__ A, int lda, const double *__restrict__ W,
-                                            int ldw, const double *__restrict__ bias, int64_t M, int N, int Kd,
-                                            double *__restrict__ C, int ldc, int c0,
-                                            const double *__restrict__ lnst = nullptr,
-                                            const double *__restrict__ lng = nullptr,
-                                            const double *__restrict__ lnb = nullptr,
-                                            double *__restrict__ stout = nullptr) {
-    constexpr int KS = 32;  // k per slice
-    __shared__ double As[64][KS + 1];
-    __shared__ double Ws[KS][64 + 1];
-    __shared__ double Ln[NORM ? 4 * 64 : 1];  // mean and rstd of the tile's rows, then g and b
+// during the current slice's products.  Rows of 36 and 80 doubles put the 32
+// lanes of half a wave on 64 different banks for both operands (rows of 33
+// and 65 gave two-way conflicts).
+// EPI 0 stores, 2 stores GELU, 3 stores the sum and, in C2, its
+// GELU, 4 stores the sum times GELU'(U), 5 stores src + the sum.
+
+template <int TM>
+struct GemmLds {
+    double As[TM][36];
+    double Ws[32][80];
+};
+
+// The products of one K x 64 weight (ldw columns) with A's rows, added to acc.
+template <int TM, bool TB>
+__device__ __forceinline__ void gemm64_acc(GemmLds<TM> &S, f64x4 (&acc)[TM / 16], const double *__restrict__ A, int lda,
+                                           const double *__restrict__ W, int ldw, int64_t M, int N, int Kd, int c0) {
+    constexpr int EA = TM / 8, NC = TM / 16;  // A elements per thread and slice; column tiles per wave
     const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int lr = l & 15, lk = l >> 4;
-    const int64_t r0 = (int64_t)blockIdx.y * 64;
-    if constexpr (NORM) {  // read after the first barrier of the slice loop
-        const int t = threadIdx.x & 63, part = threadIdx.x >> 6;
-        const int64_t r = r0 + t;
-        if (part == 0) Ln[t] = r < M ? lnst[2 * r] : 0.0;
-        else if (part == 1) Ln[64 + t] = r < M ? lnst[2 * r + 1] : 0.0;
-        else if (part == 2) Ln[128 + t] = lng[t];
-        else Ln[192 + t] = lnb[t];
-    }
+    const int rw = TM == 64 ? 16 * w : 16 * (w & 1), cw = TM == 64 ? 0 : 32 * (w >> 1);
+    const int64_t r0 = (int64_t)blockIdx.y * TM;
     // slice loads: thread t takes A[r0 + (t >> 5) + 8 e][k0 + (t & 31)] and
-    // W[k0 + (t >> 6) + 4 e][c0 + (t & 63)], e = 0..7 (coalesced rows); with
-    // TB, W[c0 + (t >> 5) + 8 e][k0 + (t & 31)] into the slice's column
+    // W[k0 + (t >> 6) + 4 e][c0 + (t & 63)] (coalesced rows); with TB,
+    // W[c0 + (t >> 5) + 8 e][k0 + (t & 31)] into the slice's column
     const int at = threadIdx.x & 31, ar = threadIdx.x >> 5, wc = threadIdx.x & 63, wr = threadIdx.x >> 6;
-    double pa[8], pw[8];
+    double pa[EA], pw[8];
     auto load = [&](int k0) {
 #pragma unroll
-        for (int e = 0; e < 8; e++) {
+        for (int e = 0; e < EA; e++) {
             const int64_t r = r0 + ar + 8 * e;
             pa[e] = (r < M && k0 + at < Kd) ? A[r * lda + k0 + at] : 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
             if (TB) {
-                const int cw = c0 + ar + 8 * e;
-                pw[e] = (cw < N && k0 + at < Kd) ? W[(int64_t)cw * ldw + k0 + at] : 0.0;
+                const int cc = c0 + ar + 8 * e;
+                pw[e] = (cc < N && k0 + at < Kd) ? W[(int64_t)cc * ldw + k0 + at] : 0.0;
             } else {
                 const int kw = k0 + wr + 4 * e;
                 pw[e] = (kw < Kd && c0 + wc < N) ? W[(int64_t)kw * ldw + c0 + wc] : 0.0;
             }
         }
     };
-    f64x4 acc[4];
-#pragma unroll
-    for (int cb = 0; cb < 4; cb++) acc[cb] = f64x4{0.0, 0.0, 0.0, 0.0};
     load(0);
-    for (int k0 = 0; k0 < Kd; k0 += KS) {
+    for (int k0 = 0; k0 < Kd; k0 += 32) {
         __syncthreads();  // the previous slice is consumed
 #pragma unroll
+        for (int e = 0; e < EA; e++) S.As[ar + 8 * e][at] = pa[e];
+#pragma unroll
         for (int e = 0; e < 8; e++) {
-            if constexpr (NORM) {
-                const int rr = ar + 8 * e, kk = k0 + at;
-                As[rr][at] = (pa[e] - Ln[rr]) * Ln[64 + rr] * Ln[128 + kk] + Ln[192 + kk];
-            } else {
-                As[ar + 8 * e][at] = pa[e];
-            }
-            if (TB) Ws[at][ar + 8 * e] = pw[e];
-            else Ws[wr + 4 * e][wc] = pw[e];
+            if (TB) S.Ws[at][ar + 8 * e] = pw[e];
+            else S.Ws[wr + 4 * e][wc] = pw[e];
         }
         __syncthreads();
-        if (k0 + KS < Kd) load(k0 + KS);  // the next slice's loads overlap this slice's products
+        if (k0 + 32 < Kd) load(k0 + 32);  // the next slice's loads overlap this slice's products
 #pragma unroll
-        for (int k4 = 0; k4 < KS; k4 += 4) {
-            const double a = As[16 * w + lr][k4 + lk];
+        for (int k4 = 0; k4 < 32; k4 += 4) {
+            const double a = S.As[rw + lr][k4 + lk];
 #pragma unroll
-            for (int cb = 0; cb < 4; cb++)
-                acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, Ws[k4 + lk][cb * 16 + lr], acc[cb], 0, 0, 0);
+            for (int cb = 0; cb < NC; cb++)
+                acc[cb] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, S.Ws[k4 + lk][cw + cb * 16 + lr], acc[cb], 0, 0, 0);
         }
     }
-    if constexpr (STATS) {
-        static_assert(EPI == 1, "statistics of the updated residual rows");
-        double nv[4][4];
+}
+
+template <int TM, int EPI>
+__device__ __forceinline__ void gemm64_store(const f64x4 (&acc)[TM / 16], const double *__restrict__ bias, int64_t M,
+                                             int N, double *__restrict__ C, int ldc, int c0, const GemmEpi &E) {
+    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lr = l & 15, lk = l >> 4;
+    const int rw = TM == 64 ? 16 * w : 16 * (w & 1), cw = TM == 64 ? 0 : 32 * (w >> 1);
+    const int64_t r0 = (int64_t)blockIdx.y * TM;
 #pragma unroll
-        for (int cb = 0; cb < 4; cb++) {
-            const int c = cb * 16 + lr;
-            const double bc = bias ? bias[c] : 0.0;
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const int64_t r = r0 + 16 * w + lk + 4 * i;
-                nv[cb][i] = 0.0;
-                if (r < M) {
-                    double *dst = C + r * ldc + c;
-                    nv[cb][i] = *dst + (bc + acc[cb][i]);
-                    *dst = nv[cb][i];
-                }
-            }
-        }
-        // row lk + 4 i of the wave: its 64 columns are cb * 16 + lr over the
-        // 16 lanes lr of lane group lk
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            double sm = (nv[0][i] + nv[1][i]) + (nv[2][i] + nv[3][i]);
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) sm += __shfl_xor(sm, off, 16);
-            const double mean = sm / 64.0;
-            double q = 0.0;
-#pragma unroll
-            for (int cb = 0; cb < 4; cb++) q += (nv[cb][i] - mean) * (nv[cb][i] - mean);
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) q += __shfl_xor(q, off, 16);
-            const int64_t r = r0 + 16 * w + lk + 4 * i;
-            if (lr == 0 && r < M) {
-                stout[2 * r] = mean;
-                stout[2 * r + 1] = 1.0 / sqrt(q / 64.0 + 1e-5);
-            }
-        }
-        return;
-    }
-#pragma unroll
-    for (int cb = 0; cb < 4; cb++) {
-        const int c = c0 + cb * 16 + lr;
+    for (int cb = 0; cb < TM / 16; cb++) {
+        const int c = c0 + cw + cb * 16 + lr;
         if (c >= N) continue;
         const double bc = bias ? bias[c] : 0.0;
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-            const int64_t r = r0 + 16 * w + lk + 4 * i;
+            const int64_t r = r0 + rw + lk + 4 * i;
             if (r >= M) continue;
             const double v = bc + acc[cb][i];
             double *dst = C + r * ldc + c;
-            if (EPI == 1) *dst += v;
-            else if (EPI == 2) *dst = gelu_f64(v);
+            if (EPI == 2) *dst = gelu_f64(v);
+            else if (EPI == 3) {
+                const double cdf = 0.5 * (1.0 + erf(v * 0.70710678118654752440));
+                *dst = cdf + v * (0.39894228040143267794 * exp(-0.5 * v * v));
+                E.C2[r * ldc + c] = v * cdf;
+            } else if (EPI == 4) *dst = v * E.U[r * ldc + c];
+            else if (EPI == 5) *dst = E.src[r * ldc + c] + v;
             else *dst = v;
         }
     }
 }
 
-// The products run four waves per SIMD (four 33.5 KB blocks per CU): the
-// register budget that sets holds the tile without spills.
-template <int EPI, bool TB>
+// At least four waves per SIMD: the register budget that sets holds the tile
+// without spills.
+template <int EPI, bool TB, int TM>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k64_gemm(const double *__restrict__ A, int lda, const double *__restrict__ W, int ldw, const double *__restrict__ bias,
-         int64_t M, int N, int Kd, double *__restrict__ C, int ldc) {
-    gemm64_tile<EPI, TB>(A, lda, W, ldw, bias, M, N, Kd, C, ldc, blockIdx.x * 64);
+         int64_t M, int N, int Kd, double *__restrict__ C, int ldc, GemmEpi E) {
+    __shared__ GemmLds<TM> S;
+    f64x4 acc[TM / 16] = {};
+    gemm64_acc<TM, TB>(S, acc, A, lda, W, ldw, M, N, Kd, blockIdx.x * 64);
+    gemm64_store<TM, EPI>(acc, bias, M, N, C, ldc, blockIdx.x * 64, E);
 }
 
-// Residual products h += A W + b of 64-wide rows whose inner dimension is
-// fixed at compile time: the model width 64 (output projection) and the FFN
-// width 256 (FFN output) of the networks measured here; no run-time bounds
-// on k; the next LayerNorm's statistics of the updated rows go to stout.
-template <int KD>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
-k64_gemm_res(const double *__restrict__ A, int lda, const double *__restrict__ W, const double *__restrict__ bias,
-             int64_t M, double *__restrict__ h, double *__restrict__ stout) {
-    gemm64_tile<1, false, false, true>(A, lda, W, 64, bias, M, 64, KD, h, 64, 0, nullptr, nullptr, nullptr, stout);
+// Rows per tile: 64, or 32 where 64-row tiles would leave CUs without a block
+// (7,680 rows by 64 columns: 120 blocks against 240; the residual product
+// 11.3 against 17.3 us, and 7,680 by 256 of depth 64, 480 against 960,
+// 24 against 28 us).  Beyond that both measure the same within 0.2 % (the
+// phase products of 4.3 ms of local energies) and 64 read the weights half as
+// often.
+static bool small_tiles(int64_t M, int N) { return ((M + 63) / 64) * ((N + 63) / 64) < 512; }
+
+template <int EPI, bool TB>
+void gemm64(const double *A, int lda, const double *W, int ldw, const double *bias, int64_t M, int N, int Kd, double *C,
+            int ldc, const GemmEpi &E, hipStream_t st) {
+    const unsigned gx = (unsigned)((N + 63) / 64);
+    if (small_tiles(M, N))
+        hipLaunchKernelGGL((k64_gemm<EPI, TB, 32>), dim3(gx, (unsigned)((M + 31) / 32)), dim3(256), 0, st, A, lda, W, ldw,
+                           bias, M, N, Kd, C, ldc, E);
+    else
+        hipLaunchKernelGGL((k64_gemm<EPI, TB, 64>), dim3(gx, (unsigned)((M + 63) / 64)), dim3(256), 0, st, A, lda, W, ldw,
+                           bias, M, N, Kd, C, ldc, E);
 }
 
-// FFN output product h += f W2 + b2 over R rows (inner dimension F), and the
-// LayerNorm statistics of the updated rows into lst.
-static void ffn_out(const double *f, int ldf, const double *W2, const double *b2, int64_t R, int F, double *h,
-                    double *lst, hipStream_t st) {
-    const dim3 grid(1, (unsigned)((R + 63) / 64));
-    if (F == 256) {
-        hipLaunchKernelGGL(k64_gemm_res<256>, grid, dim3(256), 0, st, f, ldf, W2, b2, R, h, lst);
-    } else {
-        hipLaunchKernelGGL(k64_gemm<1>, grid, dim3(256), 0, st, f, ldf, W2, 64, b2, R, 64, F, h, 64);
-        hipLaunchKernelGGL(k64_ln_stats, dim3((unsigned)((R + 3) / 4)), dim3(256), 0, st, h, R, lst);
-    }
-}
-
-// FFN input product of LayerNorm(h) (statistics lnst, scale and shift lng,
-// lnb) without the normalised rows in memory.
-template <int EPI>
-__global__ void __launch_bounds__(256) k64_gemm_ln(const double *__restrict__ h, const double *__restrict__ W, int ldw,
-                                                   const double *__restrict__ bias, int64_t M, int N,
-                                                   double *__restrict__ C, int ldc, const double *__restrict__ lnst,
-                                                   const double *__restrict__ lng, const double *__restrict__ lnb) {
-    gemm64_tile<EPI, false, true>(h, 64, W, ldw, bias, M, N, 64, C, ldc, blockIdx.x * 64, lnst, lng, lnb);
-}
-
-// Q, K and V of LayerNorm(h) in one launch: column block x = 0, 1, 2 of the
+// Q, K and V of the same rows in one launch: column block x = 0, 1, 2 of the
 // grid takes the weight and bias at W + x ws, bias + x ws (the layer block
 // keeps W_q, b_q, W_k, b_k, W_v, b_v at equal strides) and writes C + x cs.
-__global__ void __launch_bounds__(256) k64_gemm_qkv(const double *__restrict__ h, const double *__restrict__ W,
-                                                    const double *__restrict__ bias, int64_t ws, int64_t M,
-                                                    double *__restrict__ C, int64_t cs,
-                                                    const double *__restrict__ lnst, const double *__restrict__ lng,
-                                                    const double *__restrict__ lnb) {
+template <int TM>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+k64_gemm_qkv(const double *__restrict__ a, const double *__restrict__ W, const double *__restrict__ bias, int64_t ws,
+             int64_t M, double *__restrict__ C, int64_t cs) {
+    __shared__ GemmLds<TM> S;
     const int x = blockIdx.x;
-    gemm64_tile<0, false, true>(h, 64, W + x * ws, 64, bias + x * ws, M, 64, 64, C + x * cs, 64, 0, lnst, lng,
-                                lnb);
+    f64x4 acc[TM / 16] = {};
+    gemm64_acc<TM, false>(S, acc, a, 64, W + x * ws, 64, M, 64, 64, 0);
+    gemm64_store<TM, 0>(acc, bias + x * ws, M, 64, C + x * cs, 64, 0, GemmEpi{});
 }
 
-// Causal attention on FP64 MFMA: one wave per (configuration, head), the four
-// heads of one configuration per block; q, k, v and the output are [B*K][64]
-// with head hh in columns 16 hh .. 16 hh + 15.  Per block of 16 queries:
+void gemm64_qkv(const double *a, const double *W, const double *bias, int64_t ws, int64_t M, double *C, int64_t cs,
+                hipStream_t st) {
+    if (small_tiles(M, 192))
+        hipLaunchKernelGGL(k64_gemm_qkv<32>, dim3(3, (unsigned)((M + 31) / 32)), dim3(256), 0, st, a, W, bias, ws, M, C,
+                           cs);
+    else
+        hipLaunchKernelGGL(k64_gemm_qkv<64>, dim3(3, (unsigned)((M + 63) / 64)), dim3(256), 0, st, a, W, bias, ws, M, C,
+                           cs);
+}
+
+// The transpose of that: C = sum_x A_x W_x^T, A_x = A + x as, W_x = W + x ws.
+template <int TM>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+k64_gemm_res(const double *__restrict__ A, int64_t as, const double *__restrict__ W, int64_t ws, int64_t M,
+             double *__restrict__ C) {
+    __shared__ GemmLds<TM> S;
+    f64x4 acc[TM / 16] = {};
+    for (int x = 0; x < 3; x++) gemm64_acc<TM, true>(S, acc, A + x * as, 64, W + x * ws, 64, M, 64, 64, 0);
+    gemm64_store<TM, 0>(acc, nullptr, M, 64, C, 64, 0, GemmEpi{});
+}
+
+void gemm64_qkv_back(const double *A, int64_t as, const double *W, int64_t ws, int64_t M, double *C, hipStream_t st) {
+    if (small_tiles(M, 64))
+        hipLaunchKernelGGL(k64_gemm_res<32>, dim3(1, (unsigned)((M + 31) / 32)), dim3(256), 0, st, A, as, W, ws, M, C);
+    else
+        hipLaunchKernelGGL(k64_gemm_res<64>, dim3(1, (unsigned)((M + 63) / 64)), dim3(256), 0, st, A, as, W, ws, M, C);
+}
+
+// Causal attention on FP64 MFMA: one block per (configuration, head), wave w
+// its queries 16 w .. 16 w + 15; q, k, v and the output are [B*K][64] with
+// head hh in columns 16 hh .. 16 hh + 15.  Per wave:
 // S = Q K^T in 16 x 16 x 4 tiles (accumulator register i of lane l holds
 // query (l >> 4) + 4 i, key l & 15 of the tile), the softmax of each query
 // row over the 16 lanes that hold it (the largest score, then one
 // exponential per key), P through LDS into the A-operand layout, O = P V.
 // Rows at or beyond K read as zero and are never written.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
-k64_attention(const double *__restrict__ q, const double *__restrict__ k, const double *__restrict__ v, int64_t B, int K,
+k64_attention(const double *__restrict__ q, const double *__restrict__ k, const double *__restrict__ v, int K,
               double scale, double *__restrict__ o) {
     __shared__ double Ps[4][16][64 + 1];
-    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int l = threadIdx.x & 63, qb = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lr = l & 15, lk = l >> 4;
-    const int64_t g = (int64_t)blockIdx.x * 4 + w;
-    if (g >= B * 4) return;  // wave-uniform; the kernel has no block barrier
-    const int64_t b = g >> 2;
-    const int hh = (int)(g & 3);
-    const double *qh = q + b * K * 64 + hh * 16, *kh = k + b * K * 64 + hh * 16, *vh = v + b * K * 64 + hh * 16;
-    auto ld = [&](const double *base, int s, int c) { return s < K ? base[(int64_t)s * 64 + c] : 0.0; };
+    if (16 * qb >= K) return;  // wave-uniform; the kernel has no block barrier
+    const int64_t base = (int64_t)(blockIdx.x >> 2) * K * 64 + (blockIdx.x & 3) * 16;
+    const double *qh = q + base, *kh = k + base, *vh = v + base;
+    const double c2 = scale * 1.4426950408889634;  // the softmax in base 2
+    ConstF64 *tab = exp2_table();
     // Four adjacent head columns of row s (lane lk's share of the score
     // product's contraction, column 4 lk + k4): one 32-byte load.
-    auto ld4 = [&](const double *base, int s) {
-        return s < K ? *reinterpret_cast<const f64x4 *>(base + (int64_t)s * 64 + 4 * lk) : f64x4{0.0, 0.0, 0.0, 0.0};
+    auto ld4 = [&](const double *p, int s) {
+        return s < K ? *reinterpret_cast<const f64x4 *>(p + (int64_t)s * 64 + 4 * lk) : f64x4{0.0, 0.0, 0.0, 0.0};
     };
-    // B operands: K^T tiles kf[kb][k4] = K[16 kb + lr][4 lk + k4]; the V tiles
-    // V[4 kk + lk][lr] are read where the P V product takes them
-    f64x4 kf[4];
+    double(*P)[64 + 1] = Ps[qb];
+    const f64x4 qf = ld4(qh, qb * 16 + lr);
+    f64x4 st[4], vf[4];  // scores; V[16 kb + 4 i + lk][lr]
 #pragma unroll
-    for (int kb = 0; kb < 4; kb++) kf[kb] = ld4(kh, kb * 16 + lr);
-    double(*P)[64 + 1] = Ps[w];
-#pragma unroll
-    for (int qb = 0; qb < 4; qb++) {
-        const f64x4 qf = ld4(qh, qb * 16 + lr);
-        f64x4 st[4];
-#pragma unroll
-        for (int kb = 0; kb < 4; kb++) {
-            st[kb] = f64x4{0.0, 0.0, 0.0, 0.0};
-            if (kb <= qb)
-#pragma unroll
-                for (int k4 = 0; k4 < 4; k4++)
-                    st[kb] = __builtin_amdgcn_mfma_f64_16x16x4f64(qf[k4], kf[kb][k4], st[kb], 0, 0, 0);
-        }
-        // key 16 kb + lr is visible to query 16 qb + lk + 4 i when kb < qb, or kb == qb and lr <= lk + 4 i
-        double mx[4], den[4], rden[4];
+    for (int kb = 0; kb < 4; kb++) {
+        st[kb] = f64x4{0.0, 0.0, 0.0, 0.0};
+        if (kb > qb) continue;
+        const f64x4 kf = ld4(kh, kb * 16 + lr);
 #pragma unroll
         for (int i = 0; i < 4; i++) {
-            mx[i] = -INFINITY;
-#pragma unroll
-            for (int kb = 0; kb <= qb; kb++)
-                if (kb < qb || lr <= lk + 4 * i) mx[i] = fmax(mx[i], st[kb][i]);
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) mx[i] = fmax(mx[i], __shfl_xor(mx[i], off, 16));
-            den[i] = 0.0;
-#pragma unroll
-            for (int kb = 0; kb < 4; kb++) {
-                const double p =
-                    (kb < qb || (kb == qb && lr <= lk + 4 * i)) ? exp((st[kb][i] - mx[i]) * scale) : 0.0;
-                st[kb][i] = p;
-                den[i] += p;
-            }
-#pragma unroll
-            for (int off = 8; off >= 1; off >>= 1) den[i] += __shfl_xor(den[i], off, 16);
-            rden[i] = 1.0 / den[i];
+            const int s = 16 * kb + 4 * i + lk;
+            vf[kb][i] = s < K ? vh[(int64_t)s * 64 + lr] : 0.0;
+            st[kb] = __builtin_amdgcn_mfma_f64_16x16x4f64(qf[i], kf[i], st[kb], 0, 0, 0);
         }
+    }
+    // key 16 kb + lr is visible to query 16 qb + lk + 4 i when kb < qb, or kb == qb and lr <= lk + 4 i
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        double mx = -INFINITY, den = 0.0;
 #pragma unroll
         for (int kb = 0; kb < 4; kb++)
+            if (kb < qb || (kb == qb && lr <= lk + 4 * i)) mx = fmax(mx, st[kb][i]);
 #pragma unroll
-            for (int i = 0; i < 4; i++) P[lk + 4 * i][kb * 16 + lr] = st[kb][i] * rden[i];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        f64x4 ot = {0.0, 0.0, 0.0, 0.0};
+        for (int off = 8; off >= 1; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 16));
 #pragma unroll
-        for (int kk = 0; kk < 4 * (qb + 1); kk++)
-            ot = __builtin_amdgcn_mfma_f64_16x16x4f64(P[lr][4 * kk + lk], ld(vh, 4 * kk + lk, lr), ot, 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int s = qb * 16 + lk + 4 * i;
-            if (s < K) o[(b * K + s) * 64 + hh * 16 + lr] = ot[i];
+        for (int kb = 0; kb < 4; kb++) {
+            if (kb > qb) continue;
+            const double p = kb < qb || lr <= lk + 4 * i ? exp2_f64(tab, (st[kb][i] - mx) * c2) : 0.0;
+            st[kb][i] = p;
+            den += p;
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) den += __shfl_xor(den, off, 16);
+        const double rden = 1.0 / den;
+#pragma unroll
+        for (int kb = 0; kb < 4; kb++)
+            if (kb <= qb) P[lk + 4 * i][kb * 16 + lr] = st[kb][i] * rden;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    f64x4 ot = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int kb = 0; kb < 4; kb++) {
+        if (kb > qb) continue;
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            ot = __builtin_amdgcn_mfma_f64_16x16x4f64(P[lr][16 * kb + 4 * i + lk], vf[kb][i], ot, 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const int s = qb * 16 + lk + 4 * i;
+        if (s < K) o[base + (int64_t)s * 64 + lr] = ot[i];
     }
 }
 
@@ -470,100 +420,155 @@ __global__ void __launch_bounds__(256) k64_finish(ModelView M, const double *__r
     }
 }
 
-// Causal attention of the mapped rows on FP64 MFMA (the tiling of
-// k64_attention): one wave per (connection, head); query blocks from the one
-// holding s0 on, queries below s0 read as zero and are not written; keys and
-// values below s0 come from the cache of the connection's sample (list[i] / C
-// in the chunk), the rest from this pass (row off[i] - off0 + s - s0).
+// Causal attention backward on FP64 MFMA, one block per (configuration, head);
+// q, k, v, o, dout (dO) and the outputs are [B*K][64] with head hh in columns
+// 16 hh .. 16 hh + 15.  Three passes over the 16 x 16 tiles at or below the
+// diagonal, wave w taking query block w in the first two and key block w in the
+// third (at most five tiles a wave of the last two): the softmax's
+// maximum and denominator and D = dO . O of every query; dQ^T += K^T dS^T per
+// query block; dV^T += dO^T P and dK^T += Q^T dS per key block, with
+//   P^T = exp(scale (K Q^T - max)) / den,  dS^T = P^T o (V dO^T - D)
+// formed again in each (28 matrix instructions a tile in all: against keeping
+// every dQ tile through one pass, that holds four waves per SIMD without
+// spills).  Transposed tiles hold a query per lane (lr) and keys lk + 4 i, the
+// operand of the dQ product as they are; the other two contract over queries
+// and take P and dS through LDS.  Rows at or beyond K read as zero and are
+// never written.  A wave per (configuration, head), all blocks one after another,
+// left half the CUs without work at 128 configurations of K = 60: 68 us a layer,
+// now 30.
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
-k64x_attention(const double *__restrict__ q, const double *__restrict__ k, const double *__restrict__ v,
-               const double *__restrict__ kvc, const int32_t *__restrict__ list, const int32_t *__restrict__ s0v,
-               const int32_t *__restrict__ off, int32_t off0, int64_t C, int64_t B, int K, int L, int l, double scale,
-               double *__restrict__ o) {
-    __shared__ double Ps[4][16][64 + 1];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int lr = lane & 15, lk = lane >> 4;
-    const int64_t g = (int64_t)blockIdx.x * 4 + w;
-    if (g >= B * 4) return;  // wave-uniform; the kernel has no block barrier
-    const int64_t i = g >> 2;
-    const int hh = (int)(g & 3);
-    const int s0 = s0v[i];
-    const int64_t smp = list[i] / C;
-    const int64_t per = (int64_t)K * 64;
-    const double *kc = kvc + ((smp * L + l) * 2) * per + hh * 16, *vc = kc + per;
-    const int64_t rb = (int64_t)(off[i] - off0) * 64 + hh * 16;  // row s0 of this connection, head hh
-    const double *qh = q + rb, *kh = k + rb, *vh = v + rb;
-    auto ldv = [&](int s, int c) { return s >= K ? 0.0 : s < s0 ? vc[(int64_t)s * 64 + c] : vh[(int64_t)(s - s0) * 64 + c]; };
-    // The score product's contraction index is the head column 4 lk + k4, so
-    // a lane's four operands of one key (or query) row are contiguous: one
-    // 32-byte load, and the four lanes of a row read its 128 bytes.  The
-    // values are read where the P V product takes them (16 lanes of a row,
-    // 128 bytes), not held: 114 registers, four waves per SIMD.
-    f64x4 kf[4];
+k64x_attention_back(const double *__restrict__ q, const double *__restrict__ k, const double *__restrict__ v,
+                    const double *__restrict__ o, const double *__restrict__ dout, int K, double scale,
+                    double *__restrict__ dq, double *__restrict__ dk, double *__restrict__ dv) {
+    __shared__ double Tl[4][2][16][18];  // P and dS of one tile, [query][key]
+    __shared__ double St[3][64];         // max, 1 / den, D of every query
+    const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = l & 15, lk = l >> 4;
+    const int64_t base = (int64_t)(blockIdx.x >> 2) * K * 64 + (blockIdx.x & 3) * 16;
+    // The lane's row is made anew in every pass of the loops below: loads that
+    // do not change with the pass would otherwise all be held in registers.
+    int lx = lr;
+    auto rowop = [&](const double *p, int blk) -> f64x4 {  // lane lr: row 16 blk + lr, columns 4 lk ..
+        const int s = 16 * blk + lx;
+        return s < K ? *reinterpret_cast<const f64x4 *>(p + base + (int64_t)s * 64 + 4 * lk) : f64x4{0.0, 0.0, 0.0, 0.0};
+    };
+    auto colop = [&](const double *p, int blk, int i) -> double {  // row 16 blk + 4 i + lk, column lr
+        const int s = 16 * blk + 4 * i + lk;
+        return s < K ? p[base + (int64_t)s * 64 + lx] : 0.0;
+    };
+    auto tile = [&](const f64x4 &a, const f64x4 &b) -> f64x4 {  // a's rows by b's rows, contracted over the 16 columns
+        f64x4 t = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int kb = 0; kb < 4; kb++) {
-        const int s = kb * 16 + lr;
-        kf[kb] = s >= K ? f64x4{0.0, 0.0, 0.0, 0.0}
-                        : *reinterpret_cast<const f64x4 *>((s < s0 ? kc + (int64_t)s * 64 : kh + (int64_t)(s - s0) * 64) +
-                                                           4 * lk);
-    }
-    double(*P)[64 + 1] = Ps[w];
-    const int qb0 = s0 >> 4;
+        for (int i = 0; i < 4; i++) t = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[i], t, 0, 0, 0);
+        return t;
+    };
+    auto xsum = [](double x) {
+        x += __shfl_xor(x, 16, 64);
+        return x + __shfl_xor(x, 32, 64);
+    };
+    auto sync = [] {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    const int nb = (K + 15) >> 4;
+    const double c2 = scale * 1.4426950408889634;  // the softmax in base 2
+    if (w < nb) {
+        const int j = w;
+        ConstF64 *tab = exp2_table();
+        const f64x4 qf = rowop(q, j), gf = rowop(dout, j), of = rowop(o, j);
+        double D = 0.0;
 #pragma unroll
-    for (int qb = 0; qb < 4; qb++) {
-        if (qb < qb0 || 16 * qb >= K) continue;  // wave-uniform
-        const int sq = qb * 16 + lr;
-        const f64x4 qf = (sq >= s0 && sq < K) ? *reinterpret_cast<const f64x4 *>(qh + (int64_t)(sq - s0) * 64 + 4 * lk)
-                                              : f64x4{0.0, 0.0, 0.0, 0.0};
-        f64x4 st[4];
+        for (int i = 0; i < 4; i++) D += gf[i] * of[i];
+        D = xsum(D);
+        // running maximum and denominator of the lane's keys, then of the four lanes
+        double mx = -INFINITY, den = 0.0;
+#pragma unroll 1
+        for (int kb = 0; kb <= j; kb++) {
+            asm volatile("" : "+v"(lx));
+            const f64x4 st = tile(rowop(k, kb), qf);
+            bool in[4];
+            double m = mx;
 #pragma unroll
-        for (int kb = 0; kb < 4; kb++) {
-            st[kb] = f64x4{0.0, 0.0, 0.0, 0.0};
-            if (kb <= qb)
-#pragma unroll
-                for (int k4 = 0; k4 < 4; k4++)
-                    st[kb] = __builtin_amdgcn_mfma_f64_16x16x4f64(qf[k4], kf[kb][k4], st[kb], 0, 0, 0);
-        }
-        double mx[4], den[4], rden[4];
-#pragma unroll
-        for (int ii = 0; ii < 4; ii++) {
-            mx[ii] = -INFINITY;
-#pragma unroll
-            for (int kb = 0; kb <= qb; kb++)
-                if (kb < qb || lr <= lk + 4 * ii) mx[ii] = fmax(mx[ii], st[kb][ii]);
-#pragma unroll
-            for (int off2 = 8; off2 >= 1; off2 >>= 1) mx[ii] = fmax(mx[ii], __shfl_xor(mx[ii], off2, 16));
-            den[ii] = 0.0;
-#pragma unroll
-            for (int kb = 0; kb < 4; kb++) {
-                const double p =
-                    (kb < qb || (kb == qb && lr <= lk + 4 * ii)) ? exp((st[kb][ii] - mx[ii]) * scale) : 0.0;
-                st[kb][ii] = p;
-                den[ii] += p;
+            for (int i = 0; i < 4; i++) {
+                in[i] = kb < j || lk + 4 * i <= lr;
+                m = in[i] ? fmax(m, st[i]) : m;
             }
+            den *= m > mx ? exp2_f64(tab, (mx - m) * c2) : 1.0;
+            mx = m;
 #pragma unroll
-            for (int off2 = 8; off2 >= 1; off2 >>= 1) den[ii] += __shfl_xor(den[ii], off2, 16);
-            rden[ii] = 1.0 / den[ii];
+            for (int i = 0; i < 4; i++) den += in[i] ? exp2_f64(tab, (st[i] - m) * c2) : 0.0;
         }
-#pragma unroll
-        for (int kb = 0; kb < 4; kb++)
-#pragma unroll
-            for (int ii = 0; ii < 4; ii++) P[lk + 4 * ii][kb * 16 + lr] = st[kb][ii] * rden[ii];
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        f64x4 ot = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int kk = 0; kk < 4 * (qb + 1); kk++)
-            ot = __builtin_amdgcn_mfma_f64_16x16x4f64(P[lr][4 * kk + lk], ldv(4 * kk + lk, lr), ot, 0, 0, 0);
-#pragma unroll
-        for (int ii = 0; ii < 4; ii++) {
-            const int s = qb * 16 + lk + 4 * ii;
-            if (s >= s0 && s < K) o[rb + (int64_t)(s - s0) * 64 + lr] = ot[ii];
+        double ml = fmax(mx, __shfl_xor(mx, 16, 64));
+        ml = fmax(ml, __shfl_xor(ml, 32, 64));
+        den = xsum(den > 0.0 ? den * exp2_f64(tab, (mx - ml) * c2) : den);
+        mx = ml;
+        if (lk == 0) {
+            St[0][16 * j + lr] = mx;
+            St[1][16 * j + lr] = 1.0 / den;
+            St[2][16 * j + lr] = D;
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    __syncthreads();  // every query's statistics; no block barrier follows
+    if (w >= nb) return;
+    // P^T and dS^T of one tile
+    auto grads = [&](ConstF64 *tab, int j, int kb, f64x4 &p, f64x4 &ds) {
+        p = tile(rowop(k, kb), rowop(q, j));
+        const f64x4 dp = tile(rowop(v, kb), rowop(dout, j));
+        const double mx = St[0][16 * j + lr], rden = St[1][16 * j + lr], D = St[2][16 * j + lr];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            p[i] = kb == j && lk + 4 * i > lr ? 0.0 : exp2_f64(tab, (p[i] - mx) * c2) * rden;
+            ds[i] = p[i] * (dp[i] - D);
+        }
+    };
+    {
+        const int j = w;
+        ConstF64 *tab = exp2_table();
+        f64x4 dqt = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+        for (int kb = 0; kb <= j; kb++) {
+            asm volatile("" : "+v"(lx));
+            f64x4 p, ds;
+            grads(tab, j, kb, p, ds);
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                dqt = __builtin_amdgcn_mfma_f64_16x16x4f64(colop(k, kb, i), ds[i], dqt, 0, 0, 0);
+        }
+        const int s = 16 * j + lr;
+        if (s < K)
+#pragma unroll
+            for (int i = 0; i < 4; i++) dq[base + (int64_t)s * 64 + lk + 4 * i] = scale * dqt[i];
+    }
+    {
+        const int kb = w;
+        ConstF64 *tab = exp2_table();
+        f64x4 dkt = {0.0, 0.0, 0.0, 0.0}, dvt = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 1
+        for (int j = kb; j < nb; j++) {
+            asm volatile("" : "+v"(lx));
+            f64x4 p, ds;
+            grads(tab, j, kb, p, ds);
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                Tl[w][0][lr][lk + 4 * i] = p[i];
+                Tl[w][1][lr][lk + 4 * i] = ds[i];
+            }
+            sync();
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                dvt = __builtin_amdgcn_mfma_f64_16x16x4f64(colop(dout, j, i), Tl[w][0][4 * i + lk][lr], dvt, 0, 0, 0);
+                dkt = __builtin_amdgcn_mfma_f64_16x16x4f64(colop(q, j, i), Tl[w][1][4 * i + lk][lr], dkt, 0, 0, 0);
+            }
+            sync();  // the tile is rewritten
+        }
+        const int s = 16 * kb + lr;
+        if (s < K)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                dk[base + (int64_t)s * 64 + lk + 4 * i] = scale * dkt[i];
+                dv[base + (int64_t)s * 64 + lk + 4 * i] = dvt[i];
+            }
     }
 }
 
@@ -602,8 +607,7 @@ static nnqs_status enqueue_phase_f64(nnqs_model *m, const uint64_t *keys, const 
         const uint64_t *kb = list ? keys : keys + 2 * b0;
         const int32_t *lb = list ? list + b0 : nullptr;
         hipLaunchKernelGGL(k64_phase1, dim3(blocks_for(B * P)), dim3(256), 0, st, M, kb, lb, B, z1);
-        hipLaunchKernelGGL(k64_gemm<2>, dim3((unsigned)((P + 63) / 64), (unsigned)((B + 63) / 64)), dim3(256), 0, st,
-                           z1, P, W + M.off.ph_w2, P, W + M.off.ph_b2, B, P, P, z2, P);
+        gemm64<2, false>(z1, P, W + M.off.ph_w2, P, W + M.off.ph_b2, B, P, P, z2, P, GemmEpi{}, st);
         hipLaunchKernelGGL(k64_phase_out, dim3(blocks_for(B, 4)), dim3(256), 0, st, M, z2, lb, B,
                            list ? phase : phase + b0);
     }
@@ -632,16 +636,16 @@ nnqs_status enqueue_f64_list(const nnqs_model *cm, const uint64_t *xkeys, int64_
     return enqueue_phase_f64(m, xkeys, list, n, xph, st);
 }
 
-// Instances launched from other files (the FP64 backward).
-template __global__ void k64_gemm_res<64>(const double *, int, const double *, const double *, int64_t, double *,
-                                          double *);
-template __global__ void k64_gemm<0, false>(const double *, int, const double *, int, const double *, int64_t, int,
-                                            int, double *, int);
-template __global__ void k64_gemm<1, false>(const double *, int, const double *, int, const double *, int64_t, int,
-                                            int, double *, int);
-template __global__ void k64_gemm<0, true>(const double *, int, const double *, int, const double *, int64_t, int,
-                                           int, double *, int);
-template __global__ void k64_gemm<1, true>(const double *, int, const double *, int, const double *, int64_t, int,
-                                           int, double *, int);
+// Instances used by the gradient (grad_f64.hip).
+template void gemm64<0, false>(const double *, int, const double *, int, const double *, int64_t, int, int, double *, int,
+                               const GemmEpi &, hipStream_t);
+template void gemm64<0, true>(const double *, int, const double *, int, const double *, int64_t, int, int, double *, int,
+                              const GemmEpi &, hipStream_t);
+template void gemm64<3, false>(const double *, int, const double *, int, const double *, int64_t, int, int, double *, int,
+                               const GemmEpi &, hipStream_t);
+template void gemm64<4, true>(const double *, int, const double *, int, const double *, int64_t, int, int, double *, int,
+                              const GemmEpi &, hipStream_t);
+template void gemm64<5, false>(const double *, int, const double *, int, const double *, int64_t, int, int, double *, int,
+                               const GemmEpi &, hipStream_t);
 
 }  // namespace nnqs

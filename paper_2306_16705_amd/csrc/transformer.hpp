@@ -21,7 +21,7 @@ constexpr int kPhaseBits = 128;
 // Device layout of the BF16 weights (element offsets into d_bf16).
 struct Bf16Layout {
     // per layer: wqkvT[192][64] woT[64][64] w1T[256][64] w2T[64][256], each as
-    // 16-row x 32-column operand fragments (see put_frag)
+    // 16-row x 32-column operand fragments (see frag_at)
     int64_t layer0, layer_stride;
     int64_t ph_w1T, ph_w2T, total;  // ph_w1T[512][128] (rows: hidden unit, cols: bit), ph_w2T[512][512]
 };
