@@ -91,184 +91,460 @@ __device__ __forceinline__ ScreenInput load_input(const uint64_t *keys, const ui
     return in;
 }
 
-// a1[k][c] = b1[c] + sum over active inputs p of W1[p][c]  (one thread per (k, c))
-template <typename T>
-__global__ void k_screen_layer1(int N, int H, const double *__restrict__ w, const uint64_t *__restrict__ keys,
-                                const uint8_t *__restrict__ exc, int64_t n, T *__restrict__ a1) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n * H) return;
-    const int64_t k = e / H;
-    const int c = (int)(e - k * H);
-    const ScreenOff o = screen_off(N, H);
-    const ScreenInput in = load_input(keys, exc, k);
-    T acc = (T)w[o.b1 + c];
-    for (int wd = 0; wd < 2; wd++) {
-        uint64_t m = wd ? in.x.hi : in.x.lo;
-        while (m) {
-            const int b = __ffsll((unsigned long long)m) - 1;
-            m &= m - 1;
-            const int p = wd * 64 + b;
-            if (p < N) acc += (T)w[o.W1 + (int64_t)p * H + c];
-        }
+// ------------------------------------------------- forward and gradient
+// The training path: dense products on the 16x16x4 matrix instruction of the
+// precision (FP64, or FP32, whose result is the chain of fused multiply-adds
+// in ascending k, checked against fmaf over normal and denormal values).  A
+// minibatch step is six launches: the FP32 weights, layer 1 from the sparse
+// input, the hidden product, the output with its gradient, the hidden
+// product's transpose, and every weight and bias gradient together.  With
+// one output element per thread, a launch per elementwise pass and four-block
+// column sums a step of 4,096 pairs at N = 120, hidden 256 took 950 us; now
+// 164 us, the choice of the minibatch included.
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+template <typename T> struct Mma;
+template <> struct Mma<float> {
+    typedef f32x4 Acc;
+    static __device__ __forceinline__ Acc mul(float a, float b, Acc c) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
     }
-    for (int t = 0; t < 4; t++)  // 255 (absent) and any other code >= N add nothing
-        if (in.e[t] < N) acc += (T)w[o.W1 + (int64_t)((t + 1) * N + in.e[t]) * H + c];
-    a1[e] = acc;
-}
-
-// C[M][Nc] = op(A) op(B) (+ optional row bias, GELU on input, etc. done
-// separately).  Plain 16x16 LDS-tiled product for the training path.
-template <typename T>
-__global__ void __launch_bounds__(256) k_gemm(const T *__restrict__ A, int lda, bool ta, const T *__restrict__ B,
-                                              int ldb, bool tb, T *__restrict__ C, int ldc, int64_t M, int Nc,
-                                              int64_t Kd) {
-    __shared__ T As[16][17], Bs[16][17];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int64_t row = (int64_t)blockIdx.y * 16 + ty;
-    const int col = blockIdx.x * 16 + tx;
-    T acc = 0;
-    for (int64_t k0 = 0; k0 < Kd; k0 += 16) {
-        const int64_t ka = k0 + tx, kb = k0 + ty;
-        const int64_t ar = (int64_t)blockIdx.y * 16 + ty;
-        As[ty][tx] = (ar < M && ka < Kd) ? (ta ? A[ka * lda + ar] : A[ar * lda + ka]) : T(0);
-        Bs[ty][tx] = (kb < Kd && col < Nc) ? (tb ? B[(int64_t)col * ldb + kb] : B[kb * ldb + col]) : T(0);
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; kk++) acc += As[ty][kk] * Bs[kk][tx];
-        __syncthreads();
+    static __device__ __forceinline__ int row(int lk, int i) { return 4 * lk + i; }  // row of accumulator i
+};
+template <> struct Mma<double> {
+    typedef f64x4 Acc;
+    static __device__ __forceinline__ Acc mul(double a, double b, Acc c) {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
     }
-    if (row < M && col < Nc) C[row * ldc + col] = acc;
-}
+    static __device__ __forceinline__ int row(int lk, int i) { return lk + 4 * i; }
+};
 
-template <typename T> __global__ void k_gelu_copy(const T *__restrict__ a, T *__restrict__ z, int64_t cnt) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < cnt) z[e] = gelu_t<T>(a[e]);
-}
-
-template <typename T>
-__global__ void k_add_bias(T *__restrict__ a, const double *__restrict__ b, int64_t n, int H) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < n * H) a[e] += (T)b[e % H];
-}
-
-// y[k] = b3 + sum_c GELU(a2[k][c]) w3[c]
-template <typename T>
-__global__ void k_screen_out(const T *__restrict__ a2, const double *__restrict__ w, int N, int H, int64_t n,
-                             T *__restrict__ y) {
+__global__ void k_convert_f32(const double *__restrict__ s, float *__restrict__ d, int64_t n) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < n) d[k] = (float)s[k];
+}
+
+// a1[k][c] = b1[c] + sum over active inputs p of W1[p][c] in ascending p, and
+// z1 = GELU(a1).  One wave per example (its inputs are then the same for all
+// lanes, and the rows of eight of them load together), 256 columns per pass;
+// 44 rows of 1 KB from L2 bound it.  30 us with a thread per element and one
+// dependent load at a time, now 13 us (4,096 examples, N = 120).
+template <typename T>
+__global__ void __launch_bounds__(256) k_screen_layer1(int N, int H, const T *__restrict__ w,
+                                                       const uint64_t *__restrict__ keys,
+                                                       const uint8_t *__restrict__ exc, int64_t n,
+                                                       T *__restrict__ a1, T *__restrict__ z1) {
+    const int lane = threadIdx.x & 63;
+    const int64_t k = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (k >= n) return;
     const ScreenOff o = screen_off(N, H);
-    T acc = (T)w[o.b3];
-    for (int c = 0; c < H; c++) acc += gelu_t<T>(a2[k * H + c]) * (T)w[o.w3 + c];
-    y[k] = acc;
+    const ScreenInput in = load_input(keys, exc, k);
+    const uint64_t lo_in = N >= 64 ? in.x.lo : in.x.lo & ((1ull << N) - 1);
+    const uint64_t hi_in = N >= 128 ? in.x.hi : N > 64 ? in.x.hi & ((1ull << (N - 64)) - 1) : 0ull;
+    for (int c0 = 0; c0 < H; c0 += 256) {
+        int c[4];
+        T acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            c[j] = std::min(c0 + lane + 64 * j, H - 1);
+            acc[j] = w[o.b1 + c[j]];
+        }
+        uint64_t lo = lo_in, hi = hi_in;
+        while (lo | hi) {
+            int p[8];
+            T v[8][4];
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                p[u] = -1;
+                if (lo) {
+                    p[u] = __ffsll((unsigned long long)lo) - 1;
+                    lo &= lo - 1;
+                } else if (hi) {
+                    p[u] = 63 + __ffsll((unsigned long long)hi);
+                    hi &= hi - 1;
+                }
+#pragma unroll
+                for (int j = 0; j < 4; j++) v[u][j] = w[o.W1 + (int64_t)std::max(p[u], 0) * H + c[j]];
+            }
+            __builtin_amdgcn_sched_barrier(0);  // all loads before the first sum
+#pragma unroll
+            for (int u = 0; u < 8; u++)
+#pragma unroll
+                for (int j = 0; j < 4; j++) acc[j] = p[u] >= 0 ? acc[j] + v[u][j] : acc[j];
+        }
+#pragma unroll
+        for (int t = 0; t < 4; t++)  // 255 (absent) and any other code >= N add nothing
+            if (in.e[t] < N)
+#pragma unroll
+                for (int j = 0; j < 4; j++) acc[j] += w[o.W1 + (int64_t)((t + 1) * N + in.e[t]) * H + c[j]];
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+            if (c0 + lane + 64 * j < H) {
+                if (a1) a1[k * H + c[j]] = acc[j];
+                z1[k * H + c[j]] = gelu_t<T>(acc[j]);
+            }
+    }
+}
+
+// The hidden layer's product and its transpose, 32 x 64 per block, each wave
+// 16 x 32: with W, a2 = A W2 + b2 (kept if asked for) and out = GELU(a2); with
+// kBack, out = (A W2^T) GELU'(act).  Depth in slices of 64 through LDS, the
+// next slice's loads in flight (rows padded to 68 and 81: the fragments, and
+// the transposed store, then touch every bank once).  4,096 x 256 x 256 in
+// FP32: 85 us with one element per thread, now 15 us (512 blocks, four slices
+// of one memory latency each; the matrix instructions take 3.4 us of it).
+// The blocks past the row tiles of kBack's launch form the partial sums of the
+// output weights' gradient, w3p[ph][c] = sum of gy[k] z2[k][c] over k = ph, ph +
+// 16, ...: 64 columns of one phase each, one wave (a CU takes in few lines at a
+// time, so the sums want many CUs more than full ones).
+template <typename T, bool kBack>
+__global__ void __launch_bounds__(256) k_screen_hidden(const T *__restrict__ A, const T *__restrict__ W,
+                                                       const T *__restrict__ bias, const T *__restrict__ act, int64_t n,
+                                                       int H, T *__restrict__ a2, T *__restrict__ out,
+                                                       const T *__restrict__ z2, const T *__restrict__ gy,
+                                                       double *__restrict__ w3p) {
+    __shared__ T As[32][68];
+    __shared__ T Ws[64][81];
+    const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lr = l & 15, lk = l >> 4, rw = 16 * (w & 1), cw = 32 * (w >> 1);
+    const int64_t r0 = (int64_t)blockIdx.x * 32;
+    const int c0 = blockIdx.y * 64;
+    if (kBack && r0 >= n) {
+        const int ph = (int)((int64_t)blockIdx.x - (n + 31) / 32), c = std::min(c0 + l, H - 1);
+        if (w > 0) return;
+        double s = 0.0;
+        constexpr int kU = 32;  // loads in flight
+        for (int64_t k0 = ph; k0 < n; k0 += 16 * kU) {
+            T v[kU], g[kU];
+#pragma unroll
+            for (int u = 0; u < kU; u++) {
+                const int64_t k = std::min(k0 + 16 * u, n - 1);
+                v[u] = z2[k * H + c];
+                g[u] = gy[k];
+            }
+            __builtin_amdgcn_sched_barrier(0);  // the compiler would wait for each load before the next
+#pragma unroll
+            for (int u = 0; u < kU; u++)
+                if (k0 + 16 * u < n) s += (double)(v[u] * g[u]);
+        }
+        if (c0 + l < H) w3p[ph * H + c0 + l] = s;
+        return;
+    }
+    T pa[8], pw[16];
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            const int64_t r = r0 + w + 4 * e;
+            pa[e] = r < n && k0 + l < H ? A[r * H + k0 + l] : T(0);
+        }
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            const int c = c0 + (kBack ? w + 4 * e : l), k = k0 + (kBack ? l : w + 4 * e);
+            pw[e] = c < H && k < H ? W[kBack ? (int64_t)c * H + k : (int64_t)k * H + c] : T(0);
+        }
+    };
+    typename Mma<T>::Acc acc[2] = {};
+    load(0);
+    for (int k0 = 0; k0 < H; k0 += 64) {
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 8; e++) As[w + 4 * e][l] = pa[e];
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+            if (kBack) Ws[l][w + 4 * e] = pw[e];
+            else Ws[w + 4 * e][l] = pw[e];
+        }
+        __syncthreads();
+        if (k0 + 64 < H) load(k0 + 64);
+        T a[16], b[16][2];
+#pragma unroll
+        for (int q = 0; q < 16; q++) {
+            a[q] = As[rw + lr][4 * q + lk];
+            b[q][0] = Ws[4 * q + lk][cw + lr];
+            b[q][1] = Ws[4 * q + lk][cw + 16 + lr];
+        }
+        __builtin_amdgcn_sched_barrier(0);  // one LDS latency, not sixteen
+#pragma unroll
+        for (int q = 0; q < 16; q++)
+#pragma unroll
+            for (int cb = 0; cb < 2; cb++) acc[cb] = Mma<T>::mul(a[q], b[q][cb], acc[cb]);
+    }
+#pragma unroll
+    for (int cb = 0; cb < 2; cb++) {
+        const int c = c0 + cw + cb * 16 + lr;
+        if (c >= H) continue;
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int64_t r = r0 + rw + Mma<T>::row(lk, i);
+            if (r >= n) continue;
+            if (kBack) {
+                out[r * H + c] = acc[cb][i] * gelu_grad_t<T>(act[r * H + c]);
+            } else {
+                const T v = acc[cb][i] + bias[c];
+                if (a2) a2[r * H + c] = v;
+                out[r * H + c] = gelu_t<T>(v);
+            }
+        }
+    }
+}
+
+// y[k] = b3 + sum_c z2[k][c] w3[c] in ascending c; with `target`, gy[k] = 2
+// (y_k - target_k) / n and d2[k][c] = gy[k] w3[c] GELU'(a2[k][c]).  Sixteen
+// examples per block: their rows go through LDS, where 16 lanes follow one
+// chain each (the chain bounds it: 57 us when every lane also made its 256
+// GELUs in the chain, now 9 us).
+template <typename T>
+__global__ void __launch_bounds__(256) k_screen_out(const T *__restrict__ a2, const T *__restrict__ z2,
+                                                    const T *__restrict__ w, int N, int H, int64_t n,
+                                                    const double *__restrict__ target, T *__restrict__ y,
+                                                    double *__restrict__ pred, T *__restrict__ gy,
+                                                    T *__restrict__ d2) {
+    __shared__ T zs[16][257];
+    __shared__ T ws[256];
+    __shared__ T gs[16];
+    const ScreenOff o = screen_off(N, H);
+    const int64_t k0 = (int64_t)blockIdx.x * 16;
+    const int t = threadIdx.x;
+    const int rows = (int)std::min<int64_t>(16, n - k0);
+    T av[16];  // a2 of column c
+    auto load_a2 = [&](int c) {
+#pragma unroll
+        for (int r = 0; r < 16; r++) av[r] = c < H ? a2[(k0 + std::min(r, rows - 1)) * H + c] : T(0);
+    };
+    if (target) load_a2(t);  // in flight while the chain runs
+    T acc = w[o.b3];
+    for (int c0 = 0; c0 < H; c0 += 256) {
+        const int c = c0 + t, cnt = std::min(256, H - c0);
+        __syncthreads();
+        T zv[16];
+#pragma unroll
+        for (int r = 0; r < 16; r++) zv[r] = c < H ? z2[(k0 + std::min(r, rows - 1)) * H + c] : T(0);
+        ws[t] = c < H ? w[o.w3 + c] : T(0);
+        __builtin_amdgcn_sched_barrier(0);  // all loads before the first store
+#pragma unroll
+        for (int r = 0; r < 16; r++) zs[r][t] = zv[r];
+        __syncthreads();
+        if (t < 16) {
+#pragma unroll 16
+            for (int q = 0; q < cnt; q++) acc += zs[t][q] * ws[q];
+        }
+    }
+    if (t < 16 && k0 + t < n) {
+        y[k0 + t] = acc;
+        if (pred) pred[k0 + t] = (double)acc;
+        if (target) {
+            const T g = (T)(2.0 * ((double)acc - target[k0 + t]) / (double)n);
+            gy[k0 + t] = g;
+            gs[t] = g;
+        }
+    }
+    if (!target) return;
+    __syncthreads();
+    for (int c = t; c < H; c += 256) {
+        if (c != t) load_a2(c);
+        const T w3 = w[o.w3 + c];
+#pragma unroll
+        for (int r = 0; r < 16; r++)
+            if (r < rows) d2[(k0 + r) * H + c] = gs[r] * w3 * gelu_grad_t<T>(av[r]);
+    }
+}
+
+// One 32 x 32 tile of gW1 = X^T d1 (kFirst) or gW2 = z1^T d2, 16 x 16 a wave:
+// a chain of matrix instructions over the n examples (ascending, as a plain sum
+// would).  Slices of 64 examples go through LDS, the loads of three in flight.
+// X is the input as a dense 0/1 matrix (bits of x', then the one-hot fields of
+// i, j, a, b), formed from one byte of the example per element.  The tiles of
+// the first row also add up D's columns, for the biases: 16 row phases per
+// column, combined in phase order.
+constexpr int kSlice = 64, kAhead = 3;
+template <typename T> struct TileLds {  // rows padded to 48: the fragments touch every bank once
+    T A[2][kSlice][48], D[2][kSlice][48];
+};
+
+template <typename T, bool kFirst>
+__device__ __forceinline__ void screen_tile(TileLds<T> &lds, int N, int H, const uint64_t *__restrict__ keys,
+                                            const uint8_t *__restrict__ exc, int64_t n, const T *__restrict__ z1,
+                                            const T *__restrict__ D, int i0, int j0, double *__restrict__ out,
+                                            double *__restrict__ colsum) {
+    auto &As = lds.A, &Ds = lds.D;
+    typedef typename std::conditional<kFirst, uint8_t, T>::type S;
+    const int t = threadIdx.x, l = t & 63, w = t >> 6, lr = l & 15, lk = l >> 4;
+    const int M = kFirst ? 5 * N : H;
+    // element (k, column t & 31) of a slice: k = (t >> 5) + 8 e; columns beyond the matrix repeat its last
+    const int rk = t >> 5, p = std::min(i0 + (t & 31), M - 1);
+    const int dc = std::min(t & 31, H - 1 - j0), field = p / N, bit = p - field * N;
+    const S *A;
+    int as;  // elements per example
+    if constexpr (kFirst) {
+        A = field == 0 ? reinterpret_cast<const uint8_t *>(keys) + (bit >> 3) : exc + field - 1;
+        as = field == 0 ? 16 : 4;
+    } else {
+        A = z1 + p;
+        as = H;
+    }
+    D += j0;
+    // A slice's loads share a row pointer and fixed lane offsets.  The last
+    // slice's offsets hold to the last example and the slices past it repeat
+    // it; rows beyond n become zero on the way to LDS.
+    uint32_t ao[8], od[8];
+    auto offsets = [&](int last) {
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            const int k = std::min(rk + 8 * e, last);
+            ao[e] = (uint32_t)(k * as);
+            od[e] = (uint32_t)(k * H + dc);
+        }
+    };
+    offsets(kSlice);
+    const int64_t slices = (n + kSlice - 1) / kSlice, klast = (slices - 1) * kSlice;
+    S pa[kAhead][8];
+    T pd[kAhead][8];
+    auto load = [&](int q, int64_t k0) {
+        if (k0 == klast) offsets((int)(n - 1 - klast));
+        const int64_t kb = std::min(k0, klast);
+        const S *Ak = A + kb * as;
+        const T *Dk = D + kb * H;
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            pa[q][e] = Ak[ao[e]];
+            pd[q][e] = Dk[od[e]];
+        }
+    };
+    double cs[2] = {0.0, 0.0};  // row phases rk and rk + 8
+    auto store = [&](int q, int slot, int64_t k0) {
+        const int rem = (int)std::min<int64_t>(n - k0, kSlice) - rk;
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            T av;
+            if constexpr (kFirst)
+                av = (field == 0 ? (pa[q][e] >> (bit & 7)) & 1 : pa[q][e] == bit) ? T(1) : T(0);
+            else
+                av = pa[q][e];
+            const T dv = 8 * e < rem ? pd[q][e] : T(0);
+            As[slot][rk + 8 * e][t & 31] = 8 * e < rem ? av : T(0);
+            Ds[slot][rk + 8 * e][t & 31] = dv;
+            cs[e & 1] += (double)dv;
+        }
+    };
+    typename Mma<T>::Acc acc = {};
+    const int rw = 16 * (w & 1), cw = 16 * (w >> 1);
+#pragma unroll
+    for (int q = 0; q < kAhead; q++) load(q, q * kSlice);
+    store(0, 0, 0);
+    for (int64_t s0 = 0; s0 < slices; s0 += 2 * kAhead)
+#pragma unroll
+        for (int u = 0; u < 2 * kAhead; u++) {  // slice s0 + u (zeros past the last) is in slot u & 1, the next
+                                                // in registers (u + 1) % kAhead
+            __syncthreads();  // the slice is written, the other slot read
+            T a[kSlice / 4], d[kSlice / 4];
+#pragma unroll
+            for (int q = 0; q < kSlice / 4; q++) {
+                a[q] = As[u & 1][4 * q + lk][rw + lr];
+                d[q] = Ds[u & 1][4 * q + lk][cw + lr];
+            }
+            load(u % kAhead, (s0 + u + kAhead) * kSlice);
+            __builtin_amdgcn_sched_barrier(0);  // reads and loads stay ahead of the products
+            store((u + 1) % kAhead, (u + 1) & 1, (s0 + u + 1) * kSlice);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < kSlice / 4; q++) acc = Mma<T>::mul(a[q], d[q], acc);
+        }
+    const int j = j0 + cw + lr;
+    if (j < H)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int r = i0 + rw + Mma<T>::row(lk, i);
+            if (r < M) out[(int64_t)r * H + j] = (double)acc[i];
+        }
+    if (i0 == 0) {
+        double(*part)[32] = reinterpret_cast<double(*)[32]>(As);  // 16 phases
+        __syncthreads();
+        part[rk][t & 31] = cs[0];
+        part[rk + 8][t & 31] = cs[1];
+        __syncthreads();
+        if (t < 32 && j0 + t < H) {
+            double s = 0.0;
+            for (int q = 0; q < 16; q++) s += part[q][t];
+            colsum[j0 + t] = s;
+        }
+    }
+}
+
+// Every gradient of the weights and biases in one launch, so that its few
+// tiles per matrix fill the chip together.  Blocks in order: b3 (the sum of
+// gy) and w3 (its partial sums in phase order); the loss; the tiles of gW1 and
+// gW2 with b1 and b2.  n / 4 matrix instructions of 32 cycles in a row bound
+// it, 14 us for 4,096 examples.  The two products took 300 us, the sums 250 us,
+// now 59 us together (with X in memory and the column sums in blocks of
+// their own 96 us: a CU waits for about 21 ns per line there).
+template <typename T>
+__global__ void __launch_bounds__(256) k_screen_grads(int N, int H, const uint64_t *__restrict__ keys,
+                                                      const uint8_t *__restrict__ exc,
+                                                      const double *__restrict__ target, int64_t n,
+                                                      const T *__restrict__ z1, const T *__restrict__ d1,
+                                                      const T *__restrict__ d2, const T *__restrict__ y,
+                                                      const T *__restrict__ gy, const double *__restrict__ w3p,
+                                                      double *__restrict__ grad, double *__restrict__ loss) {
+    __shared__ TileLds<T> lds;
+    double *part = reinterpret_cast<double *>(&lds);
+    const ScreenOff o = screen_off(N, H);
+    const int t = threadIdx.x;
+    int b = (int)blockIdx.x;
+    if (b == 0) {  // strided partials, then a fixed-order tree
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int64_t k = t; k < n; k += 4096) {
+            T v[16];
+#pragma unroll
+            for (int q = 0; q < 16; q++) v[q] = gy[std::min(k + 256 * q, n - 1)];
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 16; q++)
+                if (k + 256 * q < n) s[q & 3] += (double)v[q];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; q++) part[t + 256 * q] = s[q];
+        __syncthreads();
+        for (int w = 512; w >= 1; w >>= 1) {
+            for (int q = t; q < w; q += 256) part[q] += part[q + w];
+            __syncthreads();
+        }
+        if (t == 0) grad[o.b3] = part[0];
+        for (int c = t; c < H; c += 256) {
+            double v = 0.0;
+#pragma unroll
+            for (int ph = 0; ph < 16; ph++) v += w3p[ph * H + c];
+            grad[o.w3 + c] = v;
+        }
+        return;
+    }
+    if (b == 1) {
+        if (!loss) return;
+        double s = 0.0;
+#pragma unroll 8
+        for (int64_t k = t; k < n; k += 256) {
+            const double r = (double)y[k] - target[k];
+            s += r * r;
+        }
+        part[t] = s;
+        __syncthreads();
+        for (int w = 128; w >= 1; w >>= 1) {
+            if (t < w) part[t] += part[t + w];
+            __syncthreads();
+        }
+        if (t == 0) *loss = part[0] / (double)n;
+        return;
+    }
+    b -= 2;
+    const int jt = (H + 31) / 32, tiles1 = (5 * N + 31) / 32 * jt;
+    if (b < tiles1)
+        screen_tile<T, true>(lds, N, H, keys, exc, n, z1, d1, b / jt * 32, b % jt * 32, grad + o.W1, grad + o.b1);
+    else
+        screen_tile<T, false>(lds, N, H, keys, exc, n, z1, d2, (b - tiles1) / jt * 32, (b - tiles1) % jt * 32, grad + o.W2,
+                              grad + o.b2);
 }
 
 template <typename T>
 __global__ void k_to_double(const T *__restrict__ s, double *__restrict__ d, int64_t n) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n) d[k] = (double)s[k];
-}
-
-// gy[k] = 2 (y_k - t_k) / n ; loss partial per block written to lossp
-template <typename T>
-__global__ void k_mse_grad(const T *__restrict__ y, const double *__restrict__ target, int64_t n,
-                           T *__restrict__ gy) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    gy[k] = (T)(2.0 * ((double)y[k] - target[k]) / (double)n);
-}
-
-__global__ void k_mse_loss(const double *__restrict__ target, const void *__restrict__ yv, bool is_double,
-                           int64_t n, double *__restrict__ loss) {
-    __shared__ double sh[256];
-    double s = 0.0;
-    for (int64_t k = threadIdx.x; k < n; k += blockDim.x) {
-        const double y = is_double ? static_cast<const double *>(yv)[k] : (double)static_cast<const float *>(yv)[k];
-        const double r = y - target[k];
-        s += r * r;
-    }
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *loss = sh[0] / (double)n;
-}
-
-// d2[k][c] = gy[k] w3[c] GELU'(a2[k][c]); also z2 = GELU(a2) for gw3
-template <typename T>
-__global__ void k_back_out(const T *__restrict__ a2, const T *__restrict__ gy, const double *__restrict__ w, int N,
-                           int H, int64_t n, T *__restrict__ d2, T *__restrict__ z2) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n * H) return;
-    const int c = (int)(e % H);
-    const ScreenOff o = screen_off(N, H);
-    const T a = a2[e];
-    d2[e] = gy[e / H] * (T)w[o.w3 + c] * gelu_grad_t<T>(a);
-    z2[e] = gelu_t<T>(a);
-}
-
-// column sums (fixed order): out[c] = sum_k M[k][c] (* vec[k] if vec)
-template <typename T>
-__global__ void __launch_bounds__(1024) k_colsum(const T *__restrict__ Mx, const T *__restrict__ vec, int64_t n,
-                                                 int H, double *__restrict__ out) {
-    // out[c] = sum_k Mx[k][c] (* vec[k]): block of 64 columns, 16 row phases
-    // per column, partials combined in a fixed order (deterministic)
-    __shared__ double part[16][64];
-    const int cl = threadIdx.x & 63, ph = threadIdx.x >> 6;
-    const int c = blockIdx.x * 64 + cl;
-    double s = 0.0;
-    if (c < H)
-        for (int64_t k = ph; k < n; k += 16) s += (double)(vec ? Mx[k * H + c] * vec[k] : Mx[k * H + c]);
-    part[ph][cl] = s;
-    __syncthreads();
-    if (ph == 0 && c < H) {
-        double t = 0.0;
-        for (int q = 0; q < 16; q++) t += part[q][cl];
-        out[c] = t;
-    }
-}
-
-template <typename T> __global__ void __launch_bounds__(1024) k_sum(const T *__restrict__ v, int64_t n,
-                                                                    double *__restrict__ out) {
-    // one block; strided partials, then a fixed-order tree
-    __shared__ double part[1024];
-    double s = 0.0;
-    for (int64_t k = threadIdx.x; k < n; k += 1024) s += (double)v[k];
-    part[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 512; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *out = part[0];
-}
-
-// d1 = dz1 * GELU'(a1) in place in dz1
-template <typename T> __global__ void k_mul_gelu_grad(T *__restrict__ dz, const T *__restrict__ a, int64_t cnt) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e < cnt) dz[e] *= gelu_grad_t<T>(a[e]);
-}
-
-// The screen input as a dense 0/1 matrix X[k][p] (p < 5N: bits of x', then
-// the one-hot fields of i, j, a, b), for the first-layer weight gradient
-// gW1 = X^T d1 as a plain product.
-template <typename T>
-__global__ void k_screen_input(int N, const uint64_t *__restrict__ keys, const uint8_t *__restrict__ exc, int64_t n,
-                               T *__restrict__ X) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= n * 5 * N) return;
-    const int64_t k = e / (5 * N);
-    const int p = (int)(e - k * 5 * N);
-    const int field = p / N, q = p - field * N;
-    bool on;
-    if (field == 0) on = ((q < 64 ? keys[2 * k] : keys[2 * k + 1]) >> (q & 63)) & 1ull;
-    else on = exc[4 * k + field - 1] == q;
-    X[e] = on ? T(1) : T(0);
-}
-
-template <typename T> __global__ void k_store_grad(const T *__restrict__ s, double *__restrict__ d, int64_t n) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k < n) d[k] = (double)s[k];
 }
@@ -658,68 +934,49 @@ __global__ void __launch_bounds__(256) k_sq_err_final(const double *__restrict__
     if (threadIdx.x == 0) out[0] = sh[0];
 }
 
-__global__ void k_convert_f32(const double *__restrict__ s, float *__restrict__ d, int64_t n) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n) d[k] = (float)s[k];
-}
-
 // Forward (and optionally the MSE gradient) in precision T.  Scratch holds
-// a1, z1, a2, d2, z2, dz1 ([n][H] each), y, gy ([n] each), the W2 gradient
-// ([H][H]), for FP32 a converted copy of W2 ([H][H]) and, with the gradient,
-// the dense input X ([n][5N]) and the W1 gradient ([5N][H]).
+// z1, z2 ([n][H] each) and y ([n]), with the gradient a1, a2, d1, d2, gy and
+// the partial sums of w3 ([16][H] FP64) too, and for FP32 a converted copy of
+// the weights.
 template <typename T>
 static nnqs_status screen_fwd_bwd(nnqs_screen *s, const uint64_t *keys, const uint8_t *exc, const double *target,
                                   int64_t n, double *pred, double *grad, double *loss, hipStream_t st) {
     const int N = s->N, H = s->H;
     const ScreenOff o = screen_off(N, H);
-    const size_t nh = (size_t)n * H, hh = (size_t)H * H;
-    const size_t nx = (size_t)n * 5 * N, xh = (size_t)5 * N * H;
-    nnqs_status r = ensure_scratch(s, (6 * nh + 2 * (size_t)n + 2 * hh + (grad ? nx + xh : 0)) * sizeof(T) + 256, st);
+    const size_t nh = (size_t)n * H, nw = sizeof(T) == 8 ? 0 : (size_t)o.total;
+    const size_t np = grad ? (size_t)16 * H : 0;
+    nnqs_status r =
+        ensure_scratch(s, np * 8 + ((grad ? 6 : 2) * nh + 2 * (size_t)n + nw) * sizeof(T) + 256, st);
     if (r != NNQS_OK) return r;
-    T *a1 = static_cast<T *>(s->scratch), *z1 = a1 + nh, *a2 = z1 + nh, *d2 = a2 + nh, *z2 = d2 + nh, *dz1 = z2 + nh,
-      *y = dz1 + nh, *gy = y + n, *w2c = gy + n, *gw2 = w2c + hh, *xin = gw2 + hh, *gw1 = xin + nx;
-    const T *W2;
-    if (sizeof(T) == 8) {
-        W2 = reinterpret_cast<const T *>(s->w + o.W2);
-    } else {
-        hipLaunchKernelGGL(k_convert_f32, dim3(gridfor((int64_t)hh)), dim3(256), 0, st, s->w + o.W2,
-                           reinterpret_cast<float *>(w2c), (int64_t)hh);
-        W2 = w2c;
-    }
-    hipLaunchKernelGGL(k_screen_layer1<T>, dim3(gridfor(nh)), dim3(256), 0, st, N, H, s->w, keys, exc, n, a1);
-    hipLaunchKernelGGL(k_gelu_copy<T>, dim3(gridfor(nh)), dim3(256), 0, st, a1, z1, (int64_t)nh);
-    hipLaunchKernelGGL(k_gemm<T>, dim3(gridfor(H, 16), (unsigned)((n + 15) / 16)), dim3(256), 0, st, z1, H, false, W2,
-                       H, false, a2, H, n, H, (int64_t)H);
-    hipLaunchKernelGGL(k_add_bias<T>, dim3(gridfor(nh)), dim3(256), 0, st, a2, s->w + o.b2, n, H);
-    hipLaunchKernelGGL(k_screen_out<T>, dim3(gridfor(n)), dim3(256), 0, st, a2, s->w, N, H, n, y);
-    if (pred) hipLaunchKernelGGL(k_to_double<T>, dim3(gridfor(n)), dim3(256), 0, st, y, pred, n);
+    double *w3p = static_cast<double *>(s->scratch);
+    T *z1 = reinterpret_cast<T *>(w3p + np), *z2 = z1 + nh, *y = z2 + nh, *gy = y + n, *wc = gy + n, *a1 = nullptr,
+      *a2 = nullptr, *d1 = nullptr, *d2 = nullptr;
     if (grad) {
-        if (loss)
-            hipLaunchKernelGGL(k_mse_loss, dim3(1), dim3(256), 0, st, target, (const void *)y, sizeof(T) == 8, n,
-                               loss);
-        hipLaunchKernelGGL(k_mse_grad<T>, dim3(gridfor(n)), dim3(256), 0, st, y, target, n, gy);
-        hipLaunchKernelGGL(k_back_out<T>, dim3(gridfor(nh)), dim3(256), 0, st, a2, gy, s->w, N, H, n, d2, z2);
-        hipLaunchKernelGGL(k_sum<T>, dim3(1), dim3(1024), 0, st, gy, n, grad + o.b3);
-        hipLaunchKernelGGL(k_colsum<T>, dim3(gridfor(H, 64)), dim3(1024), 0, st, z2, gy, n, H, grad + o.w3);
-        hipLaunchKernelGGL(k_colsum<T>, dim3(gridfor(H, 64)), dim3(1024), 0, st, d2, (const T *)nullptr, n, H,
-                           grad + o.b2);
-        // gW2 = z1^T d2 ([H][H])
-        hipLaunchKernelGGL(k_gemm<T>, dim3(gridfor(H, 16), gridfor(H, 16)), dim3(256), 0, st, z1, H, true, d2, H,
-                           false, gw2, H, (int64_t)H, H, n);
-        hipLaunchKernelGGL(k_store_grad<T>, dim3(gridfor((int64_t)hh)), dim3(256), 0, st, gw2, grad + o.W2,
-                           (int64_t)hh);
-        // dz1 = d2 W2^T, then times GELU'(a1)
-        hipLaunchKernelGGL(k_gemm<T>, dim3(gridfor(H, 16), (unsigned)((n + 15) / 16)), dim3(256), 0, st, d2, H,
-                           false, W2, H, true, dz1, H, n, H, (int64_t)H);
-        hipLaunchKernelGGL(k_mul_gelu_grad<T>, dim3(gridfor(nh)), dim3(256), 0, st, dz1, a1, (int64_t)nh);
-        hipLaunchKernelGGL(k_colsum<T>, dim3(gridfor(H, 64)), dim3(1024), 0, st, dz1, (const T *)nullptr, n, H,
-                           grad + o.b1);
-        // gW1 = X^T d1 ([5N][H])
-        hipLaunchKernelGGL(k_screen_input<T>, dim3(gridfor((int64_t)nx)), dim3(256), 0, st, N, keys, exc, n, xin);
-        hipLaunchKernelGGL(k_gemm<T>, dim3(gridfor(H, 16), gridfor((int64_t)5 * N, 16)), dim3(256), 0, st, xin, 5 * N,
-                           true, dz1, H, false, gw1, H, (int64_t)5 * N, H, n);
-        hipLaunchKernelGGL(k_store_grad<T>, dim3(gridfor((int64_t)xh)), dim3(256), 0, st, gw1, grad + o.W1,
-                           (int64_t)xh);
+        a1 = wc + nw;
+        a2 = a1 + nh;
+        d1 = a2 + nh;
+        d2 = d1 + nh;
+    }
+    const T *w;
+    if constexpr (sizeof(T) == 8) {
+        w = s->w;
+    } else {
+        hipLaunchKernelGGL(k_convert_f32, dim3(gridfor(o.total)), dim3(256), 0, st, s->w, wc, o.total);
+        w = wc;
+    }
+    const unsigned rt = gridfor(n, 32), ct = gridfor(H, 64);
+    hipLaunchKernelGGL(k_screen_layer1<T>, dim3(gridfor(n, 4)), dim3(256), 0, st, N, H, w, keys, exc, n, a1, z1);
+    hipLaunchKernelGGL((k_screen_hidden<T, false>), dim3(rt, ct), dim3(256), 0, st, (const T *)z1, w + o.W2, w + o.b2,
+                       (const T *)nullptr, n, H, a2, z2, (const T *)nullptr, (const T *)nullptr, (double *)nullptr);
+    hipLaunchKernelGGL(k_screen_out<T>, dim3(gridfor(n, 16)), dim3(256), 0, st, (const T *)a2, (const T *)z2, w, N, H, n,
+                       grad ? target : nullptr, y, pred, gy, d2);
+    if (grad) {
+        hipLaunchKernelGGL((k_screen_hidden<T, true>), dim3(rt + 16, ct), dim3(256), 0, st, (const T *)d2, w + o.W2,
+                           (const T *)nullptr, (const T *)a1, n, H, (T *)nullptr, d1, (const T *)z2, (const T *)gy, w3p);
+        const int jt = (H + 31) / 32, tiles = ((5 * N + 31) / 32 + jt) * jt;
+        hipLaunchKernelGGL(k_screen_grads<T>, dim3((unsigned)(2 + tiles)), dim3(256), 0, st, N, H, keys, exc, target, n,
+                           (const T *)z1, (const T *)d1, (const T *)d2, (const T *)y, (const T *)gy,
+                           (const double *)w3p, grad, loss);
     }
     NNQS_HIP_CHECK(hipGetLastError());
     return NNQS_OK;
