@@ -4,7 +4,7 @@
 // 64, 4 heads, FFN 256, phase hidden 512, K <= 64 orbitals.
 //
 // Phase MLP: bits[128 x 128] @ W1 and GELU(z1)[128 x 512] @ W2 on the 16x16x32
-// MFMA for 128 configurations per block, each wave owning 64 output columns
+// MFMA for 16 to 128 configurations per block, each wave owning 64 output columns
 // (weight fragments from L2, read once per block pass; z1 in LDS).
 #include <algorithm>
 #include <cmath>
@@ -48,16 +48,18 @@ static F32Layout f32_layout(int K, int L) {
 }
 
 // Phase MLP (Section 4.1): phi = b3 + w3 . GELU(GELU(bits W1 + b1) W2 + b2)
-// on BF16 MFMA with FP32 accumulation.  A block of kPhWaves waves takes 128
+// on BF16 MFMA with FP32 accumulation.  A block of kPhWaves waves takes 16 kGroups
 // configurations per pass; wave w owns output columns 64 w .. 64 w + 63 of
-// both layers, so each weight fragment is read once per 128 configurations
-// (held in registers across the eight groups of 16), the hidden layer z1
+// both layers, so each weight fragment is read once per pass (held in
+// registers across the groups of 16), the hidden layer z1
 // stays in LDS, and the four per-wave partial dot products of each
 // configuration are added in wave order at the end.
 // In list mode (see TfArgs) the configurations are xkeys[list[k]] for k
 // below the total of the four class counts, and phase[list[k]] receives them.
-constexpr int kPhWaves = 8, kPhRows = 16 * kPhWaves, kZld = kP + 8;
+constexpr int kPhWaves = 8, kZld = kP + 8;
+template <int kGroups>
 __global__ void __launch_bounds__(64 * kPhWaves) k_phase_bf16(Bf16View M, TfArgs A, double *__restrict__ phase) {
+    constexpr int kPhRows = 16 * kGroups;
     __shared__ __align__(16) __bf16 zs[kPhRows * kZld];
     __shared__ float parts[kPhWaves][kPhRows];
     const int l = threadIdx.x & 63;
@@ -69,8 +71,8 @@ __global__ void __launch_bounds__(64 * kPhWaves) k_phase_bf16(Bf16View M, TfArgs
     const int nbits = 2 * M.K;
     const int64_t n = A.list_mode ? A.hdr[0] + A.hdr[1] + A.hdr[2] + A.hdr[3] : A.n;
     for (int64_t base = (int64_t)blockIdx.x * kPhRows; base < n; base += (int64_t)gridDim.x * kPhRows) {
-        // z1 = GELU(bits @ W1 + b1) for the block's 128 configurations, this wave's 64 columns;
-        // the layer-1 B fragments (W1^T rows col0 + 16 cb + c16) serve all eight groups
+        // z1 = GELU(bits @ W1 + b1) for the block's configurations, this wave's 64 columns;
+        // the layer-1 B fragments (W1^T rows col0 + 16 cb + c16) serve all groups
         bf16x8 bw1[kPhaseBits / 32][4];
 #pragma unroll
         for (int ks = 0; ks < kPhaseBits / 32; ks++)
@@ -78,7 +80,7 @@ __global__ void __launch_bounds__(64 * kPhWaves) k_phase_bf16(Bf16View M, TfArgs
             for (int cb = 0; cb < 4; cb++)
                 bw1[ks][cb] =
                     *reinterpret_cast<const bf16x8 *>(w1T + (int64_t)(col0 + cb * 16 + c16) * kPhaseBits + ks * 32 + kq);
-        for (int rg = 0; rg < kPhWaves; rg++) {
+        for (int rg = 0; rg < kGroups; rg++) {
             const int64_t cr = base + 16 * rg + c16;
             Key x{0ull, 0ull};
             if (cr < n) {
@@ -111,19 +113,19 @@ __global__ void __launch_bounds__(64 * kPhWaves) k_phase_bf16(Bf16View M, TfArgs
         __syncthreads();  // z1 of every column written
         // phi partials: w3 . GELU(z1 @ W2 + b2) over this wave's columns, in two
         // halves of 32 columns (every W2 fragment is still read once per pass)
-        float part[kPhWaves][4];
+        float part[kGroups][4];
 #pragma unroll
-        for (int rg = 0; rg < kPhWaves; rg++)
+        for (int rg = 0; rg < kGroups; rg++)
 #pragma unroll
             for (int i = 0; i < 4; i++) part[rg][i] = 0.f;
 #pragma unroll 1
         for (int half = 0; half < 2; half++) {
-            f32x4 acc2[kPhWaves][2];
+            f32x4 acc2[kGroups][2];
 #pragma unroll
-            for (int rg = 0; rg < kPhWaves; rg++)
+            for (int rg = 0; rg < kGroups; rg++)
 #pragma unroll
                 for (int cb = 0; cb < 2; cb++) acc2[rg][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
+#pragma unroll(kGroups == 8 ? 2 : 8)
             for (int ks = 0; ks < kP; ks += 32) {
                 bf16x8 bw[2];
 #pragma unroll
@@ -131,7 +133,7 @@ __global__ void __launch_bounds__(64 * kPhWaves) k_phase_bf16(Bf16View M, TfArgs
                     bw[cb] = *reinterpret_cast<const bf16x8 *>(w2T + (int64_t)(col0 + (2 * half + cb) * 16 + c16) * kP +
                                                                ks + kq);
 #pragma unroll
-                for (int rg = 0; rg < kPhWaves; rg++) {
+                for (int rg = 0; rg < kGroups; rg++) {
                     const bf16x8 a = *reinterpret_cast<const bf16x8 *>(zs + (16 * rg + c16) * kZld + ks + kq);
 #pragma unroll
                     for (int cb = 0; cb < 2; cb++) acc2[rg][cb] = mfma16(a, bw[cb], acc2[rg][cb]);
@@ -142,13 +144,13 @@ __global__ void __launch_bounds__(64 * kPhWaves) k_phase_bf16(Bf16View M, TfArgs
                 const int col = col0 + (2 * half + cb) * 16 + c16;
                 const float bb = b2[col], ww = w3[col];
 #pragma unroll
-                for (int rg = 0; rg < kPhWaves; rg++)
+                for (int rg = 0; rg < kGroups; rg++)
 #pragma unroll
                     for (int i = 0; i < 4; i++) part[rg][i] += gelu32(acc2[rg][cb][i] + bb) * ww;
             }
         }
 #pragma unroll
-        for (int rg = 0; rg < kPhWaves; rg++) {
+        for (int rg = 0; rg < kGroups; rg++) {
 #pragma unroll
             for (int i = 0; i < 4; i++) part[rg][i] = dpp_row_sum(part[rg][i]);
             if (c16 == 0)
@@ -394,10 +396,22 @@ static unsigned tf_grid(int64_t n) {
     return (unsigned)(n < 1 ? 1 : n < cap ? n : cap);
 }
 
-static unsigned phase_grid(int64_t n) {
-    const int64_t cap = (int64_t)cu_count();  // one block per CU (z1 fills most of its LDS)
-    const int64_t b = (n + kPhRows - 1) / kPhRows;
-    return (unsigned)(b < 1 ? 1 : b < cap ? b : cap);
+template <int kGroups>
+static void phase_launch(int64_t blocks, hipStream_t st, const Bf16View &v, const TfArgs &A, double *phase) {
+    hipLaunchKernelGGL(k_phase_bf16<kGroups>, dim3((unsigned)std::max<int64_t>(blocks, 1)), dim3(kPhWaves * 64), 0, st, v,
+                       A, phase);
+}
+
+// Groups of 16 per block: the fewest that leave at most one block per CU.
+// Fewer groups shorten a block's pass (66 configurations in 41 us with eight,
+// 24 us with one), more read the weights less often where blocks would follow
+// one another (20,011: 41 us with eight, 109 us with one).
+static void phase_run(int64_t n, hipStream_t st, const Bf16View &v, const TfArgs &A, double *phase) {
+    const int64_t cus = cu_count(), groups = (n + 15) / 16;
+    if (groups <= cus) phase_launch<1>(groups, st, v, A, phase);
+    else if (groups <= 2 * cus) phase_launch<2>((groups + 1) / 2, st, v, A, phase);
+    else if (groups <= 4 * cus) phase_launch<4>((groups + 3) / 4, st, v, A, phase);
+    else phase_launch<8>(std::min((groups + 7) / 8, cus), st, v, A, phase);
 }
 
 nnqs_status enqueue_logpsi_bf16(const nnqs_model *m, const uint64_t *keys, int64_t n, double *logabs, double *phase,
@@ -417,7 +431,7 @@ nnqs_status enqueue_logpsi_bf16(const nnqs_model *m, const uint64_t *keys, int64
     }
     {
         TimedRegion tr("k_phase_bf16", st);
-        hipLaunchKernelGGL(k_phase_bf16, dim3(phase_grid(n)), dim3(kPhWaves * 64), 0, st, v, A, phase);
+        phase_run(n, st, v, A, phase);
     }
     NNQS_HIP_CHECK(hipGetLastError());
     return NNQS_OK;
@@ -483,7 +497,7 @@ nnqs_status enqueue_bf16_list(const nnqs_model *m, const uint64_t *xkeys, int64_
     }
     {
         TimedRegion tr("k_phase_bf16", st);
-        hipLaunchKernelGGL(k_phase_bf16, dim3(phase_grid(max_entries)), dim3(kPhWaves * 64), 0, st, v, A, xph);
+        phase_run(max_entries, st, v, A, xph);
     }
     NNQS_HIP_CHECK(hipGetLastError());
     return NNQS_OK;
@@ -516,7 +530,7 @@ nnqs_status enqueue_bf16_phase_list(const nnqs_model *m, const uint64_t *xkeys, 
     A.xkeys = xkeys;
     A.list_mode = 1;
     TimedRegion tr("k_phase_bf16", st);
-    hipLaunchKernelGGL(k_phase_bf16, dim3(phase_grid(max_entries)), dim3(kPhWaves * 64), 0, st, bf16_view(m), A, xph);
+    phase_run(max_entries, st, bf16_view(m), A, xph);
     NNQS_HIP_CHECK(hipGetLastError());
     return NNQS_OK;
 }

@@ -59,3 +59,21 @@ def test_part_filled_tiles(nn, K):
     for a, b in ((0, 1), (1, 4), (5, 12), (17, 274), (n - 9, n)):
         sa, sp = nn.model_logpsi(M, keys[a:b].contiguous(), nn.NNQS_BF16)
         assert torch.equal(sa, la[a:b]) and torch.equal(sp, ph[a:b]), (a, b)
+
+
+def test_phase_groups_agree(nn):
+    """The phase of a configuration is the same bits whatever the call's size:
+    lists on either side of each change of the group size (256 CUs) against
+    the configurations in calls of at most 16."""
+    K = 20
+    d = synth.config_inputs(2, K=K, n_up=5, n_dn=5, n_unique=16401, model=True)
+    M = nn.Model(d["model_shape"], 5, 5, d["weights"])
+    keys = dev(d["keys"])
+    cut = [(0, 16), (4080, 4096), (4095, 4097), (8190, 8195), (16380, 16390)]
+    few = {c: nn.model_logpsi(M, keys[c[0]:c[1]].contiguous(), nn.NNQS_BF16)[1] for c in cut}
+    for n in (4096, 4097, 8192, 8193, 16384, 16385):
+        print(f"[case] phase groups n={n}", flush=True)
+        ph = nn.model_logpsi(M, keys[:n].contiguous(), nn.NNQS_BF16)[1]
+        for (a, b), want in few.items():
+            m = min(b, n) - a
+            assert m <= 0 or torch.equal(ph[a:a + m], want[:m]), (n, a)
