@@ -16,7 +16,7 @@
 #include <algorithm>
 #include <cmath>
 
-#include "model.hpp"
+#include "transformer.hpp"
 
 namespace nnqs {
 
@@ -56,101 +56,176 @@ __device__ __forceinline__ int bas_token(const double *logp, double u) {
 }
 
 // One token per sample slot i < total; slot i belongs to the prefix u with
-// offs[u] <= i < offs[u + 1].  The lanes of a wave that land on the same
-// (prefix, token) add their count with one atomic.
+// offs[u] <= i < offs[u + 1].  A block takes 256 slots in a row: its threads
+// together find the first one's prefix (256 marks per round), and as every
+// prefix has a slot, the block's prefixes are the next 256 at most, whose
+// offsets go through LDS and its draws are counted there: one atomic per
+// (prefix, token) of a block.
 __global__ void __launch_bounds__(256) k_bas_draw(uint64_t total, int s, uint64_t seed,
                                                   const uint64_t *__restrict__ offs, int64_t n,
                                                   const double *__restrict__ cond,
                                                   unsigned long long *__restrict__ child) {
-    const int lane = threadIdx.x & 63;
-    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    for (uint64_t base = (uint64_t)blockIdx.x * blockDim.x + (threadIdx.x - lane); base < total; base += stride) {
-        const uint64_t i = base + lane;
-        int64_t key = -1;
+    __shared__ uint64_t so[256];
+    __shared__ uint32_t drawn[4 * 256];
+    const int t = threadIdx.x;
+    for (uint64_t base = (uint64_t)blockIdx.x * 256; base < total; base += (uint64_t)gridDim.x * 256) {
+        int64_t lo = 0, hi = n;  // offs[lo] <= base, and offs[hi] > base or hi = n
+        while (hi - lo > 1) {
+            const int64_t step = (hi - lo + 255) / 256, q = lo + t * step;
+            const int c = __syncthreads_count(q < hi && offs[q] <= base);
+            lo += (c - 1) * step;
+            hi = lo + step < hi ? lo + step : hi;
+        }
+        so[t] = lo + t < n ? offs[lo + t] : ~0ull;
+#pragma unroll
+        for (int q = 0; q < 4; q++) drawn[t + 256 * q] = 0;
+        __syncthreads();
+        const uint64_t i = base + t;
         if (i < total) {
-            int64_t lo = 0, hi = n;  // offs[lo] <= i < offs[hi]
-            while (hi - lo > 1) {
-                const int64_t mid = (lo + hi) >> 1;
-                if (offs[mid] <= i) lo = mid;
-                else hi = mid;
-            }
-            const int t = bas_token(cond + 4 * lo, bas_uniform(seed, s, i));
-            key = t >= 0 ? 4 * lo + t : -1;  // no allowed token: the prefix leaves the sector (not for valid models)
+            int k = 0;
+#pragma unroll
+            for (int step = 128; step >= 1; step >>= 1)
+                if (so[k + step] <= i) k += step;
+            const int64_t u = lo + k;
+            const int tok = bas_token(cond + 4 * u, bas_uniform(seed, s, i));
+            // no allowed token: the prefix leaves the sector (not for valid models)
+            if (tok >= 0) atomicAdd(&drawn[4 * k + tok], 1u);
         }
-        uint64_t pending = __ballot(key >= 0);
-        while (pending) {
-            const int leader = __ffsll((unsigned long long)pending) - 1;
-            const int64_t lk = __shfl(key, leader, 64);
-            const uint64_t same = __ballot(key == lk);
-            if (lane == leader) atomicAdd(child + lk, (unsigned long long)__popcll(same));
-            pending &= ~same;
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const uint32_t c = drawn[t + 256 * q];
+            if (c) atomicAdd(child + 4 * lo + t + 256 * q, (unsigned long long)c);
         }
+        __syncthreads();  // so and drawn are read before the next slots' are set
     }
 }
 
-// Exclusive prefix sums of n values (one block; each thread scans a
-// contiguous run) into out[0..n], out[n] = the total.
-template <typename T, typename F>
-__global__ void __launch_bounds__(1024) k_bas_scan(int64_t n, F value, T *__restrict__ out) {
-    __shared__ T part[1025];
-    const int64_t per = (n + 1023) / 1024;
-    const int64_t b0 = threadIdx.x * per, b1 = b0 + per < n ? b0 + per : n;
-    T run = 0;
-    for (int64_t k = b0; k < b1; k++) run += value(k);
-    part[threadIdx.x + 1] = run;
+constexpr int kBasBlock = 256;  // prefixes per block of the two kernels below
+
+__device__ __forceinline__ int children(const unsigned long long *child, int64_t u) {
+    return (child[4 * u] > 0) + (child[4 * u + 1] > 0) + (child[4 * u + 2] > 0) + (child[4 * u + 3] > 0);
+}
+
+// Sum over the block of v, for every thread (sh: 4 values).
+__device__ __forceinline__ int64_t block_sum(int64_t v, int64_t *sh) {
+    for (int d = 32; d; d >>= 1) v += __shfl_xor(v, d, 64);
     __syncthreads();
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    return ((sh[0] + sh[1]) + sh[2]) + sh[3];
+}
+
+__device__ __forceinline__ int64_t slots(const unsigned long long *child, int64_t u) {
+    return (int64_t)((child[4 * u] + child[4 * u + 1]) + (child[4 * u + 2] + child[4 * u + 3]));
+}
+
+// Children of each block's prefixes, and the slots they hold.
+__global__ void __launch_bounds__(kBasBlock) k_bas_count(int64_t n, const unsigned long long *__restrict__ child,
+                                                         int64_t *__restrict__ blk) {
+    __shared__ int64_t sh[4];
+    const int64_t u = (int64_t)blockIdx.x * kBasBlock + threadIdx.x;
+    const int64_t c = block_sum(u < n ? children(child, u) : 0, sh);
+    const int64_t s = block_sum(u < n ? slots(child, u) : 0, sh);
     if (threadIdx.x == 0) {
-        part[0] = 0;
-        for (int t = 1; t <= 1024; t++) part[t] += part[t - 1];
+        blk[2 * (int64_t)blockIdx.x] = c;
+        blk[2 * (int64_t)blockIdx.x + 1] = s;
+    }
+}
+
+// The arrays of one position's prefixes.
+struct BasLevel {
+    uint64_t *keys, *cnt, *offs;  // key, slots, first slot
+    double *lp;                   // log-probability of the path
+    unsigned long long *child;    // [4] slots drawn for each token
+    int32_t *path;                // [64] ancestors by position (with cached rows; else null)
+};
+
+// Children of prefix u, in (parent, token) order: the parent's key with the
+// token of position s (spatial orbital K-1-s: up bit 2i, down bit 2i+1), its
+// slots, the path's log-probability and ancestors.  A block's first child
+// follows the children of the blocks before it; every block adds those up
+// itself (a scan by one block and a launch of its own per array took 52 us a
+// position, of which 1,024 additions in a row were most).  No child beyond
+// `cap` is written; the last block reports the total.
+__global__ void __launch_bounds__(kBasBlock) k_bas_expand(int64_t n, int64_t cap, int K, int s, BasLevel P, BasLevel N,
+                                                          const double *__restrict__ cond,
+                                                          const int64_t *__restrict__ blk, int64_t *__restrict__ total) {
+    __shared__ int64_t sh[4];
+    __shared__ int wsum[4];
+    __shared__ int64_t wslots[4];
+    __shared__ uint8_t parent[4 * kBasBlock];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    int64_t before = 0, off = 0;  // children and slots of the blocks before
+    for (int64_t b = t; b < (int64_t)blockIdx.x; b += kBasBlock) {
+        before += blk[2 * b];
+        off += blk[2 * b + 1];
+    }
+    before = block_sum(before, sh);
+    off = block_sum(off, sh);
+    const int64_t u = (int64_t)blockIdx.x * kBasBlock + t;
+    const int mine = u < n ? children(P.child, u) : 0;
+    const int64_t held = u < n ? slots(P.child, u) : 0;
+    int pos = mine;  // inclusive scans over the wave
+    int64_t sl = held;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int v = __shfl_up(pos, d, 64);
+        const int64_t x = __shfl_up(sl, d, 64);
+        if (lane >= d) {
+            pos += v;
+            sl += x;
+        }
+    }
+    if (lane == 63) {
+        wsum[w] = pos;
+        wslots[w] = sl;
     }
     __syncthreads();
-    T pos = part[threadIdx.x];
-    for (int64_t k = b0; k < b1; k++) {
-        out[k] = pos;
-        pos += value(k);
+    pos -= mine;
+    off += sl - held;
+    for (int q = 0; q < w; q++) {
+        pos += wsum[q];
+        off += wslots[q];
     }
-    if (threadIdx.x == 0) out[n] = part[1024];
-}
-
-struct CountOf {
-    const uint64_t *c;
-    __device__ uint64_t operator()(int64_t k) const { return c[k]; }
-};
-struct ChildrenOf {
-    const unsigned long long *child;
-    __device__ int64_t operator()(int64_t k) const {
-        return (int64_t)(child[4 * k] > 0) + (child[4 * k + 1] > 0) + (child[4 * k + 2] > 0) + (child[4 * k + 3] > 0);
+    const int all = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+    if (blockIdx.x == gridDim.x - 1 && t == 0) *total = before + all;
+    if (u < n) {
+        const int i = K - 1 - s;
+        for (int tk = 0; tk < 4; tk++) {
+            const unsigned long long c = P.child[4 * u + tk];
+            if (!c) continue;
+            const int64_t p = before + pos;
+            parent[pos++] = (uint8_t)t;
+            if (p < cap) {
+                Key x;
+                x.lo = P.keys[2 * u];
+                x.hi = P.keys[2 * u + 1];
+                if (tk & 1) key_flip(x, 2 * i);
+                if (tk & 2) key_flip(x, 2 * i + 1);
+                N.keys[2 * p] = x.lo;
+                N.keys[2 * p + 1] = x.hi;
+                N.cnt[p] = c;
+                N.offs[p] = (uint64_t)off;
+                N.lp[p] = P.lp[u] + cond[4 * u + tk];
+#pragma unroll
+                for (int q = 0; q < 4; q++) N.child[4 * p + q] = 0;
+            }
+            off += (int64_t)c;
+        }
     }
-};
-
-__global__ void k_bas_zero(unsigned long long *p, int64_t n) {
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x) p[k] = 0;
-}
-
-// Children of prefix u, in token order, at pos[u]...: the parent's key with
-// the token of position s (spatial orbital K-1-s: up bit 2i, down bit 2i+1),
-// its slot count and the path's log-probability.
-__global__ void k_bas_expand(int64_t n, int K, int s, const uint64_t *__restrict__ keys, const double *__restrict__ lp,
-                             const double *__restrict__ cond, const unsigned long long *__restrict__ child,
-                             const int64_t *__restrict__ pos, uint64_t *__restrict__ nkeys, uint64_t *__restrict__ ncnt,
-                             double *__restrict__ nlp) {
-    const int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (u >= n) return;
-    const int i = K - 1 - s;
-    int64_t p = pos[u];
-    for (int t = 0; t < 4; t++) {
-        const unsigned long long c = child[4 * u + t];
-        if (!c) continue;
-        Key x;
-        x.lo = keys[2 * u];
-        x.hi = keys[2 * u + 1];
-        if (t & 1) key_flip(x, 2 * i);
-        if (t & 2) key_flip(x, 2 * i + 1);
-        nkeys[2 * p] = x.lo;
-        nkeys[2 * p + 1] = x.hi;
-        ncnt[p] = c;
-        nlp[p] = lp[u] + cond[4 * u + t];
-        p++;
+    if (!N.path) return;
+    __syncthreads();
+    const int q0 = 4 * (t & 15);  // 16 lanes per child, four positions each
+    if (q0 > s) return;
+#pragma unroll 4
+    for (int j = t >> 4; j < all; j += kBasBlock / 16) {
+        const int64_t p = before + j, up = (int64_t)blockIdx.x * kBasBlock + parent[j];
+        int4 v = q0 < s ? *reinterpret_cast<const int4 *>(P.path + up * 64 + q0) : int4{0, 0, 0, 0};
+        if (q0 == s) v.x = (int32_t)up;
+        else if (q0 + 1 == s) v.y = (int32_t)up;
+        else if (q0 + 2 == s) v.z = (int32_t)up;
+        else if (q0 + 3 == s) v.w = (int32_t)up;
+        if (p < cap) *reinterpret_cast<int4 *>(N.path + p * 64 + q0) = v;
     }
 }
 
@@ -162,33 +237,131 @@ __global__ void k_bas_finish(int64_t n, const uint64_t *__restrict__ cnt, const 
     logabs_out[u] = 0.5 * lp[u];
 }
 
-__global__ void k_bas_init(uint64_t *keys, uint64_t *cnt, double *lp, uint64_t total) {
-    keys[0] = 0ull;
-    keys[1] = 0ull;
-    cnt[0] = total;
-    lp[0] = 0.0;
+__global__ void k_bas_init(BasLevel P, uint64_t total) {
+    P.keys[0] = 0ull;
+    P.keys[1] = 0ull;
+    P.cnt[0] = total;
+    P.offs[0] = 0ull;
+    P.lp[0] = 0.0;
+    for (int q = 0; q < 4; q++) P.child[q] = 0;
 }
 
-struct BasScratch {
-    uint64_t *pk = nullptr, *nk = nullptr, *pc = nullptr, *nc = nullptr, *offs = nullptr;
-    double *pl = nullptr, *nl = nullptr, *cond = nullptr, *la = nullptr, *ph = nullptr;
-    unsigned long long *child = nullptr;
-    int64_t *pos = nullptr;
-    ~BasScratch() {
-        hipFree(pk);
-        hipFree(nk);
-        hipFree(pc);
-        hipFree(nc);
-        hipFree(offs);
-        hipFree(pl);
-        hipFree(nl);
-        hipFree(cond);
-        hipFree(la);
-        hipFree(ph);
-        hipFree(child);
-        hipFree(pos);
+}  // namespace nnqs
+
+// Workspace of a sampling call: two levels of up to `cap` prefixes, and for the
+// BF16 network every position's rows, grown to the number of prefixes seen.
+// A call takes the model's workspace, or makes one where another call has it,
+// and leaves it with the model if it holds at most kBasKeep bytes.
+struct BasWork {
+    size_t cap = 0, row_cap[64] = {}, bytes = 0;
+    bool paths = false;
+    void *level[2] = {}, *path[2] = {};
+    double *cond = nullptr, *la = nullptr;
+    int64_t *blk = nullptr, *total = nullptr;  // total: host memory
+    void *rows[64] = {};
+    ~BasWork() {
+        for (int i = 0; i < 2; i++) {
+            (void)hipFree(level[i]);
+            (void)hipFree(path[i]);
+        }
+        (void)hipFree(cond);
+        (void)hipFree(la);
+        (void)hipFree(blk);
+        (void)hipHostFree(total);
+        for (void *r : rows) (void)hipFree(r);
     }
 };
+
+namespace nnqs {
+
+constexpr size_t kBasKeep = (size_t)4 << 30;
+
+void bas_model_free(nnqs_model *m) { delete m->bas_work.exchange(nullptr); }
+
+// Holds a workspace for one call; the stream is idle when it goes back.
+struct BasHold {
+    nnqs_model *m;
+    hipStream_t st;
+    BasWork *w;
+    BasHold(nnqs_model *model, hipStream_t stream) : m(model), st(stream), w(model->bas_work.exchange(nullptr)) {
+        if (!w) w = new BasWork();
+    }
+    ~BasHold() {
+        (void)hipStreamSynchronize(st);
+        BasWork *none = nullptr;
+        if (w->bytes > kBasKeep || !m->bas_work.compare_exchange_strong(none, w)) delete w;
+    }
+};
+
+static bool bas_grow(BasWork &W, size_t cap, bool paths) {
+    if (W.cap >= cap && (W.paths || !paths)) return true;
+    for (int i = 0; i < 2; i++) {
+        (void)hipFree(W.level[i]);
+        (void)hipFree(W.path[i]);
+        W.level[i] = W.path[i] = nullptr;
+    }
+    (void)hipFree(W.cond);
+    (void)hipFree(W.la);
+    (void)hipFree(W.blk);
+    W.cond = W.la = nullptr;
+    W.blk = nullptr;
+    cap = std::max(cap, W.cap);
+    paths = paths || W.paths;
+    W.cap = 0;
+    W.paths = false;
+    bool ok = W.total || hipHostMalloc(reinterpret_cast<void **>(&W.total), 8) == hipSuccess;
+    for (int i = 0; i < 2; i++) ok = ok && hipMalloc(&W.level[i], cap * 72) == hipSuccess;
+    ok = ok && hipMalloc(&W.cond, cap * 32) == hipSuccess && hipMalloc(&W.la, cap * 8) == hipSuccess &&
+         hipMalloc(&W.blk, (cap / kBasBlock + 1) * 16) == hipSuccess;
+    if (!ok) return false;
+    if (paths) {
+        for (int i = 0; i < 2; i++) paths = paths && hipMalloc(&W.path[i], cap * 256) == hipSuccess;
+        if (!paths) {  // sampling goes on without cached rows
+            (void)hipGetLastError();
+            for (int i = 0; i < 2; i++) {
+                (void)hipFree(W.path[i]);
+                W.path[i] = nullptr;
+            }
+        }
+    }
+    W.cap = cap;
+    W.paths = paths;
+    W.bytes = cap * (2 * 72 + 32 + 8 + (paths ? 512 : 0));
+    for (size_t r : W.row_cap) W.bytes += r;
+    return true;
+}
+
+static BasLevel bas_level(const BasWork &W, int i, bool paths) {
+    BasLevel v{};
+    uint8_t *p = static_cast<uint8_t *>(W.level[i]);
+    v.keys = reinterpret_cast<uint64_t *>(p);
+    v.cnt = reinterpret_cast<uint64_t *>(p + W.cap * 16);
+    v.offs = reinterpret_cast<uint64_t *>(p + W.cap * 24);
+    v.lp = reinterpret_cast<double *>(p + W.cap * 32);
+    v.child = reinterpret_cast<unsigned long long *>(p + W.cap * 40);
+    v.path = paths ? static_cast<int32_t *>(W.path[i]) : nullptr;
+    return v;
+}
+
+// Room for the rows of n prefixes at position s, with a quarter to spare and
+// at most a quarter of the free memory at a time; false: not to be had.
+static bool bas_rows(BasWork &W, int s, size_t need, size_t most) {
+    if (W.row_cap[s] >= need) return true;
+    const size_t want = std::min(need + need / 4, most);
+    size_t free_b = 0, all_b = 0;
+    if (hipMemGetInfo(&free_b, &all_b) != hipSuccess || want > free_b / 4) return false;
+    (void)hipFree(W.rows[s]);
+    W.bytes -= W.row_cap[s];
+    W.rows[s] = nullptr;
+    W.row_cap[s] = 0;
+    if (hipMalloc(&W.rows[s], want) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    W.row_cap[s] = want;
+    W.bytes += want;
+    return true;
+}
 
 }  // namespace nnqs
 
@@ -207,49 +380,58 @@ extern "C" nnqs_status nnqs_bas(nnqs_model *model, int32_t precision, uint64_t s
     if (precision != NNQS_FP64 && precision != NNQS_BF16) return fail(NNQS_EUNSUPPORTED, "sampling runs in FP64 or BF16");
     hipStream_t st = as_stream(stream);
     const int K = model->desc.n_orb;
-    const size_t cap = (size_t)capacity;
-    BasScratch S;
-    if (hipMalloc(&S.pk, cap * 16) != hipSuccess || hipMalloc(&S.nk, cap * 16) != hipSuccess ||
-        hipMalloc(&S.pc, cap * 8) != hipSuccess || hipMalloc(&S.nc, cap * 8) != hipSuccess ||
-        hipMalloc(&S.offs, (cap + 1) * 8) != hipSuccess || hipMalloc(&S.pl, cap * 8) != hipSuccess ||
-        hipMalloc(&S.nl, cap * 8) != hipSuccess || hipMalloc(&S.cond, cap * 32) != hipSuccess ||
-        hipMalloc(&S.la, cap * 8) != hipSuccess || hipMalloc(&S.ph, cap * 8) != hipSuccess ||
-        hipMalloc(&S.child, cap * 32) != hipSuccess || hipMalloc(&S.pos, (cap + 1) * 8) != hipSuccess)
-        return fail(NNQS_ENOMEM, "sampling scratch for %lld prefixes", (long long)capacity);
-    hipLaunchKernelGGL(k_bas_init, dim3(1), dim3(1), 0, st, S.pk, S.pc, S.pl, (uint64_t)n_samples);
+    const bool bf16 = precision == NNQS_BF16;
+    // every prefix has a slot: never more prefixes than samples
+    const size_t cap = (size_t)std::min<uint64_t>((uint64_t)capacity, n_samples);
+    BasHold hold(model, st);
+    BasWork &W = *hold.w;
+    if (!bas_grow(W, cap, bf16)) return fail(NNQS_ENOMEM, "sampling scratch for %lld prefixes", (long long)cap);
+    bool cached = bf16 && W.paths;
+    const size_t entry = rows_entry_bytes(model->desc.n_layers);
+    BasLevel P = bas_level(W, 0, cached), N = bas_level(W, 1, cached);
+    hipLaunchKernelGGL(k_bas_init, dim3(1), dim3(1), 0, st, P, (uint64_t)n_samples);
+    const unsigned dg = (unsigned)std::min<uint64_t>((n_samples + 255) / 256, 8192);
     int64_t n = 1;
     for (int s = 0; s < K; s++) {
-        nnqs_status r = precision == NNQS_FP64 ? enqueue_logpsi_f64(model, S.pk, n, S.la, nullptr, st, s, S.cond)
-                                               : enqueue_bf16_cond(model, S.pk, n, s, S.cond, S.la, st);
+        cached = cached && bas_rows(W, s, (size_t)n * entry, cap * entry);
+        nnqs_status r;
+        if (cached) {
+            RowsArgs A{};
+            A.keys = P.keys;
+            A.path = P.path;
+            A.n = n;
+            A.s = s;
+            A.cond = W.cond;
+            for (int i = 0; i <= s; i++) A.rows.p[i] = static_cast<__bf16 *>(W.rows[i]);
+            r = enqueue_bf16_rows(model, A, st);
+        } else {
+            r = bf16 ? enqueue_bf16_cond(model, P.keys, n, s, W.cond, W.la, st)
+                     : enqueue_logpsi_f64(model, P.keys, n, W.la, nullptr, st, s, W.cond);
+        }
         if (r != NNQS_OK) return r;
-        hipLaunchKernelGGL((k_bas_scan<uint64_t, CountOf>), dim3(1), dim3(1024), 0, st, n, CountOf{S.pc}, S.offs);
-        hipLaunchKernelGGL(k_bas_zero, dim3((unsigned)std::min<int64_t>((4 * n + 255) / 256, 4096)), dim3(256), 0, st,
-                           S.child, 4 * n);
-        const unsigned dg = (unsigned)std::min<uint64_t>((n_samples + 255) / 256, 8192);
-        hipLaunchKernelGGL(k_bas_draw, dim3(dg), dim3(256), 0, st, (uint64_t)n_samples, s, seed, (const uint64_t *)S.offs,
-                           n, (const double *)S.cond, S.child);
-        hipLaunchKernelGGL((k_bas_scan<int64_t, ChildrenOf>), dim3(1), dim3(1024), 0, st, n, ChildrenOf{S.child},
-                           S.pos);
-        int64_t m = 0;
-        NNQS_HIP_CHECK(hipMemcpyAsync(&m, S.pos + n, 8, hipMemcpyDeviceToHost, st));
-        NNQS_HIP_CHECK(hipStreamSynchronize(st));
-        if (m > capacity) return fail(NNQS_ERANGE, "%lld prefixes at position %d exceed the capacity %lld", (long long)m, s,
-                                      (long long)capacity);
-        hipLaunchKernelGGL(k_bas_expand, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, K, s,
-                           (const uint64_t *)S.pk, (const double *)S.pl, (const double *)S.cond,
-                           (const unsigned long long *)S.child, (const int64_t *)S.pos, S.nk, S.nc, S.nl);
+        hipLaunchKernelGGL(k_bas_draw, dim3(dg), dim3(256), 0, st, (uint64_t)n_samples, s, seed,
+                           (const uint64_t *)P.offs, n, (const double *)W.cond, P.child);
+        const unsigned nb = (unsigned)((n + kBasBlock - 1) / kBasBlock);
+        hipLaunchKernelGGL(k_bas_count, dim3(nb), dim3(kBasBlock), 0, st, n, (const unsigned long long *)P.child, W.blk);
+        if (!cached) P.path = N.path = nullptr;
+        hipLaunchKernelGGL(k_bas_expand, dim3(nb), dim3(kBasBlock), 0, st, n, (int64_t)cap, K, s, P, N,
+                           (const double *)W.cond, (const int64_t *)W.blk, W.total);
         NNQS_HIP_CHECK(hipGetLastError());
-        std::swap(S.pk, S.nk);
-        std::swap(S.pc, S.nc);
-        std::swap(S.pl, S.nl);
+        NNQS_HIP_CHECK(hipStreamSynchronize(st));
+        const int64_t m = *const_cast<volatile int64_t *>(W.total);
+        if (m > (int64_t)cap) return fail(NNQS_ERANGE, "%lld prefixes at position %d exceed the capacity %lld",
+                                          (long long)m, s, (long long)capacity);
+        if (m < 1) return fail(NNQS_EHIP, "no token is allowed at position %d", s);
+        std::swap(P, N);
         n = m;
     }
-    NNQS_HIP_CHECK(hipMemcpyAsync(keys_out, S.pk, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
-    hipLaunchKernelGGL(k_bas_finish, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, (const uint64_t *)S.pc,
-                       (const double *)S.pl, counts_out, logabs_out);
+    NNQS_HIP_CHECK(hipMemcpyAsync(keys_out, P.keys, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
+    hipLaunchKernelGGL(k_bas_finish, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n, (const uint64_t *)P.cnt,
+                       (const double *)P.lp, counts_out, logabs_out);
     NNQS_HIP_CHECK(hipGetLastError());
     if (phase_out) {
-        nnqs_status r = enqueue_logpsi(model, keys_out, n, precision, S.la, phase_out, st);
+        nnqs_status r = bf16 ? enqueue_phase_bf16(model, keys_out, n, phase_out, st)
+                             : enqueue_logpsi(model, keys_out, n, precision, W.la, phase_out, st);
         if (r != NNQS_OK) return r;
     }
     NNQS_HIP_CHECK(hipStreamSynchronize(st));

@@ -279,6 +279,7 @@ nnqs_status nnqs_model_destroy(nnqs_model *m) {
     hipFree(m->d_grads);
     bf16_model_free(m);
     eloc_model_free(m);
+    bas_model_free(m);
     delete m;
     return NNQS_OK;
 }

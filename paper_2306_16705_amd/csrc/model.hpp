@@ -1,6 +1,8 @@
 // Internal definitions of the wave-function model (see model.hip).
 #pragma once
 
+#include <atomic>
+
 #include "internal.hpp"
 
 namespace nnqs {
@@ -102,10 +104,13 @@ struct nnqs_model {
     unsigned long long *d_ddbest = nullptr;
     uint8_t *d_repmask = nullptr, *d_refmask = nullptr;
     int64_t ddcap = 0, maskcap = 0;
+    // batch sampling's workspace, while no call has it (bas.hip)
+    std::atomic<struct BasWork *> bas_work{nullptr};
 };
 
 namespace nnqs {
 ModelView model_view(const nnqs_model *m);
+void bas_model_free(nnqs_model *m);
 nnqs_status enqueue_logpsi(const nnqs_model *m, const uint64_t *keys, int64_t n, int32_t precision, double *logabs,
                            double *phase, hipStream_t st);
 // allocates the reduced-precision copies; refresh writes them from the FP64 weights

@@ -452,6 +452,23 @@ nnqs_status enqueue_bf16_cond(const nnqs_model *m, const uint64_t *keys, int64_t
     return NNQS_OK;
 }
 
+nnqs_status enqueue_bf16_rows(const nnqs_model *m, const RowsArgs &A, hipStream_t st) {
+    if (!m->bf16_ok) return fail(NNQS_EUNSUPPORTED, "BF16 forward needs d_model 64, 4 heads, FFN 256, P 512, K <= 64");
+    TimedRegion tr("k_transformer_rows", st);
+    return tf_launch_rows(cu_count(), st, bf16_view(m), A);
+}
+
+nnqs_status enqueue_phase_bf16(const nnqs_model *m, const uint64_t *keys, int64_t n, double *phase, hipStream_t st) {
+    if (!m->bf16_ok) return fail(NNQS_EUNSUPPORTED, "BF16 forward needs d_model 64, 4 heads, FFN 256, P 512, K <= 64");
+    TfArgs A{};
+    A.keys = keys;
+    A.n = n;
+    TimedRegion tr("k_phase_bf16", st);
+    phase_run(n, st, bf16_view(m), A, phase);
+    NNQS_HIP_CHECK(hipGetLastError());
+    return NNQS_OK;
+}
+
 int64_t bf16_cache_elems(const nnqs_model *m) { return (int64_t)m->desc.n_layers * (kH / 2) * kKvPerPair; }
 
 nnqs_status enqueue_bf16_cached(const nnqs_model *m, const uint64_t *keys, int64_t n, double *logabs, __bf16 *kv,

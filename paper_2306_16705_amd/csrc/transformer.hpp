@@ -5,6 +5,7 @@
 // FP32 accumulation; LayerNorm, softmax, GELU and the output head stay FP32.
 #pragma once
 
+#include <algorithm>
 #include <cmath>
 
 #include "model.hpp"
@@ -879,6 +880,23 @@ __device__ __forceinline__ void transformer(const Bf16View &M0, const TfArgs &A0
 // Launches (transformer_*.hip); grid: blocks of kTfWaves waves.
 void tf_launch_sample(bool fp8, unsigned grid, hipStream_t st, const Bf16View &M, const TfArgs &A);
 void tf_launch_list(bool fp8, unsigned grid, hipStream_t st, const Bf16View &M, const TfArgs &A);
+// One position of batch sampling (transformer_rows.hip): conditionals of
+// position s for n prefixes.
+struct RowPtrs {
+    __bf16 *p[64];  // per position: the rows of its prefixes ([L][2 pairs of heads][K 32 | V 32] each)
+};
+struct RowsArgs {
+    const uint64_t *keys;   // [n][2], bits of the tokens before s
+    const int32_t *path;    // [n][64]: the prefix's ancestor among those of position i < s
+    int64_t n;
+    int s, per;             // per: prefixes per wave (set by the launch)
+    double *cond;           // [n][4]
+    RowPtrs rows;           // rows of positions < s read, of s written
+};
+nnqs_status tf_launch_rows(int cus, hipStream_t st, const Bf16View &M, RowsArgs A);
+size_t rows_entry_bytes(int n_layers);  // of one prefix's row
+nnqs_status enqueue_bf16_rows(const nnqs_model *m, const RowsArgs &A, hipStream_t st);
+nnqs_status enqueue_phase_bf16(const nnqs_model *m, const uint64_t *keys, int64_t n, double *phase, hipStream_t st);
 void tf_launch_batch(unsigned grid, hipStream_t st, const Bf16View &M0, const TfItem *items, int n_items);
 
 }  // namespace nnqs
