@@ -24,7 +24,7 @@ struct nnqs_batch {
     int waves = 12;
     size_t lds = 0;
     unsigned grid = 0;
-    int ntiles = 0;
+    int ntiles = 0, nscan = 0;  // tiles of the enumerated systems, then of those whose tables are read whole
     nnqs::SaBatchItem *d_items = nullptr;
     nnqs::SaTile *d_tiles = nullptr;
     int *d_counter = nullptr;
@@ -50,7 +50,7 @@ static nnqs_status batch_plan(nnqs_batch *b) {
     batch_drop_graph(b);
     const int n_items = (int)b->items.size();
     std::vector<SaBatchItem> hi(n_items);
-    std::vector<SaTile> tiles;
+    std::vector<SaTile> tiles, scan;
     int fl_min = b->tune.filter_log2_bits;
     b->W = 1;
     for (const auto &it : b->items)
@@ -83,16 +83,20 @@ static nnqs_status batch_plan(nnqs_batch *b) {
         d.phase = it.phase;
         d.eloc = it.eloc;
         d.status = it.table->status;
-        for (int64_t s0 = 0; s0 < it.n; s0 += b->tune.tile_samples) {
+        const bool scans = sa_scans(d.S, it.n, it.n, kScanFixed / 16);
+        const int64_t per = scans ? 16 : b->tune.tile_samples;
+        for (int64_t s0 = 0; s0 < it.n; s0 += per) {
             SaTile t;
             t.item = k;
             t.begin = s0;
-            t.count = (int32_t)std::min<int64_t>(b->tune.tile_samples, it.n - s0);
-            tiles.push_back(t);
+            t.count = (int32_t)std::min<int64_t>(per, it.n - s0);
+            (scans ? scan : tiles).push_back(t);
         }
     }
+    b->ntiles = (int)std::min<size_t>(tiles.size(), INT32_MAX);
+    b->nscan = (int)std::min<size_t>(scan.size(), INT32_MAX);
+    tiles.insert(tiles.end(), scan.begin(), scan.end());
     if (tiles.size() > (size_t)INT32_MAX) return fail(NNQS_EINVAL, "too many tiles");
-    b->ntiles = (int)tiles.size();
     hipFree(b->d_items);
     hipFree(b->d_tiles);
     b->d_items = nullptr;
@@ -122,8 +126,10 @@ static nnqs_status batch_step(nnqs_batch *b, hipStream_t st) {
         nnqs_status s = nnqs_table_build(it.table, it.keys, it.logabs, it.phase, it.n, 0, st);
         if (s != NNQS_OK) return s;
     }
-    sa_launch_batch(b->W, b->tune.search, b->grid, b->waves, b->lds, st, b->d_items, b->d_tiles, b->ntiles,
-                    b->d_counter);
+    if (b->nscan) sa_launch_scan_batch(b->W, st, b->d_items, b->d_tiles + b->ntiles, b->nscan);
+    if (b->ntiles)
+        sa_launch_batch(b->W, b->tune.search, b->grid, b->waves, b->lds, st, b->d_items, b->d_tiles, b->ntiles,
+                        b->d_counter);
     NNQS_HIP_CHECK(hipGetLastError());
     for (const auto &it : b->items) {
         if (!it.energy) continue;

@@ -13,6 +13,9 @@
 // log-polar amplitude ratio and a per-lane Neumaier sum (Eq. 4 fused with
 // the accumulation as in Section 3.4 item 2).  The filter has no false
 // negatives, so every table member connected to x is found.
+//
+// A table that holds fewer members than x has connections is scanned instead
+// (scan_sample).
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -521,6 +524,283 @@ __global__ void __launch_bounds__(kSaMaxThreads) k_eloc_sa_batch(const SaBatchIt
 
 __global__ void k_reset_counter(int *c) { *c = 0; }
 
+// ---------------------------------------------------------------- scan path
+// A table smaller than the number of connections of a sample is cheaper to
+// read whole: the connected members are those that differ from x in zero, two
+// or four bits with the spins' electron numbers kept.  A wave takes one sample
+// and 64 members at a time, kScanAhead loads in flight; the few that differ in
+// at most four bits go through the queue of 64, and their indices are their
+// table entries, so there is no filter, no search and nothing to stage.  Per
+// hit the same element, ratio and compensated sums as sa_sample; samples far
+// below the largest amplitude take the ratio from exp and sincos here too.
+// Of equal members (NNQS_EDUP) the first counts, as a search would find it.
+// Bound: VALU issue and the L1's 64 bytes per cycle in long tables (1.3e12
+// members a second), the latency of the hits' integrals in short ones.  K = 58,
+// 1,501 members and samples (C = 803,986): 1,355 us enumerated, 90 us scanned.
+constexpr int kScanWaves = 4, kScanAhead = 4;
+
+// wave_diag and single_element with eight integral loads in flight and their
+// sums in the same order: a scan has few other instructions to cover the
+// latency of one load after another (K = 58, 1,501 samples: 227 against 129 us).
+__device__ __forceinline__ double scan_diag(const SysView &S, const WaveLds &wl) {
+    const int lane = lane_id();
+    const int nu = S.n_up, ntot = S.n_up + S.n_dn, K = S.K;
+    auto occ = [&](int t) -> int { return t < nu ? wl.occ[0][t] : wl.occ[1][t - nu]; };
+    double part = 0.0;
+    for (int t = lane; t < ntot; t += 64) {
+        const int ip = occ(t) >> 1;
+        part += S.h[ip * K + ip];
+    }
+    const int npairs = ntot * ntot;
+    for (int t0 = lane; t0 < npairs; t0 += 64 * 8) {
+        double jv[8], kv[8];
+        bool same[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            const int t = t0 + 64 * u < npairs ? t0 + 64 * u : lane, a = t / ntot, b = t - a * ntot;
+            const int p = occ(a), q = occ(b), e = (p >> 1) * K + (q >> 1);
+            jv[u] = S.Jm[e];
+            kv[u] = S.Km[e];
+            same[u] = ((p ^ q) & 1) == 0;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            if (t0 + 64 * u < npairs) {
+                double v = jv[u];
+                if (same[u]) v -= kv[u];
+                part += 0.5 * v;
+            }
+    }
+    return S.ecore + wave_sum_plain(part);
+}
+
+__device__ __forceinline__ double scan_single(const SysView &S, const Key &x, int q, int p) {
+    const int K = S.K, ip = p >> 1, iq = q >> 1, sp = p & 1;
+    double v = S.h[ip * K + iq];
+    uint64_t lo = x.lo, hi = x.hi;
+    while (lo | hi) {  // the occupied orbitals are the same for all lanes
+        int k[8];
+        double c[8], e[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) {
+            k[u] = -1;
+            if (lo) {
+                k[u] = __ffsll((unsigned long long)lo) - 1;
+                lo &= lo - 1;
+            } else if (hi) {
+                k[u] = 63 + __ffsll((unsigned long long)hi);
+                hi &= hi - 1;
+            }
+            const int ik = k[u] < 0 ? 0 : k[u] >> 1;
+            c[u] = g_at(S, ip, iq, ik, ik);
+            e[u] = g_at(S, ip, ik, ik, iq);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < 8; u++)
+            if (k[u] >= 0) {
+                double t = c[u];
+                if ((k[u] & 1) == sp) t -= e[u];
+                v += t;
+            }
+    }
+    return v;
+}
+
+// Members [k0, k1) for sample smp; the two compensated sums go to sum[0..3] as
+// (real, its error, imaginary, its error).  False: the sample is refused.
+template <int W>
+__device__ __forceinline__ bool scan_sample(const SysView &S, const TableView &T, WaveLds &wl, int64_t smp, uint32_t k0,
+                                            uint32_t k1, const uint64_t *__restrict__ keys,
+                                            const double *__restrict__ logabs, const double *__restrict__ phase,
+                                            double *__restrict__ eloc, int *status, double (&sum)[4]) {
+    const int lane = lane_id();
+    Key x;
+    x.lo = keys[2 * smp];
+    x.hi = keys[2 * smp + 1];
+    const double la = logabs[smp], ph = phase[smp];
+    if (!sample_conserves(S, x) || !isfinite(la) || !isfinite(ph)) {
+        if (lane == 0) {
+            eloc[2 * smp] = NAN;
+            eloc[2 * smp + 1] = NAN;
+            set_status(status, sample_conserves(S, x) ? NNQS_ERANGE : NNQS_ECONSERVE);
+        }
+        return false;
+    }
+    build_lists(S, x, wl);
+    const double diag = scan_diag(S, wl);
+    const double lmax = T.lmax[0];
+    const bool exact = !(la - lmax >= -600.0);
+    double xs = 0.0, xsn, xcs;
+    sincos(ph, &xsn, &xcs);
+    if (!exact) xs = exp(lmax - la);
+    NSum are{0.0, 0.0}, aim{0.0, 0.0};
+    int qh = 0, qt = 0;  // wave-uniform ring counters (ring of 256)
+    auto process = [&](uint32_t k) {
+        const Key y = load_key<2>(T.keys, k);
+        const Key hole = {x.lo & ~y.lo, x.hi & ~y.hi}, part = {y.lo & ~x.lo, y.hi & ~x.hi};
+        const int hu = __popcll(hole.lo & EVEN_BITS) + __popcll(hole.hi & EVEN_BITS);
+        const int hd = __popcll(hole.lo & ODD_BITS) + __popcll(hole.hi & ODD_BITS);
+        const int pu = __popcll(part.lo & EVEN_BITS) + __popcll(part.hi & EVEN_BITS);
+        const int pd = __popcll(part.lo & ODD_BITS) + __popcll(part.hi & ODD_BITS);
+        if (hu != pu || hd != pd || hu + hd > 2 || ((part.lo & ~S.valid0) | (part.hi & ~S.valid1))) return;
+        if (k > 0 && key_eq(load_key<2>(T.keys, k - 1), y)) return;
+        auto first = [](const Key &b) { return b.lo ? __ffsll((unsigned long long)b.lo) - 1 : 63 + __ffsll((unsigned long long)b.hi); };
+        auto last = [](const Key &b) { return b.hi ? 127 - __clzll((long long)b.hi) : 63 - __clzll((long long)b.lo); };
+        int i = 255, j = 255, a = 255, b = 255, sg;
+        if (hu + hd > 0) {
+            i = first(hole);
+            a = first(part);
+        }
+        if (hu + hd == 2) {
+            j = last(hole);
+            b = last(part);
+        }
+        const double hv = i != 255 && j == 255 ? (single_parity(x, i, a) ? -1 : 1) * scan_single(S, x, i, a)
+                                               : excitation_element(S, x, diag, i, j, a, b, &sg);
+        if (!exact) {
+            const double ar = T.amp[2 * (size_t)k], ai = T.amp[2 * (size_t)k + 1];
+            are.add(hv * (xs * (ar * xcs + ai * xsn)));
+            aim.add(hv * (xs * (ai * xcs - ar * xsn)));
+        } else {
+            const double r = exp(T.logabs[k] - la);
+            double sn, cs;
+            sincos(T.phase[k] - ph, &sn, &cs);
+            are.add(hv * (r * cs));
+            aim.add(hv * (r * sn));
+        }
+    };
+    for (uint32_t base = k0; base < k1; base += 64 * kScanAhead) {
+        Key y[kScanAhead];
+#pragma unroll
+        for (int q = 0; q < kScanAhead; q++) {
+            const uint32_t k = base + 64 * q + lane;
+            y[q] = load_key<W>(T.keys, k < k1 ? k : k1 - 1);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        uint64_t near[kScanAhead], any = 0;
+#pragma unroll
+        for (int q = 0; q < kScanAhead; q++) {
+            int c = __popcll(x.lo ^ y[q].lo);
+            if (W == 2) c += __popcll(x.hi ^ y[q].hi);
+            near[q] = __ballot(c <= 4 && base + 64 * q + lane < k1);
+            any |= near[q];
+        }
+        if (!any) continue;
+#pragma unroll
+        for (int q = 0; q < kScanAhead; q++) {
+            if (near[q] >> lane & 1) wl.queue[(qt + mbcnt(near[q])) & 255] = base + 64 * q + lane;
+            qt += __popcll(near[q]);
+            while (qt - qh >= 64) {
+                wave_sync();
+                process(wl.queue[(qh + lane) & 255]);
+                qh += 64;
+                wave_sync();
+            }
+        }
+    }
+    wave_sync();
+    if (lane < qt - qh) process(wl.queue[(qh + lane) & 255]);
+    sum[0] = are.s;
+    sum[1] = are.c;
+    sum[2] = aim.s;
+    sum[3] = aim.c;
+    wave_nsum(sum[0], sum[1]);
+    wave_nsum(sum[2], sum[3]);
+    wave_sync();
+    return true;
+}
+
+__device__ __forceinline__ void scan_store(const double (&sum)[4], int64_t smp, double *__restrict__ eloc) {
+    if (lane_id() == 0) {
+        eloc[2 * smp] = sum[0] + sum[1];
+        eloc[2 * smp + 1] = sum[2] + sum[3];
+    }
+}
+
+// kSplit: the block's waves share one sample, a run of the members each
+// (merged in order); else a sample per wave.
+template <int W, bool kSplit>
+__global__ void __launch_bounds__(64 * kScanWaves) k_eloc_scan(SysView S, TableView T, const uint64_t *__restrict__ keys,
+                                                              const double *__restrict__ logabs,
+                                                              const double *__restrict__ phase, int64_t n,
+                                                              double *__restrict__ eloc, int *status) {
+    __shared__ WaveLds wl[kScanWaves];
+    __shared__ double sums[kScanWaves][4];
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    double sum[4];
+    const uint32_t m = (uint32_t)T.n;
+    if (!kSplit) {
+        const int64_t smp = (int64_t)blockIdx.x * kScanWaves + wid;
+        if (smp < n && scan_sample<W>(S, T, wl[wid], smp, 0u, m, keys, logabs, phase, eloc, status, sum))
+            scan_store(sum, smp, eloc);
+        return;
+    }
+    const int64_t smp = blockIdx.x;
+    const uint32_t per = ((m + kScanWaves - 1) / kScanWaves + 63) & ~63u;
+    const uint32_t k0 = wid * per < m ? wid * per : m, k1 = k0 + per < m ? k0 + per : m;
+    // refused for every wave alike
+    if (!scan_sample<W>(S, T, wl[wid], smp, k0, k1, keys, logabs, phase, eloc, status, sum)) return;
+    if (lane_id() == 0)
+#pragma unroll
+        for (int q = 0; q < 4; q++) sums[wid][q] = sum[q];
+    __syncthreads();
+    if (wid > 0) return;
+#pragma unroll
+    for (int w = 1; w < kScanWaves; w++) {
+        nsum_merge(sum[0], sum[1], sums[w][0], sums[w][1]);
+        nsum_merge(sum[2], sum[3], sums[w][2], sums[w][3]);
+    }
+    scan_store(sum, smp, eloc);
+}
+
+// One tile (a system and a run of its samples) per block.
+template <int W>
+__global__ void __launch_bounds__(64 * kScanWaves) k_eloc_scan_batch(const SaBatchItem *__restrict__ items,
+                                                                    const SaTile *__restrict__ tiles) {
+    __shared__ WaveLds wl[kScanWaves];
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const SaTile tl = tiles[blockIdx.x];
+    const SaBatchItem &it = items[tl.item];
+    double sum[4];
+    for (int64_t smp = tl.begin + wid; smp < tl.begin + tl.count; smp += kScanWaves)
+        if (scan_sample<W>(it.S, it.T, wl[wid], smp, 0u, (uint32_t)it.T.n, it.keys, it.logabs, it.phase, it.eloc,
+                           it.status, sum))
+            scan_store(sum, smp, it.eloc);
+}
+
+// Enumerating costs the connections C of each sample, scanning the table's
+// members, at about twice the rate (K = 24, C = 16,471, 32,000 members and
+// samples: 937 against 850 us; at 65,536 1.94 against 3.4 ms).  `fixed`: members
+// scanned in the time that enumeration takes to stage its filter and to run its
+// second pass (K = 12, C = 1,425, 3,000 members and samples: 63 against 49 us).
+bool sa_scans(const SysView &S, int64_t table_n, int64_t n, int64_t fixed) {
+    return (double)n * (double)table_n <= (double)n * (double)S.C * 1.5 + (double)fixed;
+}
+
+void sa_launch_scan(int W, int cus, hipStream_t st, const SysView &S, const TableView &T, const uint64_t *keys,
+                    const double *logabs, const double *phase, int64_t n, double *eloc, int *status) {
+    // Few samples: the block's waves share one (K = 58, 1,501 members and samples:
+    // 90 against 129 us; with a wave of work for every slot it costs more, K = 24,
+    // 8,000: 149 against 132 us).
+    const bool split = n <= 8 * (int64_t)cus && T.n >= 256;
+    const dim3 g((unsigned)(split ? n : (n + kScanWaves - 1) / kScanWaves)), b(64 * kScanWaves);
+    if (W == 1) {
+        if (split) hipLaunchKernelGGL((k_eloc_scan<1, true>), g, b, 0, st, S, T, keys, logabs, phase, n, eloc, status);
+        else hipLaunchKernelGGL((k_eloc_scan<1, false>), g, b, 0, st, S, T, keys, logabs, phase, n, eloc, status);
+    } else {
+        if (split) hipLaunchKernelGGL((k_eloc_scan<2, true>), g, b, 0, st, S, T, keys, logabs, phase, n, eloc, status);
+        else hipLaunchKernelGGL((k_eloc_scan<2, false>), g, b, 0, st, S, T, keys, logabs, phase, n, eloc, status);
+    }
+}
+
+void sa_launch_scan_batch(int W, hipStream_t st, const SaBatchItem *items, const SaTile *tiles, int ntiles) {
+    const dim3 g((unsigned)ntiles), b(64 * kScanWaves);
+    if (W == 1) hipLaunchKernelGGL(k_eloc_scan_batch<1>, g, b, 0, st, items, tiles);
+    else hipLaunchKernelGGL(k_eloc_scan_batch<2>, g, b, 0, st, items, tiles);
+}
+
 // Canonical-order export of every connection (tests): one wave per sample,
 // lanes stride over the canonical index.
 __global__ void __launch_bounds__(256) k_connections(SysView S, const uint64_t *__restrict__ keys, int64_t n,
@@ -744,6 +1024,12 @@ nnqs_status nnqs_eloc_table(const nnqs_system *sys, nnqs_table *tab, const uint6
         lds = sa_lds_bytes(fl, tv.split_levels, W, waves);
     }
     if (lds > (size_t)sys->max_lds) return fail(NNQS_EINVAL, "LDS budget exceeded (%zu bytes)", lds);
+    if (sa_scans(sys->view, tv.n, n, kScanFixed)) {
+        sa_launch_scan(W, sys->cu_count, st, sys->view, tv, keys, logabs, phase, n, eloc, tab->status);
+        NNQS_HIP_CHECK(hipGetLastError());
+        if (energy) return enqueue_energy(tab, counts, eloc, n, energy, st);
+        return NNQS_OK;
+    }
     const unsigned grid = (unsigned)(sys->cu_count * tab->tune.blocks_per_cu);
     NNQS_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const dim3 g(grid), b(waves * 64);

@@ -1,0 +1,61 @@
+"""Sample-aware energies by scanning the table against the enumeration: the
+same table and samples in a call of few samples (scanned) and of many
+(enumerated), with members of other sectors among them, and samples that are
+not members or lie far below the largest amplitude.
+
+Both add the same FP64 terms with compensated sums in another order: 1e-12 of
+max(1, |E|).  Small tables on either side of 64 and 256 members against the
+oracle, as the other sample-aware tests."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from synth.gen import sector_size
+from tests.gpu_util import assert_eloc_close, dev, eloc_complex
+from tests.test_gpu_sample_aware import _eloc_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def nn():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2306_16705_amd as nn
+    return nn
+
+
+@pytest.mark.parametrize("K,nu,nd,n", [(12, 3, 3, 9000), (40, 2, 2, 16000)])
+def test_scan_equals_enumeration(nn, K, nu, nd, n):
+    print(f"[case] scan vs enumeration K={K} n={n}", flush=True)
+    d = synth.config_inputs(2, K=K, n_up=nu, n_dn=nd, n_unique=n)
+    keys, la, ph = d["keys"][:n].copy(), d["logabs"][:n].copy(), d["phase"][:n]
+    la[7::501] -= 650.0  # the exact ratio's samples
+    S = nn.System(d["N"], nu, nd, d["h"], d["g"], d["e_core"])
+    T = nn.Table(S, n + 4)
+    # members one spin flip away from a sample: other sectors, never connected
+    other = keys[:4].copy()
+    for r in range(4):
+        x = int(other[r, 0]) | int(other[r, 1]) << 64
+        up = next(p for p in range(0, 2 * K, 2) if x >> p & 1)
+        dn = next(p for p in range(1, 2 * K, 2) if not x >> p & 1)
+        x ^= 1 << up | 1 << dn
+        other[r] = np.uint64(x & (1 << 64) - 1), np.uint64(x >> 64)
+    tk = np.concatenate([keys[n // 10:], other])  # the first tenth of the samples are no members
+    T.build(dev(tk), dev(np.concatenate([la[n // 10:], la[:4]])), dev(np.concatenate([ph[n // 10:], ph[:4]])))
+    many, _ = nn.eloc_table(S, T, dev(keys), None, dev(la), dev(ph), with_energy=False)
+    many = eloc_complex(many)
+    for a, b in ((0, 1), (0, 65), (n // 10 - 9, n // 10 + 40), (n - 700, n)):
+        few, _ = nn.eloc_table(S, T, dev(keys[a:b]), None, dev(la[a:b]), dev(ph[a:b]), with_energy=False)
+        few = eloc_complex(few)
+        assert np.all(np.abs(few - many[a:b]) <= 1e-12 * np.maximum(1.0, np.abs(many[a:b]))), (a, b)
+
+
+@pytest.mark.parametrize("K,nu,nd", [(6, 2, 3), (33, 3, 2)])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 257])
+def test_small_tables_match_the_oracle(nn, K, nu, nd, n):
+    print(f"[case] scan K={K} n={n}", flush=True)
+    d = synth.config_inputs(2, K=K, n_up=nu, n_dn=nd, n_unique=min(n, sector_size(K, nu, nd)))
+    S, T, g, ora, absum, ci, en = _eloc_case(nn, d)
+    assert_eloc_close(g, ora, absum, label=f"K={K} n={n}")
