@@ -10,9 +10,10 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import synth
 from synth.gen import sector_size
-from tests.gpu_util import assert_eloc_close, dev, eloc_complex
+from tests.gpu_util import assert_eloc_close, dev, eloc_complex, keys_np
 from tests.test_gpu_sample_aware import _eloc_case
 
 pytestmark = pytest.mark.gpu
@@ -59,3 +60,24 @@ def test_small_tables_match_the_oracle(nn, K, nu, nd, n):
     d = synth.config_inputs(2, K=K, n_up=nu, n_dn=nd, n_unique=min(n, sector_size(K, nu, nd)))
     S, T, g, ora, absum, ci, en = _eloc_case(nn, d)
     assert_eloc_close(g, ora, absum, label=f"K={K} n={n}")
+
+
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 1000, 8191, 8192, 8193])
+def test_table_order_on_both_sorts(nn, n):
+    """Tables on either side of the largest that is sorted by counting, with a
+    key given twice from n = 64 on (the first given comes first)."""
+    print(f"[case] table order n={n}", flush=True)
+    d = synth.config_inputs(2, K=40, n_up=4, n_dn=3, n_unique=n)
+    keys, la, ph = d["keys"].copy(), d["logabs"], d["phase"]
+    if n >= 64:
+        keys[n - 1] = keys[3]
+    T = nn.Table(nn.System(d["N"], 4, 3, d["h"], d["g"], d["e_core"]), n)
+    T.build(dev(keys), dev(la), dev(ph))
+    k, l, p = T.export()
+    order = np.lexsort((np.arange(n), keys[:, 0], keys[:, 1]))
+    assert (keys_np(k) == keys[order]).all()
+    assert (l.cpu().numpy() == la[order]).all() and (p.cpu().numpy() == ph[order]).all()
+    if n < 64:
+        assert oracle.sort_table(keys, la, ph)[3] and T.status() == 0
+    else:
+        assert T.status() != 0
