@@ -83,7 +83,7 @@ static nnqs_status batch_plan(nnqs_batch *b) {
         d.phase = it.phase;
         d.eloc = it.eloc;
         d.status = it.table->status;
-        const bool scans = sa_scans(d.S, it.n, it.n, kScanFixed / 16);
+        const bool scans = sa_scans(d.S, it.n, it.n, 0);
         const int64_t per = scans ? 16 : b->tune.tile_samples;
         for (int64_t s0 = 0; s0 < it.n; s0 += per) {
             SaTile t;

@@ -770,13 +770,16 @@ __global__ void __launch_bounds__(64 * kScanWaves) k_eloc_scan_batch(const SaBat
             scan_store(sum, smp, it.eloc);
 }
 
-// Enumerating costs the connections C of each sample, scanning the table's
-// members, at about twice the rate (K = 24, C = 16,471, 32,000 members and
-// samples: 937 against 850 us; at 65,536 1.94 against 3.4 ms).  `fixed`: members
-// scanned in the time that enumeration takes to stage its filter and to run its
-// second pass (K = 12, C = 1,425, 3,000 members and samples: 63 against 49 us).
+// Enumerating costs the connections C of each sample and the time of some 5,000
+// more for its lists, search and queue; scanning the table's members costs about
+// two thirds as much each (members and samples, enumerated against scanned: K =
+// 12, C = 1,425, 6,000: 104 against 90 us, 12,000: 187 against 205; K = 16, C =
+// 4,236, 12,000: 195 against 217; K = 24, C = 16,471, 32,000: 937 against 850,
+// 65,536: 1.94 against 3.4 ms).  `fixed`: members scanned in the time that
+// enumeration takes to stage its filter and to run its second pass (K = 10, C =
+// 610, 3,000: 57 against 45 us).
 bool sa_scans(const SysView &S, int64_t table_n, int64_t n, int64_t fixed) {
-    return (double)n * (double)table_n <= (double)n * (double)S.C * 1.5 + (double)fixed;
+    return (double)n * (double)table_n <= (double)n * ((double)S.C * 1.5 + 5000.0) + (double)fixed;
 }
 
 void sa_launch_scan(int W, int cus, hipStream_t st, const SysView &S, const TableView &T, const uint64_t *keys,

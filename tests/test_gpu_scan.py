@@ -14,6 +14,7 @@ import oracle
 import synth
 from synth.gen import sector_size
 from tests.gpu_util import assert_eloc_close, dev, eloc_complex, keys_np
+from tests.test_gpu_batch import _items
 from tests.test_gpu_sample_aware import _eloc_case
 
 pytestmark = pytest.mark.gpu
@@ -27,14 +28,17 @@ def nn():
     return nn
 
 
-@pytest.mark.parametrize("K,nu,nd,n", [(12, 3, 3, 9000), (40, 2, 2, 16000)])
-def test_scan_equals_enumeration(nn, K, nu, nd, n):
-    print(f"[case] scan vs enumeration K={K} n={n}", flush=True)
+@pytest.mark.parametrize("tune", [{}, dict(search=2), dict(waves_per_block=16), dict(waves_per_block=8, search=2, filter_log2_bits=12,
+                                                                                splitter_levels=3)])
+@pytest.mark.parametrize("K,nu,nd,n", [(12, 3, 3, 16000), (40, 2, 2, 24000)])
+def test_scan_equals_enumeration(nn, K, nu, nd, n, tune):
+    print(f"[case] scan vs enumeration K={K} n={n} {tune}", flush=True)
     d = synth.config_inputs(2, K=K, n_up=nu, n_dn=nd, n_unique=n)
     keys, la, ph = d["keys"][:n].copy(), d["logabs"][:n].copy(), d["phase"][:n]
     la[7::501] -= 650.0  # the exact ratio's samples
     S = nn.System(d["N"], nu, nd, d["h"], d["g"], d["e_core"])
     T = nn.Table(S, n + 4)
+    T.set_tune(**tune)
     # members one spin flip away from a sample: other sectors, never connected
     other = keys[:4].copy()
     for r in range(4):
@@ -51,6 +55,26 @@ def test_scan_equals_enumeration(nn, K, nu, nd, n):
         few, _ = nn.eloc_table(S, T, dev(keys[a:b]), None, dev(la[a:b]), dev(ph[a:b]), with_energy=False)
         few = eloc_complex(few)
         assert np.all(np.abs(few - many[a:b]) <= 1e-12 * np.maximum(1.0, np.abs(many[a:b]))), (a, b)
+
+
+@pytest.mark.parametrize("search", [1, 2])
+def test_batch_of_scanned_and_enumerated_systems(nn, search):
+    print(f"[case] mixed batch search={search}", flush=True)
+    specs = [dict(K=12, n_up=3, n_dn=3, n_unique=16000), dict(K=24, n_up=6, n_dn=6, n_unique=500),
+             dict(K=40, n_up=2, n_dn=2, n_unique=24000)]
+    items = _items(nn, specs)
+    B = nn.Batch(items)
+    B.set_tune(search=search)
+    B.run()
+    for it in items:
+        whole = eloc_complex(it["eloc"])
+        for a in (0, 8000, 15900):
+            k, l, p = (it[key][a:a + 64].contiguous() for key in ("keys", "logabs", "phase"))
+            if len(k) == 0:
+                continue
+            few, _ = nn.eloc_table(it["system"], it["table"], k, None, l, p, with_energy=False)
+            want = whole[a:a + len(k)]
+            assert np.all(np.abs(eloc_complex(few) - want) <= 1e-12 * np.maximum(1.0, np.abs(want)))
 
 
 @pytest.mark.parametrize("K,nu,nd", [(6, 2, 3), (33, 3, 2)])
