@@ -22,13 +22,16 @@
 // Bound: FP64 MFMA (K = 60: 27.8 MFLOP per configuration, 64 of whose rows
 // are run for 60).  Against one kernel per product with the rows in memory
 // between them (about 11 KB of traffic per row and layer), one MI355X, whole
-// calls: log|psi| and phase of 1,001 configurations at K = 60 1,118 -> 706 us;
-// FP64 E_loc of 8 samples at K = 16 (25,544 x') 9,544 -> 4,337 us.  Matrix
+// calls: log|psi| and phase of 1,001 configurations at K = 60 1,118 -> 682 us;
+// FP64 E_loc of 8 samples at K = 16 (25,544 x') 9,544 -> 4,270 us (678 and 4,271
+// us with the products summed into the residual, twice the rounding error of
+// log|psi|).  Matrix
 // products alone (no softmax, GELU, LayerNorm or loads) take 70 % of the
 // present time: FP64 vector work adds to them (GELU 9 %, attention 16 % of
 // it), as does the latency of each step's barrier; eight or twelve waves in
 // lockstep per block were 8 and 19 % slower, three blocks per CU (168
-// registers, spilling) 2 % slower.
+// registers) 2 % slower.  At the 256 registers of two blocks some addresses
+// spill (204 bytes a lane, 244 in list mode).
 #include <cmath>
 
 #include "f64_kernels.hpp"
@@ -58,9 +61,12 @@ struct T64Args {
     double *cond_out;  // [n][4] (may be null)
 };
 
+constexpr int kParked = 14;  // of a lane's 16 residual values; all 16 would leave room for one block per CU
+
 struct T64Lds {
     double w[2][kStepDoubles];
     double kv[kW64][2][kKvTile];
+    double park[kW64][kParked][64];  // each lane's own: no wait but its own
     double lp[kW64];
     int64_t tile0[5], cnt[4];
     int cpt[4];
@@ -354,12 +360,26 @@ __device__ __forceinline__ void transformer_f64(const ModelView &M, const T64Arg
             uint32_t lv = lk;  // a fresh value per layer: the vectors' addresses are not kept in registers
             asm volatile("" : "+v"(lv));
             f64x4 xn[4];
+            // A product that goes into the residual is summed in h from zero while
+            // the residual waits, and added to it once with its bias: summed into
+            // the residual itself, every step would round at the residual's size.
+            double kept[16 - kParked];
+            auto park = [&] {
+#pragma unroll
+                for (int e = 0; e < 16; e++) {
+                    if (e < kParked) S.park[w][e][l] = h[e >> 2][e & 3];
+                    else kept[e - kParked] = h[e >> 2][e & 3];
+                    h[e >> 2][e & 3] = 0.0;
+                }
+            };
+            auto unpark = [&](const double *__restrict__ bias) {
+#pragma unroll
+                for (int e = 0; e < 16; e++)
+                    h[e >> 2][e & 3] = (e < kParked ? S.park[w][e][l] : kept[e - kParked]) + (bias[4 * e + lv] + h[e >> 2][e & 3]);
+            };
             if (on) {
                 layernorm64(h, Lw + LO.ln1_g, Lw + LO.ln1_b, lv, xn);
-#pragma unroll
-                for (int t = 0; t < 4; t++)
-#pragma unroll
-                    for (int i = 0; i < 4; i++) h[t][i] += (Lw + LO.bo)[16 * t + 4 * i + lv];
+                park();
             }
 #pragma unroll 1
             for (int hh = 0; hh < 4; hh++) {
@@ -431,11 +451,9 @@ __device__ __forceinline__ void transformer_f64(const ModelView &M, const T64Arg
                 }
             }
             if (on) {
+                unpark(Lw + LO.bo);
                 layernorm64(h, Lw + LO.ln2_g, Lw + LO.ln2_b, lv, xn);
-#pragma unroll
-                for (int t = 0; t < 4; t++)
-#pragma unroll
-                    for (int i = 0; i < 4; i++) h[t][i] += (Lw + LO.b2)[16 * t + 4 * i + lv];
+                park();
             }
 #pragma unroll 1
             for (int sp = 8; sp < steps; sp++) {
@@ -455,6 +473,7 @@ __device__ __forceinline__ void transformer_f64(const ModelView &M, const T64Arg
                     add_rows(wb, f64x4{g[0], g[1], g[2], g[3]}, l, h);
                 }
             }
+            if (on) unpark(Lw + LO.b2);
         }
         // final LayerNorm, head, mask (Eq. 12, read with the lower bound too)
         // and the log-probability of the actual token
