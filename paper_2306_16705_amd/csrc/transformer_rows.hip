@@ -9,9 +9,10 @@ namespace nnqs {
 // A wave takes up to 16 prefixes, one row each, in the layout of tf_tile with
 // prefixes in the place of a block's rows: every product of the layer serves
 // 16 prefixes.  Only attention differs: the keys and values are each prefix's
-// own, so the score product runs once per prefix on its keys with the queries
-// of the other prefixes cleared, which adds zeros to their columns, and so
-// does the value product.  The softmax runs once for all 16.  Values come as
+// own, so the score product runs once per prefix on its keys and only that
+// prefix's column is taken from it (an infinity or NaN among one prefix's keys
+// and values stays its own), and so does the value product.  The softmax runs
+// once for all 16.  Values come as
 // rows; a product with an identity makes the untransposed tile that tf_tile
 // holds.  Products, sums and their order per row are those of the whole
 // forward, so the conditionals are the same bits.
@@ -77,6 +78,10 @@ __device__ __forceinline__ void rows_tile(const Bf16View &M, const RowsArgs &A, 
 #pragma unroll
     for (int e = 0; e < 8; e++) ones[e] = (__bf16)1.0f;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+    auto keep = [](bool mine, const f32x4 &v, f32x4 &to) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) to[i] = mine ? v[i] : to[i];
+    };
 
     f32x4 h[4];
     {
@@ -151,13 +156,11 @@ __device__ __forceinline__ void rows_tile(const Bf16View &M, const RowsArgs &A, 
                 for (int p = 0; p < cnt; p++) {
                     Frag kf[QB + 1];
                     fetch(p, at, curK, kf);
-                    const uint32_t pm = c16 == p ? ~0u : 0u;
+                    const bool mine = c16 == p;
 #pragma unroll
-                    for (int hs = 0; hs < 2; hs++) {
-                        const Frag qp = half(qh[hs], pm);
+                    for (int hs = 0; hs < 2; hs++)
 #pragma unroll
-                        for (int kb = 0; kb <= QB; kb++) st[hs][kb] = mfma16(kf[kb], qp, st[hs][kb]);
-                    }
+                        for (int kb = 0; kb <= QB; kb++) keep(mine, mfma16(kf[kb], qh[hs], zero), st[hs][kb]);
                 }
                 Frag bp[2][2];
                 f32x4 den[2];
@@ -194,7 +197,7 @@ __device__ __forceinline__ void rows_tile(const Bf16View &M, const RowsArgs &A, 
                 for (int p = 0; p < cnt; p++) {
                     Frag vr[QB + 1];
                     fetch(p, at + 32, curV, vr);
-                    const uint32_t pm = c16 == p ? ~0u : 0u;
+                    const bool mine = c16 == p;
 #pragma unroll
                     for (int hs = 0; hs < 2; hs++) {
                         Quad2 vq[4];
@@ -203,9 +206,10 @@ __device__ __forceinline__ void rows_tile(const Bf16View &M, const RowsArgs &A, 
                             vq[kb] = Quad2{{0u, 0u}};
                             if (kb <= QB) vq[kb] = Act<false>::pack(mfma16(vr[kb <= QB ? kb : 0], sel[hs], zero));
                         }
+                        f32x4 o = zero;
 #pragma unroll
-                        for (int pp = 0; 2 * pp <= QB; pp++)
-                            ot[hs] = mfma16(join(vq[2 * pp], vq[2 * pp + 1]), half(bp[hs][pp], pm), ot[hs]);
+                        for (int pp = 0; 2 * pp <= QB; pp++) o = mfma16(join(vq[2 * pp], vq[2 * pp + 1]), bp[hs][pp], o);
+                        keep(mine, o, ot[hs]);
                     }
                 }
                 wave_sync();  // cur is read before the next pair rewrites it
