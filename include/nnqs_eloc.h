@@ -473,9 +473,11 @@ nnqs_status nnqs_screen_judge(nnqs_screen *screen, const uint64_t *xkeys, const 
 /* Timing of the library's own hot launches: with enable = 1 (which also
  * clears earlier records) every launch of k_transformer_bf16 (whole
  * sequences), k_transformer_bf16_list (prefix-reusing connections),
- * k_phase_bf16 and k_screen_infer is bracketed by HIP events recorded on the
- * stream it runs on; enable = 0 stops recording.  Not for use while a stream
- * is being captured into a graph. */
+ * k_transformer_rows (batch sampling), k_phase_bf16, k_screen_infer and the
+ * sample-aware k_eloc_sa / k_eloc_scan (and their batched forms, with _batch)
+ * is bracketed by HIP events recorded on the stream it runs on; enable = 0
+ * stops recording.  Not for use while a stream is being captured into a
+ * graph. */
 nnqs_status nnqs_timing_enable(int32_t enable);
 
 /* Waits for the recorded events and returns the summed duration (ms) and

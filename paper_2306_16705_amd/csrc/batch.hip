@@ -83,7 +83,7 @@ static nnqs_status batch_plan(nnqs_batch *b) {
         d.phase = it.phase;
         d.eloc = it.eloc;
         d.status = it.table->status;
-        const bool scans = sa_scans(d.S, it.n, it.n, 0);
+        const bool scans = sa_scans(d.S, it.n, it.n, b->cu_count, true);
         const int64_t per = scans ? 16 : b->tune.tile_samples;
         for (int64_t s0 = 0; s0 < it.n; s0 += per) {
             SaTile t;
@@ -126,10 +126,15 @@ static nnqs_status batch_step(nnqs_batch *b, hipStream_t st) {
         nnqs_status s = nnqs_table_build(it.table, it.keys, it.logabs, it.phase, it.n, 0, st);
         if (s != NNQS_OK) return s;
     }
-    if (b->nscan) sa_launch_scan_batch(b->W, st, b->d_items, b->d_tiles + b->ntiles, b->nscan);
-    if (b->ntiles)
+    if (b->nscan) {
+        TimedRegion tr("k_eloc_scan_batch", st);
+        sa_launch_scan_batch(b->W, st, b->d_items, b->d_tiles + b->ntiles, b->nscan);
+    }
+    if (b->ntiles) {
+        TimedRegion tr("k_eloc_sa_batch", st);
         sa_launch_batch(b->W, b->tune.search, b->grid, b->waves, b->lds, st, b->d_items, b->d_tiles, b->ntiles,
                         b->d_counter);
+    }
     NNQS_HIP_CHECK(hipGetLastError());
     for (const auto &it : b->items) {
         if (!it.energy) continue;

@@ -16,6 +16,7 @@
 //
 // A table that holds fewer members than x has connections is scanned instead
 // (scan_sample).
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -770,24 +771,39 @@ __global__ void __launch_bounds__(64 * kScanWaves) k_eloc_scan_batch(const SaBat
             scan_store(sum, smp, it.eloc);
 }
 
-// Enumerating costs the connections C of each sample and the time of some 5,000
-// more for its lists, search and queue; scanning the table's members costs about
-// two thirds as much each (members and samples, enumerated against scanned: K =
-// 12, C = 1,425, 6,000: 104 against 90 us, 12,000: 187 against 205; K = 16, C =
-// 4,236, 12,000: 195 against 217; K = 24, C = 16,471, 32,000: 937 against 850,
-// 65,536: 1.94 against 3.4 ms).  `fixed`: members scanned in the time that
-// enumeration takes to stage its filter and to run its second pass (K = 10, C =
-// 610, 3,000: 57 against 45 us).
-bool sa_scans(const SysView &S, int64_t table_n, int64_t n, int64_t fixed) {
-    return (double)n * (double)table_n <= (double)n * ((double)S.C * 1.5 + 5000.0) + (double)fixed;
+// The block's waves share a sample where there are few of them (K = 58, 1,501
+// members and samples: 90 against 129 us); with a wave of work for every slot
+// that costs more (K = 24, 8,000: 149 against 132 us).
+static bool scan_splits(int64_t table_n, int64_t n, int cus) { return n <= 8 * (int64_t)cus && table_n >= 256; }
+
+// Where the lines lie (us, enumerated against scanned, single calls).
+//  * Per sample, enumerating costs its C connections and some more for its lists,
+//    search and queue, scanning the table's members about half as much each.
+//    Members = samples: C = 703, 8,000: 102, 98; 12,000: 151, 185.  C = 1,425,
+//    10,000: 144, 138; 12,000: 160, 181.  C = 4,236, 10,000: 196, 150; 16,000:
+//    228, 278.  C = 7,876, 20,000: 414, 401; 24,000: 492, 516.  C = 16,471,
+//    32,000: 898, 810; 48,000: 1,413, 1,564.  (Enumeration goes in rounds of one
+//    sample per wave, 3,072 samples: between those it is up to 15 % off the line,
+//    C = 4,236, 12,000: 168, 193.)
+//  * Enumeration also takes 30 us to stage its filter and for its second pass,
+//    whatever n is (a single call pays it, a batch shares it), in which a scan
+//    that fills the chip reads 3e7 members and one of up to 2,048 samples, on
+//    its waits for memory, half of that.
+//  * Below a sample per CU neither gets shorter with fewer samples: n = 1, C =
+//    3,193, 100,000 members: 40, 38; a million: 173, 460.  C = 1,425, 256
+//    samples, 16,000: 53, 24; 100,000: 92, 71; C = 703, 2,048 samples, 12,000:
+//    58, 57; C = 1,425, 2,048 samples, 100,000: 97, 180.
+bool sa_scans(const SysView &S, int64_t table_n, int64_t n, int cus, bool batched) {
+    const double per_sample = 1.8 * (double)S.C + 5000.0;
+    const double start = batched ? 0.0
+                         : scan_splits(table_n, n, cus) ? 1.4e7 / (double)std::max<int64_t>(n, cus)
+                                                        : 3.0e7 / (double)std::max<int64_t>(n, 6000);
+    return (double)table_n <= per_sample + start;
 }
 
 void sa_launch_scan(int W, int cus, hipStream_t st, const SysView &S, const TableView &T, const uint64_t *keys,
                     const double *logabs, const double *phase, int64_t n, double *eloc, int *status) {
-    // Few samples: the block's waves share one (K = 58, 1,501 members and samples:
-    // 90 against 129 us; with a wave of work for every slot it costs more, K = 24,
-    // 8,000: 149 against 132 us).
-    const bool split = n <= 8 * (int64_t)cus && T.n >= 256;
+    const bool split = scan_splits(T.n, n, cus);
     const dim3 g((unsigned)(split ? n : (n + kScanWaves - 1) / kScanWaves)), b(64 * kScanWaves);
     if (W == 1) {
         if (split) hipLaunchKernelGGL((k_eloc_scan<1, true>), g, b, 0, st, S, T, keys, logabs, phase, n, eloc, status);
@@ -1027,8 +1043,11 @@ nnqs_status nnqs_eloc_table(const nnqs_system *sys, nnqs_table *tab, const uint6
         lds = sa_lds_bytes(fl, tv.split_levels, W, waves);
     }
     if (lds > (size_t)sys->max_lds) return fail(NNQS_EINVAL, "LDS budget exceeded (%zu bytes)", lds);
-    if (sa_scans(sys->view, tv.n, n, kScanFixed)) {
-        sa_launch_scan(W, sys->cu_count, st, sys->view, tv, keys, logabs, phase, n, eloc, tab->status);
+    if (sa_scans(sys->view, tv.n, n, sys->cu_count, false)) {
+        {
+            TimedRegion tr("k_eloc_scan", st);
+            sa_launch_scan(W, sys->cu_count, st, sys->view, tv, keys, logabs, phase, n, eloc, tab->status);
+        }
         NNQS_HIP_CHECK(hipGetLastError());
         if (energy) return enqueue_energy(tab, counts, eloc, n, energy, st);
         return NNQS_OK;
@@ -1039,21 +1058,24 @@ nnqs_status nnqs_eloc_table(const nnqs_system *sys, nnqs_table *tab, const uint6
     const bool wide = waves > kSaMaxThreads / 64;
     const SysView &SV = sys->view;
     int *stt = tab->status;
-    if (W == 1) {
-        if (search == 2) {
-            if (wide) sa_launch_one<1, 1, kSaWideThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
-            else sa_launch_one<1, 1, kSaMaxThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
+    {  // the exact pass follows
+        TimedRegion tr("k_eloc_sa", st);
+        if (W == 1) {
+            if (search == 2) {
+                if (wide) sa_launch_one<1, 1, kSaWideThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
+                else sa_launch_one<1, 1, kSaMaxThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
+            } else {
+                if (wide) sa_launch_one<1, 0, kSaWideThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
+                else sa_launch_one<1, 0, kSaMaxThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
+            }
         } else {
-            if (wide) sa_launch_one<1, 0, kSaWideThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
-            else sa_launch_one<1, 0, kSaMaxThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
-        }
-    } else {
-        if (search == 2) {
-            if (wide) sa_launch_one<2, 1, kSaWideThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
-            else sa_launch_one<2, 1, kSaMaxThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
-        } else {
-            if (wide) sa_launch_one<2, 0, kSaWideThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
-            else sa_launch_one<2, 0, kSaMaxThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
+            if (search == 2) {
+                if (wide) sa_launch_one<2, 1, kSaWideThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
+                else sa_launch_one<2, 1, kSaMaxThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
+            } else {
+                if (wide) sa_launch_one<2, 0, kSaWideThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
+                else sa_launch_one<2, 0, kSaMaxThreads>(g, b, lds, st, SV, tv, fl, keys, logabs, phase, n, eloc, stt);
+            }
         }
     }
     {  // exact pass (12-wave blocks, filter folded to fit)

@@ -337,8 +337,7 @@ void sa_launch_batch(int W, int search, unsigned grid, int waves, size_t lds, hi
 void sa_launch_reset(int *counter, hipStream_t st);
 // Whether a table of table_n members is read whole for each of n samples, and
 // the launches of that path.
-constexpr int64_t kScanFixed = 30'000'000;  // members read in the time the enumeration takes to start
-bool sa_scans(const SysView &S, int64_t table_n, int64_t n, int64_t fixed);
+bool sa_scans(const SysView &S, int64_t table_n, int64_t n, int cus, bool batched);
 void sa_launch_scan(int W, int cus, hipStream_t st, const SysView &S, const TableView &T, const uint64_t *keys,
                     const double *logabs, const double *phase, int64_t n, double *eloc, int *status);
 void sa_launch_scan_batch(int W, hipStream_t st, const SaBatchItem *items, const SaTile *tiles, int ntiles);

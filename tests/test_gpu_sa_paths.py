@@ -1,0 +1,63 @@
+"""Which of the two sample-aware paths a call takes, by the launches the
+library's timing records, and the result of either against the oracle.
+
+Few samples against a table that is large for their number of connections are
+enumerated: a scan is spread over no more than four waves per sample."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from tests.gpu_util import assert_eloc_close, dev, eloc_complex
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def nn():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2306_16705_amd as nn
+    return nn
+
+
+def launches(nn, names, call):
+    """What `call` returns, and the recorded launches of each name."""
+    nn.timing_enable(True)
+    try:
+        r = call()
+        torch.cuda.synchronize()
+        return r, [nn.timing_read(k)[1] for k in names]
+    finally:
+        nn.timing_enable(False)
+
+
+@pytest.fixture(scope="module")
+def sector():
+    """Every determinant of K = 12, 4 up and 4 down (C = 1,425), in random order."""
+    d = synth.config_inputs(1, K=12, n_up=4, n_dn=4)
+    p = np.random.default_rng([16705, 95]).permutation(len(d["keys"]))
+    for k in ("keys", "logabs", "phase", "counts"):
+        d[k] = np.ascontiguousarray(d[k][p])
+    return d
+
+
+@pytest.mark.parametrize("members,n,scans", [(1, 1, True), (40000, 1, True), (40000, 256, True), (100000, 1, False),
+                                             (240000, 3, False), (100000, 256, False), (12000, 2048, True),
+                                             (20000, 2048, False), (60000, 2048, False), (7000, 2049, True),
+                                             (7000, 20000, True), (14000, 2049, False), (20000, 14000, False)])
+def test_the_rule(nn, sector, members, n, scans):
+    print(f"[case] path of {n} samples, {members} members", flush=True)
+    d = sector
+    S = nn.System(d["N"], 4, 4, d["h"], d["g"], d["e_core"])
+    T = nn.Table(S, members)
+    keys, la, ph = d["keys"], d["logabs"], d["phase"]
+    T.build(dev(keys[:members]), dev(la[:members]), dev(ph[:members]))
+    (e, _), got = launches(nn, ("k_eloc_scan", "k_eloc_sa"), lambda: nn.eloc_table(
+        S, T, dev(keys[:n]), None, dev(la[:n]), dev(ph[:n]), with_energy=False))
+    assert got == ([1, 0] if scans else [0, 1])
+    chk = np.linspace(0, n - 1, min(n, 100)).astype(np.int64)
+    ora, absum = oracle.eloc_table(12, 4, 4, d["h"], d["g"], d["e_core"], keys[:members], la[:members], ph[:members],
+                                   keys[chk], la[chk], ph[chk], with_absum=True)
+    assert_eloc_close(eloc_complex(e)[chk], ora, absum, label=f"{n} of {members}")
