@@ -804,6 +804,16 @@ bool sa_scans(const SysView &S, int64_t table_n, int64_t n, int cus, bool batche
 void sa_launch_scan(int W, int cus, hipStream_t st, const SysView &S, const TableView &T, const uint64_t *keys,
                     const double *logabs, const double *phase, int64_t n, double *eloc, int *status) {
     const bool split = scan_splits(T.n, n, cus);
+    // A launch holds fewer than 2^32 threads: more samples take several (a loop
+    // over samples in the kernel costs it a wave per SIMD, 145 registers for 118).
+    constexpr int64_t kMaxSamples = (int64_t)1 << 24;
+    for (; n > kMaxSamples; n -= kMaxSamples) {
+        sa_launch_scan(W, cus, st, S, T, keys, logabs, phase, kMaxSamples, eloc, status);
+        keys += 2 * kMaxSamples;
+        logabs += kMaxSamples;
+        phase += kMaxSamples;
+        eloc += 2 * kMaxSamples;
+    }
     const dim3 g((unsigned)(split ? n : (n + kScanWaves - 1) / kScanWaves)), b(64 * kScanWaves);
     if (W == 1) {
         if (split) hipLaunchKernelGGL((k_eloc_scan<1, true>), g, b, 0, st, S, T, keys, logabs, phase, n, eloc, status);
