@@ -289,13 +289,13 @@ __global__ void __launch_bounds__(256) k_screen_hidden(const T *__restrict__ A, 
 }
 
 // y[k] = b3 + sum_c z2[k][c] w3[c] in ascending c; with `target`, gy[k] = 2
-// (y_k - target_k) / n and d2[k][c] = gy[k] w3[c] GELU'(a2[k][c]).  Sixteen
+// (y_k - target_k) / total and d2[k][c] = gy[k] w3[c] GELU'(a2[k][c]).  Sixteen
 // examples per block: their rows go through LDS, where 16 lanes follow one
 // chain each (the chain bounds it: 57 us when every lane also made its 256
 // GELUs in the chain, now 9 us).
 template <typename T>
 __global__ void __launch_bounds__(256) k_screen_out(const T *__restrict__ a2, const T *__restrict__ z2,
-                                                    const T *__restrict__ w, int N, int H, int64_t n,
+                                                    const T *__restrict__ w, int N, int H, int64_t n, int64_t total,
                                                     const double *__restrict__ target, T *__restrict__ y,
                                                     double *__restrict__ pred, T *__restrict__ gy,
                                                     T *__restrict__ d2) {
@@ -333,7 +333,7 @@ __global__ void __launch_bounds__(256) k_screen_out(const T *__restrict__ a2, co
         y[k0 + t] = acc;
         if (pred) pred[k0 + t] = (double)acc;
         if (target) {
-            const T g = (T)(2.0 * ((double)acc - target[k0 + t]) / (double)n);
+            const T g = (T)(2.0 * ((double)acc - target[k0 + t]) / (double)total);
             gy[k0 + t] = g;
             gs[t] = g;
         }
@@ -965,11 +965,21 @@ static nnqs_status screen_fwd_bwd(nnqs_screen *s, const uint64_t *keys, const ui
         w = wc;
     }
     const unsigned rt = gridfor(n, 32), ct = gridfor(H, 64);
-    hipLaunchKernelGGL(k_screen_layer1<T>, dim3(gridfor(n, 4)), dim3(256), 0, st, N, H, w, keys, exc, n, a1, z1);
+    // a launch holds fewer than 2^32 threads, and these two take 64 and 16 per example
+    constexpr int64_t kMaxRows = (int64_t)1 << 24;
+    for (int64_t k0 = 0; k0 < n; k0 += kMaxRows) {
+        const int64_t m = std::min(kMaxRows, n - k0);
+        hipLaunchKernelGGL(k_screen_layer1<T>, dim3(gridfor(m, 4)), dim3(256), 0, st, N, H, w, keys + 2 * k0, exc + 4 * k0,
+                           m, a1 ? a1 + k0 * H : nullptr, z1 + k0 * H);
+    }
     hipLaunchKernelGGL((k_screen_hidden<T, false>), dim3(rt, ct), dim3(256), 0, st, (const T *)z1, w + o.W2, w + o.b2,
                        (const T *)nullptr, n, H, a2, z2, (const T *)nullptr, (const T *)nullptr, (double *)nullptr);
-    hipLaunchKernelGGL(k_screen_out<T>, dim3(gridfor(n, 16)), dim3(256), 0, st, (const T *)a2, (const T *)z2, w, N, H, n,
-                       grad ? target : nullptr, y, pred, gy, d2);
+    for (int64_t k0 = 0; k0 < n; k0 += kMaxRows) {
+        const int64_t m = std::min(kMaxRows, n - k0);
+        hipLaunchKernelGGL(k_screen_out<T>, dim3(gridfor(m, 16)), dim3(256), 0, st, (const T *)(a2 ? a2 + k0 * H : nullptr),
+                           (const T *)(z2 + k0 * H), w, N, H, m, n, grad ? target + k0 : nullptr, y + k0,
+                           pred ? pred + k0 : nullptr, gy + k0, d2 ? d2 + k0 * H : nullptr);
+    }
     if (grad) {
         hipLaunchKernelGGL((k_screen_hidden<T, true>), dim3(rt + 16, ct), dim3(256), 0, st, (const T *)d2, w + o.W2,
                            (const T *)nullptr, (const T *)a1, n, H, (T *)nullptr, d1, (const T *)z2, (const T *)gy, w3p);

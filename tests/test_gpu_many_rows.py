@@ -35,3 +35,14 @@ def test_samples_of_a_scanned_table(nn):
     assert torch.equal(e[:36], few)  # fewer than 256 members: never split
     assert bool((e.view(-1, 36, 2) == few).all())
 
+
+def test_examples_of_a_screen(nn):
+    print("[case] screen of 2^26 + 32 examples", flush=True)
+    d = synth.config_inputs(1)
+    keys = dev(d["keys"])
+    exc = torch.randint(0, 9, (36, 4), generator=torch.Generator().manual_seed(3)).to(torch.uint8).cuda()
+    scr = nn.Screen(8, 1, np.random.default_rng([16705, 96]).normal(0, 0.3, 5 * 8 + 5))
+    few = scr.forward(keys, exc, nn.NNQS_FP64)
+    y = scr.forward(_repeat(keys), _repeat(exc), nn.NNQS_FP64)
+    assert torch.equal(y[:36], few)
+    assert bool((y.view(-1, 36) == few).all())
