@@ -497,18 +497,26 @@ typedef struct {
     int32_t tile_samples;      /* batched launch: samples per work tile, 1..65536 */
 } nnqs_tune;
 
-/* Sets the launch parameters used by later nnqs_eloc_table calls on `tab`.
- * NULL restores the defaults.  Errors: EINVAL (out of range). */
+/* Sets the launch parameters used by later nnqs_eloc_table calls on `tab`
+ * that enumerate the connections of each sample.  A table that is small for
+ * the number of connections is read whole for each sample instead,
+ * whatever the parameters (the choice depends on the table's size, the number
+ * of connections and the number of samples of the call).  The two, and
+ * calls of few and many samples on the second, add the same terms in another
+ * order: a sample's E_loc may differ in its last bits between calls of
+ * different sizes.  NULL restores the defaults.  Errors: EINVAL (out of range). */
 nnqs_status nnqs_table_set_tune(nnqs_table *tab, const nnqs_tune *tune);
 
 /* Reads back the parameters in use. */
 nnqs_status nnqs_table_get_tune(const nnqs_table *tab, nnqs_tune *tune);
 
 /* Autotuner of nnqs_eloc_table: times every candidate schedule (waves per
- * block {8, 12, 16} x splitter levels {8, 10, 12} x search {1, 2}) on the samples themselves (the table is
- * rebuilt from keys / logabs / phase for each), best of `reps` calls after
- * one warm-up call, and leaves `tab` built with the fastest, which it
- * returns (best, best_ms may be NULL).  eloc [n][2] is scratch.  Results do
+ * block {8, 12, 16} x splitter levels {8, 10, 12} x search {1, 2}) on the
+ * samples themselves (the table is rebuilt from keys / logabs / phase for
+ * each), best of `reps` calls after one warm-up call, and leaves `tab` built
+ * with the fastest, which it returns (best, best_ms may be NULL).  A table of
+ * n members that is read whole for its n samples keeps its schedule, which is
+ * returned with the call's time.  eloc [n][2] is scratch.  Results do
  * not depend on the schedule beyond rounding order.  Synchronises `stream`.
  * Errors: EINVAL, EHIP and those of the build and evaluation. */
 nnqs_status nnqs_table_autotune(const nnqs_system *sys, nnqs_table *tab, const uint64_t *keys, const double *logabs,
@@ -623,7 +631,8 @@ nnqs_status nnqs_batch_get_tune(const nnqs_batch *batch, nnqs_tune *tune);
 /* Autotuner: times every candidate schedule (waves per block {8, 12} x
  * splitter levels {8, 10, 12} x search {1, 2} x tile samples {64, 256, 1024})
  * on the batch itself, best of `reps` steps after one warm-up step each,
- * keeps the fastest and returns it (best, best_ms may be NULL).  Runs many
+ * keeps the fastest and returns it (best, best_ms may be NULL); the schedule
+ * in use where every system's table is read whole.  Runs many
  * steps on `stream` and synchronises it; drops a captured graph. */
 nnqs_status nnqs_batch_autotune(nnqs_batch *batch, int32_t reps, nnqs_tune *best, double *best_ms, void *stream);
 

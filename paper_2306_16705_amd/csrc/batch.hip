@@ -260,7 +260,8 @@ nnqs_status nnqs_batch_get_tune(const nnqs_batch *b, nnqs_tune *tune) {
 // Times every candidate schedule on the batch itself (one untimed warm-up
 // step, then the best of `reps` timed steps each) and keeps the fastest.
 // Candidates: waves per block {8, 12} x splitter levels {8, 10, 12} x search
-// variant {1, 2} x tile size {64, 256, 1024}.  Results are identical for
+// variant {1, 2} x tile size {64, 256, 1024}; where every system is scanned,
+// which no schedule changes, only the one in use.  Results are identical for
 // every candidate (one wave per sample, fixed order), so only time decides.
 nnqs_status nnqs_batch_autotune(nnqs_batch *b, int32_t reps, nnqs_tune *best_out, double *best_ms, void *stream) {
     clear_error();
@@ -274,38 +275,44 @@ nnqs_status nnqs_batch_autotune(nnqs_batch *b, int32_t reps, nnqs_tune *best_out
     nnqs_tune best = start;
     float best_t = 1e30f;
     nnqs_status s = NNQS_OK;
-    for (int waves : {8, 12})
-        for (int sl : {8, 10, 12})
-            for (int search : {1, 2})
-                for (int tile : {64, 256, 1024}) {
-                    nnqs_tune c = start;
-                    c.waves_per_block = waves;
-                    c.splitter_levels = sl;
-                    c.search = search;
-                    c.tile_samples = tile;
-                    b->tune = c;
-                    s = batch_plan(b);
-                    if (s != NNQS_OK) continue;  // e.g. does not fit the LDS: skip the candidate
-                    s = batch_step(b, st);
-                    if (s != NNQS_OK) goto done;
-                    float tmin = 1e30f;
-                    for (int r = 0; r < reps; r++) {
-                        if (hipEventRecord(e0, st) != hipSuccess) { s = fail(NNQS_EHIP, "event record failed"); goto done; }
-                        s = batch_step(b, st);
-                        if (s != NNQS_OK) goto done;
-                        if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
-                            s = fail(NNQS_EHIP, "event timing failed");
-                            goto done;
-                        }
-                        float ms = 0.f;
-                        hipEventElapsedTime(&ms, e0, e1);
-                        tmin = std::min(tmin, ms);
+    std::vector<nnqs_tune> candidates;
+    if (b->ntiles == 0) candidates.push_back(start);
+    else
+        for (int waves : {8, 12})
+            for (int sl : {8, 10, 12})
+                for (int search : {1, 2})
+                    for (int tile : {64, 256, 1024}) {
+                        nnqs_tune c = start;
+                        c.waves_per_block = waves;
+                        c.splitter_levels = sl;
+                        c.search = search;
+                        c.tile_samples = tile;
+                        candidates.push_back(c);
                     }
-                    if (tmin < best_t) {
-                        best_t = tmin;
-                        best = c;
-                    }
-                }
+    for (const nnqs_tune &c : candidates) {
+        b->tune = c;
+        s = batch_plan(b);
+        if (s != NNQS_OK) continue;  // e.g. does not fit the LDS: skip the candidate
+        s = batch_step(b, st);
+        if (s != NNQS_OK) goto done;
+        float tmin = 1e30f;
+        for (int r = 0; r < reps; r++) {
+            if (hipEventRecord(e0, st) != hipSuccess) { s = fail(NNQS_EHIP, "event record failed"); goto done; }
+            s = batch_step(b, st);
+            if (s != NNQS_OK) goto done;
+            if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
+                s = fail(NNQS_EHIP, "event timing failed");
+                goto done;
+            }
+            float ms = 0.f;
+            hipEventElapsedTime(&ms, e0, e1);
+            tmin = std::min(tmin, ms);
+        }
+        if (tmin < best_t) {
+            best_t = tmin;
+            best = c;
+        }
+    }
     s = NNQS_OK;
 done:
     hipEventDestroy(e0);

@@ -1114,7 +1114,8 @@ nnqs_status nnqs_eloc_table(const nnqs_system *sys, nnqs_table *tab, const uint6
 // Autotuner of the single-system path: for every candidate schedule the
 // table is rebuilt from the samples, one untimed call warms up, and the best
 // of `reps` timed calls counts.  Candidates: waves per block {8, 12, 16} x
-// splitter levels {8, 10, 12} x search {1, 2}.
+// splitter levels {8, 10, 12} x search {1, 2}; for a table that is scanned,
+// which no schedule changes, only the one it has.
 nnqs_status nnqs_table_autotune(const nnqs_system *sys, nnqs_table *tab, const uint64_t *keys, const double *logabs,
                                 const double *phase, int64_t n, double *eloc, int32_t reps, nnqs_tune *best_out,
                                 double *best_ms, void *stream) {
@@ -1130,40 +1131,46 @@ nnqs_status nnqs_table_autotune(const nnqs_system *sys, nnqs_table *tab, const u
     nnqs_tune best = start;
     float best_t = 1e30f;
     nnqs_status s = NNQS_OK;
-    for (int waves : {8, 12, 16})
-        for (int sl : {8, 10, 12})
-            for (int search : {1, 2}) {
-                nnqs_tune c = start;
-                c.waves_per_block = waves;
-                c.splitter_levels = sl;
-                c.search = search;
-                tab->tune = c;
-                s = nnqs_table_build(tab, keys, logabs, phase, n, 0, stream);
-                if (s != NNQS_OK) goto done;
-                s = nnqs_eloc_table(sys, tab, keys, nullptr, logabs, phase, n, eloc, nullptr, 0, stream);
-                if (s == NNQS_EINVAL) continue;  // does not fit: skip the candidate
-                if (s != NNQS_OK) goto done;
-                float tmin = 1e30f;
-                for (int r = 0; r < reps; r++) {
-                    if (hipEventRecord(e0, st) != hipSuccess) {
-                        s = fail(NNQS_EHIP, "event record failed");
-                        goto done;
-                    }
-                    s = nnqs_eloc_table(sys, tab, keys, nullptr, logabs, phase, n, eloc, nullptr, 0, stream);
-                    if (s != NNQS_OK) goto done;
-                    if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
-                        s = fail(NNQS_EHIP, "event timing failed");
-                        goto done;
-                    }
-                    float ms = 0.f;
-                    hipEventElapsedTime(&ms, e0, e1);
-                    tmin = ms < tmin ? ms : tmin;
+    std::vector<nnqs_tune> candidates;
+    if (sa_scans(sys->view, n, n, sys->cu_count, false)) candidates.push_back(start);
+    else
+        for (int waves : {8, 12, 16})
+            for (int sl : {8, 10, 12})
+                for (int search : {1, 2}) {
+                    nnqs_tune c = start;
+                    c.waves_per_block = waves;
+                    c.splitter_levels = sl;
+                    c.search = search;
+                    candidates.push_back(c);
                 }
-                if (tmin < best_t) {
-                    best_t = tmin;
-                    best = c;
-                }
+    for (const nnqs_tune &c : candidates) {
+        tab->tune = c;
+        s = nnqs_table_build(tab, keys, logabs, phase, n, 0, stream);
+        if (s != NNQS_OK) goto done;
+        s = nnqs_eloc_table(sys, tab, keys, nullptr, logabs, phase, n, eloc, nullptr, 0, stream);
+        if (s == NNQS_EINVAL) continue;  // does not fit: skip the candidate
+        if (s != NNQS_OK) goto done;
+        float tmin = 1e30f;
+        for (int r = 0; r < reps; r++) {
+            if (hipEventRecord(e0, st) != hipSuccess) {
+                s = fail(NNQS_EHIP, "event record failed");
+                goto done;
             }
+            s = nnqs_eloc_table(sys, tab, keys, nullptr, logabs, phase, n, eloc, nullptr, 0, stream);
+            if (s != NNQS_OK) goto done;
+            if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
+                s = fail(NNQS_EHIP, "event timing failed");
+                goto done;
+            }
+            float ms = 0.f;
+            hipEventElapsedTime(&ms, e0, e1);
+            tmin = ms < tmin ? ms : tmin;
+        }
+        if (tmin < best_t) {
+            best_t = tmin;
+            best = c;
+        }
+    }
     s = NNQS_OK;
 done:
     hipEventDestroy(e0);

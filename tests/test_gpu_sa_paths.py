@@ -61,3 +61,26 @@ def test_the_rule(nn, sector, members, n, scans):
     ora, absum = oracle.eloc_table(12, 4, 4, d["h"], d["g"], d["e_core"], keys[:members], la[:members], ph[:members],
                                    keys[chk], la[chk], ph[chk], with_absum=True)
     assert_eloc_close(eloc_complex(e)[chk], ora, absum, label=f"{n} of {members}")
+
+
+def test_autotuners_keep_a_schedule_that_changes_nothing(nn):
+    """Scanned tables: timing schedules would pick one by chance."""
+    d = synth.config_inputs(2, K=24, n_up=6, n_dn=6, n_unique=3000)
+    print("[case] autotuners on scanned tables", flush=True)
+    S = nn.System(d["N"], 6, 6, d["h"], d["g"], d["e_core"])
+    keys, la, ph = dev(d["keys"]), dev(d["logabs"]), dev(d["phase"])
+    T = nn.Table(S, 3000)
+    T.set_tune(waves_per_block=5, splitter_levels=9, search=2, filter_log2_bits=15)
+    before = T.get_tune()
+    (tune, ms), got = launches(nn, ("k_eloc_scan", "k_eloc_sa"), lambda: T.autotune(keys, la, ph, reps=2))
+    assert tune == before and T.get_tune() == before and 0.0 < ms < 1e3
+    assert got == [3, 0]
+    item = dict(system=S, table=T, keys=keys, logabs=la, phase=ph, counts=dev(d["counts"], torch.int32),
+                eloc=torch.empty((3000, 2), dtype=torch.float64, device="cuda"),
+                energy=torch.empty(4, dtype=torch.float64, device="cuda"))
+    B = nn.Batch([item])
+    B.set_tune(waves_per_block=6, splitter_levels=7, tile_samples=33)
+    before = B.get_tune()
+    (tune, ms), got = launches(nn, ("k_eloc_scan_batch", "k_eloc_sa_batch"), lambda: B.autotune(reps=2))
+    assert tune == before and B.get_tune() == before and 0.0 < ms < 1e3
+    assert got == [3, 0]
