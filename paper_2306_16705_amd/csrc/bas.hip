@@ -14,6 +14,7 @@
 // order, children are kept in (parent, token) order, so the result depends
 // only on the seed and the conditionals.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 
 #include "transformer.hpp"
@@ -248,17 +249,23 @@ __global__ void k_bas_init(BasLevel P, uint64_t total) {
 
 }  // namespace nnqs
 
-// Workspace of a sampling call: two levels of up to `cap` prefixes, and for the
-// BF16 network every position's rows, grown to the number of prefixes seen.
-// A call takes the model's workspace, or makes one where another call has it,
-// and leaves it with the model if it holds at most kBasKeep bytes.
+// Workspace of a sampling call: two levels of prefixes, scratch of one level,
+// and for the BF16 network each level's paths and every position's rows, all
+// grown to the number of prefixes seen.  A call takes the model's workspace, or
+// makes one where another call has it, and leaves it with the model as long as
+// all models together hold at most kBasKeep bytes.
 struct BasWork {
-    size_t cap = 0, row_cap[64] = {}, bytes = 0;
-    bool paths = false;
+    size_t level_cap[2] = {}, path_cap[2] = {}, scratch_cap = 0, row_bytes[64] = {};
     void *level[2] = {}, *path[2] = {};
     double *cond = nullptr, *la = nullptr;
     int64_t *blk = nullptr, *total = nullptr;  // total: host memory
     void *rows[64] = {};
+    size_t bytes() const {
+        size_t b = 40 * scratch_cap;
+        for (int i = 0; i < 2; i++) b += 72 * level_cap[i] + 256 * path_cap[i];
+        for (size_t r : row_bytes) b += r;
+        return b;
+    }
     ~BasWork() {
         for (int i = 0; i < 2; i++) {
             (void)hipFree(level[i]);
@@ -275,91 +282,119 @@ struct BasWork {
 namespace nnqs {
 
 constexpr size_t kBasKeep = (size_t)4 << 30;
+static std::atomic<size_t> g_bas_kept{0};  // held by models between their calls
 
-void bas_model_free(nnqs_model *m) { delete m->bas_work.exchange(nullptr); }
+// The model's idle workspace, which its next owner takes off the sum.
+static BasWork *bas_take(nnqs_model *m) {
+    BasWork *w = m->bas_work.exchange(nullptr);
+    if (w) g_bas_kept -= w->bytes();
+    return w;
+}
+
+void bas_model_free(nnqs_model *m) { delete bas_take(m); }
 
 // Holds a workspace for one call; the stream is idle when it goes back.
 struct BasHold {
     nnqs_model *m;
     hipStream_t st;
     BasWork *w;
-    BasHold(nnqs_model *model, hipStream_t stream) : m(model), st(stream), w(model->bas_work.exchange(nullptr)) {
+    bool drop = false;  // give its memory back
+    BasHold(nnqs_model *model, hipStream_t stream) : m(model), st(stream), w(bas_take(model)) {
         if (!w) w = new BasWork();
     }
     ~BasHold() {
         (void)hipStreamSynchronize(st);
-        BasWork *none = nullptr;
-        if (w->bytes > kBasKeep || !m->bas_work.compare_exchange_strong(none, w)) delete w;
+        const size_t b = w->bytes();
+        size_t kept = g_bas_kept.load();
+        while (!drop && kept + b <= kBasKeep)
+            if (g_bas_kept.compare_exchange_weak(kept, kept + b)) {
+                BasWork *none = nullptr;
+                if (m->bas_work.compare_exchange_strong(none, w)) return;
+                g_bas_kept -= b;  // another call has left one
+                break;
+            }
+        delete w;
     }
 };
 
-static bool bas_grow(BasWork &W, size_t cap, bool paths) {
-    if (W.cap >= cap && (W.paths || !paths)) return true;
-    for (int i = 0; i < 2; i++) {
-        (void)hipFree(W.level[i]);
-        (void)hipFree(W.path[i]);
-        W.level[i] = W.path[i] = nullptr;
+static bool bas_alloc(void **p, size_t bytes) {
+    (void)hipFree(*p);
+    *p = nullptr;
+    if (hipMalloc(p, bytes) == hipSuccess) return true;
+    (void)hipGetLastError();
+    *p = nullptr;
+    return false;
+}
+
+// Entries to allocate for `need` of at most `most`: twice as many, so that a
+// call grows its arrays a few times only.
+static size_t bas_want(size_t need, size_t most) { return std::min(std::max(2 * need, (size_t)1 << 16), most); }
+
+// Room for n prefixes in level i, and for the scratch of a level of n; what was
+// in them is not kept.
+static bool bas_room(BasWork &W, int i, size_t n, size_t most) {
+    if (W.level_cap[i] >= n) return true;
+    const size_t cap = bas_want(n, most);
+    W.level_cap[i] = 0;
+    if (!bas_alloc(&W.level[i], cap * 72)) return false;
+    W.level_cap[i] = cap;
+    return true;
+}
+
+static bool bas_scratch(BasWork &W, size_t n, size_t most) {
+    if (!W.total && hipHostMalloc(reinterpret_cast<void **>(&W.total), 8) != hipSuccess) {
+        (void)hipGetLastError();
+        W.total = nullptr;
+        return false;
     }
-    (void)hipFree(W.cond);
-    (void)hipFree(W.la);
-    (void)hipFree(W.blk);
-    W.cond = W.la = nullptr;
-    W.blk = nullptr;
-    cap = std::max(cap, W.cap);
-    paths = paths || W.paths;
-    W.cap = 0;
-    W.paths = false;
-    bool ok = W.total || hipHostMalloc(reinterpret_cast<void **>(&W.total), 8) == hipSuccess;
-    for (int i = 0; i < 2; i++) ok = ok && hipMalloc(&W.level[i], cap * 72) == hipSuccess;
-    ok = ok && hipMalloc(&W.cond, cap * 32) == hipSuccess && hipMalloc(&W.la, cap * 8) == hipSuccess &&
-         hipMalloc(&W.blk, (cap / kBasBlock + 1) * 16) == hipSuccess;
-    if (!ok) return false;
-    if (paths) {
-        for (int i = 0; i < 2; i++) paths = paths && hipMalloc(&W.path[i], cap * 256) == hipSuccess;
-        if (!paths) {  // sampling goes on without cached rows
-            (void)hipGetLastError();
-            for (int i = 0; i < 2; i++) {
-                (void)hipFree(W.path[i]);
-                W.path[i] = nullptr;
-            }
-        }
-    }
-    W.cap = cap;
-    W.paths = paths;
-    W.bytes = cap * (2 * 72 + 32 + 8 + (paths ? 512 : 0));
-    for (size_t r : W.row_cap) W.bytes += r;
+    if (W.scratch_cap >= n) return true;
+    const size_t cap = bas_want(n, most);
+    W.scratch_cap = 0;
+    if (!bas_alloc(reinterpret_cast<void **>(&W.cond), cap * 32) || !bas_alloc(reinterpret_cast<void **>(&W.la), cap * 8) ||
+        !bas_alloc(reinterpret_cast<void **>(&W.blk), (cap / kBasBlock + 1) * 16))
+        return false;
+    W.scratch_cap = cap;
+    return true;
+}
+
+// Memory for `bytes` more, a quarter of what is free at a time at most.
+static bool bas_spare(size_t bytes) {
+    size_t free_b = 0, all_b = 0;
+    return hipMemGetInfo(&free_b, &all_b) == hipSuccess && bytes <= free_b / 4;
+}
+
+static bool bas_paths(BasWork &W, int i, size_t n) {
+    if (W.path_cap[i] >= n) return true;
+    const size_t cap = W.level_cap[i];
+    if (!bas_spare(cap * 256)) return false;
+    W.path_cap[i] = 0;
+    if (!bas_alloc(&W.path[i], cap * 256)) return false;
+    W.path_cap[i] = cap;
     return true;
 }
 
 static BasLevel bas_level(const BasWork &W, int i, bool paths) {
     BasLevel v{};
+    const size_t cap = W.level_cap[i];
     uint8_t *p = static_cast<uint8_t *>(W.level[i]);
     v.keys = reinterpret_cast<uint64_t *>(p);
-    v.cnt = reinterpret_cast<uint64_t *>(p + W.cap * 16);
-    v.offs = reinterpret_cast<uint64_t *>(p + W.cap * 24);
-    v.lp = reinterpret_cast<double *>(p + W.cap * 32);
-    v.child = reinterpret_cast<unsigned long long *>(p + W.cap * 40);
+    v.cnt = reinterpret_cast<uint64_t *>(p + cap * 16);
+    v.offs = reinterpret_cast<uint64_t *>(p + cap * 24);
+    v.lp = reinterpret_cast<double *>(p + cap * 32);
+    v.child = reinterpret_cast<unsigned long long *>(p + cap * 40);
     v.path = paths ? static_cast<int32_t *>(W.path[i]) : nullptr;
     return v;
 }
 
-// Room for the rows of n prefixes at position s, with a quarter to spare and
-// at most a quarter of the free memory at a time; false: not to be had.
+// Room for `need` bytes of rows at position s, with a quarter to spare; false:
+// not to be had.
 static bool bas_rows(BasWork &W, int s, size_t need, size_t most) {
-    if (W.row_cap[s] >= need) return true;
+    if (W.row_bytes[s] >= need) return true;
     const size_t want = std::min(need + need / 4, most);
-    size_t free_b = 0, all_b = 0;
-    if (hipMemGetInfo(&free_b, &all_b) != hipSuccess || want > free_b / 4) return false;
-    (void)hipFree(W.rows[s]);
-    W.bytes -= W.row_cap[s];
-    W.rows[s] = nullptr;
-    W.row_cap[s] = 0;
-    if (hipMalloc(&W.rows[s], want) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    W.row_cap[s] = want;
-    W.bytes += want;
+    if (!bas_spare(want)) return false;
+    W.row_bytes[s] = 0;
+    if (!bas_alloc(&W.rows[s], want)) return false;
+    W.row_bytes[s] = want;
     return true;
 }
 
@@ -385,15 +420,24 @@ extern "C" nnqs_status nnqs_bas(nnqs_model *model, int32_t precision, uint64_t s
     const size_t cap = (size_t)std::min<uint64_t>((uint64_t)capacity, n_samples);
     BasHold hold(model, st);
     BasWork &W = *hold.w;
-    if (!bas_grow(W, cap, bf16)) return fail(NNQS_ENOMEM, "sampling scratch for %lld prefixes", (long long)cap);
-    bool cached = bf16 && W.paths;
+    const auto no_memory = [&](int64_t prefixes) {
+        hold.drop = true;
+        return fail(NNQS_ENOMEM, "sampling scratch for %lld prefixes", (long long)prefixes);
+    };
+    bool cached = bf16;  // rows of the positions before kept
     const size_t entry = rows_entry_bytes(model->desc.n_layers);
-    BasLevel P = bas_level(W, 0, cached), N = bas_level(W, 1, cached);
+    int at = 0;  // level of the prefixes
+    if (!bas_room(W, at, 1, cap)) return no_memory(1);
+    BasLevel P = bas_level(W, at, false);
     hipLaunchKernelGGL(k_bas_init, dim3(1), dim3(1), 0, st, P, (uint64_t)n_samples);
     const unsigned dg = (unsigned)std::min<uint64_t>((n_samples + 255) / 256, 8192);
     int64_t n = 1;
     for (int s = 0; s < K; s++) {
-        cached = cached && bas_rows(W, s, (size_t)n * entry, cap * entry);
+        const size_t next = std::min((size_t)(4 * n), cap);  // children, at most
+        if (!bas_scratch(W, (size_t)n, cap) || !bas_room(W, at ^ 1, next, cap)) return no_memory((int64_t)next);
+        cached = cached && bas_paths(W, at ^ 1, next) && bas_rows(W, s, (size_t)n * entry, cap * entry);
+        BasLevel N = bas_level(W, at ^ 1, cached);
+        if (!cached) P.path = nullptr;
         nnqs_status r;
         if (cached) {
             RowsArgs A{};
@@ -413,7 +457,6 @@ extern "C" nnqs_status nnqs_bas(nnqs_model *model, int32_t precision, uint64_t s
                            (const uint64_t *)P.offs, n, (const double *)W.cond, P.child);
         const unsigned nb = (unsigned)((n + kBasBlock - 1) / kBasBlock);
         hipLaunchKernelGGL(k_bas_count, dim3(nb), dim3(kBasBlock), 0, st, n, (const unsigned long long *)P.child, W.blk);
-        if (!cached) P.path = N.path = nullptr;
         hipLaunchKernelGGL(k_bas_expand, dim3(nb), dim3(kBasBlock), 0, st, n, (int64_t)cap, K, s, P, N,
                            (const double *)W.cond, (const int64_t *)W.blk, W.total);
         NNQS_HIP_CHECK(hipGetLastError());
@@ -422,7 +465,8 @@ extern "C" nnqs_status nnqs_bas(nnqs_model *model, int32_t precision, uint64_t s
         if (m > (int64_t)cap) return fail(NNQS_ERANGE, "%lld prefixes at position %d exceed the capacity %lld",
                                           (long long)m, s, (long long)capacity);
         if (m < 1) return fail(NNQS_EHIP, "no token is allowed at position %d", s);
-        std::swap(P, N);
+        P = N;
+        at ^= 1;
         n = m;
     }
     NNQS_HIP_CHECK(hipMemcpyAsync(keys_out, P.keys, (size_t)n * 16, hipMemcpyDeviceToDevice, st));
@@ -430,6 +474,7 @@ extern "C" nnqs_status nnqs_bas(nnqs_model *model, int32_t precision, uint64_t s
                        (const double *)P.lp, counts_out, logabs_out);
     NNQS_HIP_CHECK(hipGetLastError());
     if (phase_out) {
+        if (!bf16 && !bas_scratch(W, (size_t)n, cap)) return no_memory(n);
         nnqs_status r = bf16 ? enqueue_phase_bf16(model, keys_out, n, phase_out, st)
                              : enqueue_logpsi(model, keys_out, n, precision, W.la, phase_out, st);
         if (r != NNQS_OK) return r;
