@@ -156,8 +156,8 @@ nnqs_status enqueue_logpsi_f64(const nnqs_model *m, const uint64_t *keys, int64_
                                double *pre = nullptr);
 // FP64 prefix-reusing forward of n listed connections from a sample cache
 // written by enqueue_logpsi_f64's kvc / pre outputs (per sample
-// [L][2][K][64] + [K + 1] doubles); each x' from its first changed position
-// on; see model_f64.hip.
+// f64_cache_doubles and 4 doubles); each x' from the row block of its first
+// changed position on; see transformer_f64.hip.
 int64_t f64_cache_doubles(const nnqs_model *m);
 
 // Ascending bitonic sort of P (a power of two >= 2) 128-bit keys sk[2 i],

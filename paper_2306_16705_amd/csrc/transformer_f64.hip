@@ -31,7 +31,7 @@
 // it), as does the latency of each step's barrier; eight or twelve waves in
 // lockstep per block were 8 and 19 % slower, three blocks per CU (168
 // registers) 2 % slower.  At the 256 registers of two blocks some addresses
-// spill (204 bytes a lane, 244 in list mode).
+// spill (224 bytes a lane, 264 in list mode).
 #include <cmath>
 
 #include "f64_kernels.hpp"
@@ -48,7 +48,7 @@ struct T64Args {
     int64_t n;
     double *logabs;
     const double *packed;  // the layers' weights as k64_pack leaves them
-    double *kv_out;   // sample mode: cache written (may be null): [L][4 heads][K, V][4 blocks][256] per configuration
+    double *kv_out;   // sample mode: cache written (may be null): [L][4 heads][K, V][row blocks][256] per configuration
     double *pre_out;  // prefix sums of log pi over the first 16 b positions, b = 0..3 (with kv_out)
     const double *kv_in;   // list mode
     const double *pre_in;
@@ -277,6 +277,7 @@ __device__ __forceinline__ void transformer_f64(const ModelView &M, const T64Arg
     // rows that reach the result: all, or up to the position whose conditionals are asked for
     const int rows = !kList && A.cond_out ? A.cond_pos + 1 : K;
     const int nb_all = (rows + 15) >> 4;
+    const int64_t kv_head = 2 * nb_all * kKvTile;  // cached K and V of one head and layer (written for whole rows only)
     if (threadIdx.x < 4) S.cnt[threadIdx.x] = kList ? A.hdr[threadIdx.x] : threadIdx.x == 0 ? A.n : 0;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -418,9 +419,9 @@ __device__ __forceinline__ void transformer_f64(const ModelView &M, const T64Arg
                     *reinterpret_cast<f64x4 *>(S.kv[role][0] + 4 * l) = kt;
                     *reinterpret_cast<f64x4 *>(S.kv[role][1] + 4 * l) = v;
                     if (!kList && A.kv_out) {
-                        double *dst = A.kv_out + (((tb + c) * L + layer) * 4 + hh) * (8 * kKvTile) + QB * kKvTile + 4 * l;
+                        double *dst = A.kv_out + (((tb + c) * L + layer) * 4 + hh) * kv_head + QB * kKvTile + 4 * l;
                         *reinterpret_cast<f64x4 *>(dst) = kt;
-                        *reinterpret_cast<f64x4 *>(dst + 4 * kKvTile) = v;
+                        *reinterpret_cast<f64x4 *>(dst + nb_all * kKvTile) = v;
                     }
                 }
                 step_ready();  // also: K and V of every row block written
@@ -433,9 +434,9 @@ __device__ __forceinline__ void transformer_f64(const ModelView &M, const T64Arg
                     for (int i = 0; i < 4; i++) qt[i] = wb[32 * kFrag + 4 * i + lk];
                     project(wb, xn, l, qt, q2);
                     qt += q2;
-                    const double *kvc = kList ? A.kv_in + ((smp * L + layer) * 4 + hh) * (8 * kKvTile) : nullptr;
+                    const double *kvc = kList ? A.kv_in + ((smp * L + layer) * 4 + hh) * kv_head : nullptr;
                     auto kv_tile = [&](int kb, int which) -> f64x4 {
-                        if (kList && kb < b0) return *reinterpret_cast<const f64x4 *>(kvc + (4 * which + kb) * kKvTile + 4 * l);
+                        if (kList && kb < b0) return *reinterpret_cast<const f64x4 *>(kvc + (nb_all * which + kb) * kKvTile + 4 * l);
                         return *reinterpret_cast<const f64x4 *>(S.kv[c * nb + kb - b0][which] + 4 * l);
                     };
                     f64x4 o;
@@ -551,7 +552,9 @@ __global__ void __launch_bounds__(64 * kW64, 2) k64_transformer(ModelView M, T64
 
 __global__ void __launch_bounds__(64 * kW64, 2) k64_transformer_list(ModelView M, T64Args A) { transformer_f64<true>(M, A); }
 
-int64_t f64_cache_doubles(const nnqs_model *m) { return (int64_t)m->desc.n_layers * 4 * 8 * kKvTile; }
+int64_t f64_cache_doubles(const nnqs_model *m) {
+    return (int64_t)m->desc.n_layers * 4 * 2 * ((m->desc.n_orb + 15) / 16) * kKvTile;
+}
 
 static unsigned grid64(int64_t n) {
     int dev = 0, cus = 256;
