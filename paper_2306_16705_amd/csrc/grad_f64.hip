@@ -338,7 +338,7 @@ static size_t grad_carve(const nnqs_model *m, int64_t Bmax, int64_t n, double *b
     size_t at = 0;
     auto take = [&](size_t cnt) {
         double *p = base ? base + at : nullptr;
-        at += cnt;
+        at += (cnt + 3) & ~(size_t)3;  // whole 32-byte loads, as the attention kernels make
         return p;
     };
     S.Hin = take((L + 1) * Rd);
