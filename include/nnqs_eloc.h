@@ -287,8 +287,10 @@ nnqs_status nnqs_bas(nnqs_model *model, int32_t precision, uint64_t seed, uint64
  * part of the ansatz: its entries are zero.  With logabs / phase (device [n],
  * both or neither) the forward values of the same pass are written too.
  * Needs d_model 64, 4 heads, d_ff a multiple of 64 (the FP64 batched
- * forward).  Grows model-owned scratch (about 33 KB per sequence row of a
- * 256-configuration pass); calls on one model must not overlap.
+ * forward).  Grows model-owned scratch (passes of up to 256 configurations; at
+ * four layers and d_ff 256 about 63 KB per sequence row of a pass and a copy of
+ * the gradient per 768 rows: 1.05 GB at 256 configurations of 60 orbitals);
+ * calls on one model must not overlap.
  * Errors: EINVAL, EUNSUPPORTED, ENOMEM, EHIP. */
 nnqs_status nnqs_model_grad(nnqs_model *model, const uint64_t *keys, int64_t n, const double *c_logabs,
                             const double *c_phase, double *grad, double *logabs, double *phase, void *stream);
@@ -450,8 +452,8 @@ typedef struct {
  * only rows from 16 b on, attending to the sample's cached rows before (by
  * causality of the attention and of the autoregressive product of Eq. 8 the
  * rows up to s0 equal the sample's; results are identical to the whole
- * forward of x').  The FP64 refinement runs each refined x' from row s0
- * itself, reading the sample's FP64 keys and values below it.  `stats`
+ * forward of x').  The FP64 refinement runs each refined x' from the same row
+ * on, reading the sample's FP64 keys and values of the blocks before.  `stats`
  * (host, may be NULL) receives the counters; with refinement (or a screen in
  * FP64) or stats the call synchronises `stream` (the refined and selected
  * counts size the following launches), so such a call cannot be captured
@@ -587,14 +589,16 @@ nnqs_status nnqs_eloc_pauli(const nnqs_pauli *pauli, nnqs_table *tab, const uint
                             uint32_t flags, void *stream);
 
 /* ------------------------------------------------------------ batching */
-/* Many systems (uneven N, electron and sample counts) evaluated by one
- * persistent sample-aware launch.  A step of a batch: for every item with a
+/* Many systems (uneven N, electron and sample counts) evaluated together by
+ * the sample-aware method.  A step of a batch: for every item with a
  * model, log|psi| and phase of its samples from the BF16 network (written to
  * the item's logabs / phase); for every item, its table built from the
- * samples; one persistent launch over all (system, sample-tile) work items,
- * pulled by blocks from a device counter; for every item with `energy`, the
- * weighted energy (Eq. 6).  A step neither synchronises the host nor
- * allocates, so it can be captured into a hipGraph and replayed. */
+ * samples; one launch over the samples of the systems whose tables are read
+ * whole (see nnqs_table_set_tune), and one persistent launch over all (system,
+ * sample-tile) work items of the others, pulled by blocks from a device
+ * counter; for every item with `energy`, the weighted energy (Eq. 6).  A step
+ * neither synchronises the host nor allocates, so it can be captured into a
+ * hipGraph and replayed. */
 typedef struct nnqs_batch nnqs_batch;
 
 typedef struct {

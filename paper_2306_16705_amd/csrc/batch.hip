@@ -1,14 +1,16 @@
 // Batched sample-aware local energy over many systems (uneven N and sample
-// counts) in one persistent launch, optionally captured in a hipGraph, with
-// launch schedules chosen by timing (the autotuner below).
+// counts) in two launches, optionally captured in a hipGraph, with launch
+// schedules chosen by timing (the autotuner below).
 //
 // One step of a batch, all on the caller's stream:
 //   1. for each system with a model: log|psi| and phase of its samples from
 //      the BF16 network (Section 3.1 ansatz; the sample-aware method takes the
 //      samples' own amplitudes, Section 3.4 item 4);
 //   2. for each system: the sorted sample table;
-//   3. one persistent k_eloc_sa_batch launch over every (system, sample)
-//      tile: blocks pull tiles from a device counter;
+//   3. one k_eloc_scan_batch launch over the samples of the systems whose
+//      tables are read whole, and one persistent k_eloc_sa_batch launch over
+//      every (system, sample) tile of the others: blocks pull tiles from a
+//      device counter;
 //   4. for each system: the weighted energy of Eq. 6.
 // Nothing in a step synchronises the host or allocates, so the step can be
 // captured into a graph and replayed.
@@ -93,10 +95,10 @@ static nnqs_status batch_plan(nnqs_batch *b) {
             (scans ? scan : tiles).push_back(t);
         }
     }
-    b->ntiles = (int)std::min<size_t>(tiles.size(), INT32_MAX);
-    b->nscan = (int)std::min<size_t>(scan.size(), INT32_MAX);
+    if (tiles.size() + scan.size() > (size_t)INT32_MAX) return fail(NNQS_EINVAL, "too many tiles");
+    b->ntiles = (int)tiles.size();
+    b->nscan = (int)scan.size();
     tiles.insert(tiles.end(), scan.begin(), scan.end());
-    if (tiles.size() > (size_t)INT32_MAX) return fail(NNQS_EINVAL, "too many tiles");
     hipFree(b->d_items);
     hipFree(b->d_tiles);
     b->d_items = nullptr;

@@ -39,9 +39,9 @@ __global__ void k64x_attention_back(const double *__restrict__ q, const double *
 // Causal attention of [B*K][64] rows, one block per (configuration, head).
 __global__ void k64_attention(const double *__restrict__ q, const double *__restrict__ k,
                               const double *__restrict__ v, int K, double scale, double *__restrict__ o);
-// Output head: log-probability of each row's token (and the conditionals of position cpos).
+// Output head: log-probability of each row's token.
 __global__ void k64_head(ModelView M, const double *__restrict__ a, const int8_t *__restrict__ tok, int64_t B,
-                         double *__restrict__ lp, int cpos, double *__restrict__ cond);
+                         double *__restrict__ lp);
 // log|psi| = 1/2 sum of the rows' log-probabilities; phase = b3 + z2 . w3.
 __global__ void k64_finish(ModelView M, const double *__restrict__ lp, const double *__restrict__ z2, int64_t B,
                            double *__restrict__ logabs, double *__restrict__ phase);

@@ -147,7 +147,7 @@ struct TnProblem {
     int64_t R, goff, boff;
     int tile0, splits;  // first block; row splits of each of its tiles
 };
-constexpr int kTnMax = 48;  // 3.5 KB of kernel arguments; four layers in one launch
+constexpr int kTnMax = 48;  // 3.1 KB of kernel arguments; four layers in one launch
 struct TnGroup {
     TnProblem p[kTnMax];
     int n;
@@ -470,8 +470,7 @@ nnqs_status enqueue_model_grad(nnqs_model *m, const uint64_t *keys, int64_t n, c
         ph.C2 = S.Z2;
         gemm64<3, false>(S.Z1, P, W + OF.ph_w2, P, W + OF.ph_b2, B, P, P, S.U2, P, ph, st);
         if (la_out && ph_out) {
-            hipLaunchKernelGGL(k64_head, dim3(nblocks(R, 4)), dim3(256), 0, st, M, S.AF, S.tok, B, S.LP, -1,
-                               (double *)nullptr);
+            hipLaunchKernelGGL(k64_head, dim3(nblocks(R, 4)), dim3(256), 0, st, M, S.AF, S.tok, B, S.LP);
             hipLaunchKernelGGL(k64_finish, dim3(nblocks(B, 4)), dim3(256), 0, st, M, S.LP, S.Z2, B, la_out + b0,
                                ph_out + b0);
         }

@@ -3,11 +3,9 @@
 // kernels of the gradient's forward, which keeps every activation: LayerNorm
 // one wave per row, the dense layers an LDS-tiled FP64 MFMA product (64 x 64
 // output tile per block) with bias, GELU or residual-add epilogues, causal
-// attention on FP64 MFMA one wave per (configuration, head).  Only the
+// attention on FP64 MFMA one block per (configuration, head).  Only the
 // summation order differs from a one-configuration-at-a-time evaluation.
 #include <cmath>
-#include <climits>
-#include <vector>
 
 #include "f64_kernels.hpp"
 
@@ -66,8 +64,8 @@ __global__ void __launch_bounds__(256) k64_layernorm(const double *__restrict__ 
 // during the current slice's products.  Rows of 36 and 80 doubles put the 32
 // lanes of half a wave on 64 different banks for both operands (rows of 33
 // and 65 gave two-way conflicts).
-// EPI 0 stores, 2 stores GELU, 3 stores the sum and, in C2, its
-// GELU, 4 stores the sum times GELU'(U), 5 stores src + the sum.
+// EPI 0 stores, 2 stores GELU, 3 stores GELU' and, in C2, GELU, 4 stores the
+// sum times U (a GELU' of the forward), 5 stores src + the sum.
 
 template <int TM>
 struct GemmLds {
@@ -315,11 +313,8 @@ k64_attention(const double *__restrict__ q, const double *__restrict__ k, const 
 // Output head with the logit bias, the mask (Eq. 12, read with the lower
 // bound too) and the log-probability of the actual token: one wave per
 // (config, position).
-// With `cond`, the masked conditional log-probabilities of all four tokens at
-// position cpos are also written to cond[b][4] (batch sampling).
 __global__ void __launch_bounds__(256) k64_head(ModelView M, const double *__restrict__ a,
-                                                const int8_t *__restrict__ tok, int64_t B, double *__restrict__ lp,
-                                                int cpos, double *__restrict__ cond) {
+                                                const int8_t *__restrict__ tok, int64_t B, double *__restrict__ lp) {
     // lane = model column (d = 64)
     const int K = M.K;
     const int lane = threadIdx.x & 63;
@@ -356,11 +351,7 @@ __global__ void __launch_bounds__(256) k64_head(ModelView M, const double *__res
     for (int t = 0; t < 4; t++)
         if (ok[t]) den += exp(z[t] - mx);
     const int ts = tok[row];
-    const double lden = log(den);
-    lp[row] = ok[ts] ? (z[ts] - mx) - lden : -INFINITY;
-    if (cond && s == cpos)
-#pragma unroll
-        for (int t = 0; t < 4; t++) cond[b * 4 + t] = ok[t] ? (z[t] - mx) - lden : -INFINITY;
+    lp[row] = ok[ts] ? (z[ts] - mx) - log(den) : -INFINITY;
 }
 
 // First phase layer from the occupation bits: z1[b][j] = GELU(b1[j] + sum
@@ -637,8 +628,6 @@ nnqs_status enqueue_f64_list(const nnqs_model *cm, const uint64_t *xkeys, int64_
 }
 
 // Instances used by the gradient (grad_f64.hip).
-template void gemm64<0, false>(const double *, int, const double *, int, const double *, int64_t, int, int, double *, int,
-                               const GemmEpi &, hipStream_t);
 template void gemm64<0, true>(const double *, int, const double *, int, const double *, int64_t, int, int, double *, int,
                               const GemmEpi &, hipStream_t);
 template void gemm64<3, false>(const double *, int, const double *, int, const double *, int64_t, int, int, double *, int,
