@@ -22,8 +22,8 @@
 // Bound: FP64 MFMA (K = 60: 27.8 MFLOP per configuration, 64 of whose rows
 // are run for 60).  Against one kernel per product with the rows in memory
 // between them (about 11 KB of traffic per row and layer), one MI355X, whole
-// calls: log|psi| and phase of 1,001 configurations at K = 60 1,118 -> 682 us;
-// FP64 E_loc of 8 samples at K = 16 (25,544 x') 9,544 -> 4,270 us (678 and 4,271
+// calls: log|psi| and phase of 1,001 configurations at K = 60 1,118 -> 671 us;
+// FP64 E_loc of 8 samples at K = 16 (25,544 x') 9,544 -> 4,215 us (680 and 4,276
 // us with the products summed into the residual, twice the rounding error of
 // log|psi|).  Matrix
 // products alone (no softmax, GELU, LayerNorm or loads) take 70 % of the
@@ -133,10 +133,12 @@ __device__ __forceinline__ void layernorm64(const f64x4 (&h)[4], const double *_
 
 // Steps of a layer: 2 hh and 2 hh + 1 for head hh, then F / 16 of the FFN.
 // Fragments (k4 = 0 .. 15, t = 0 .. 3; element [lk][lr] is row 4 k4 + lk,
-// column lr of a 64 x 16 slice, or of rows and column block t) and vectors:
+// column lr of a 64 x 16 slice, or of rows and column block t) and vectors (the
+// last of each sum with the sum's bias from kSumBias on):
 //  2 hh:     k4: W_k, 16 + k4: W_v of the head's columns; b_k, b_v
-//  2 hh + 1: k4: W_q of the head's columns; 16 + 4 i + t: W_o rows 16 hh + 4 i ..; b_q
-//  8 + u:    k4: W1 of hidden units 16 u ..; 16 + 4 i + t: W2 rows 16 u + 4 i ..; b1
+//  2 hh + 1: k4: W_q of the head's columns; 16 + 4 i + t: W_o rows 16 hh + 4 i ..; b_q, b_o
+//  8 + u:    k4: W1 of hidden units 16 u ..; 16 + 4 i + t: W2 rows 16 u + 4 i ..; b1, b2
+constexpr int kSumBias = 32 * kFrag + 64;
 __host__ __device__ inline int f64_steps(int F) { return 8 + F / 16; }
 
 __global__ void __launch_bounds__(256) k64_pack(ModelView M, double *__restrict__ out) {
@@ -150,7 +152,8 @@ __global__ void __launch_bounds__(256) k64_pack(ModelView M, double *__restrict_
         int64_t src = -1;
         if (e >= 32 * kFrag) {
             const int v = e - 32 * kFrag;
-            if (s >= 8) src = v < 16 ? o.b1 + 16 * (s - 8) + v : -1;
+            if (e >= kSumBias) src = s == 7 ? o.bo + e - kSumBias : s == steps - 1 ? o.b2 + e - kSumBias : -1;
+            else if (s >= 8) src = v < 16 ? o.b1 + 16 * (s - 8) + v : -1;
             else if (s & 1) src = v < 16 ? o.bq + 8 * (s - 1) + v : -1;
             else src = v < 16 ? o.bk + 8 * s + v : v < 32 ? o.bv + 8 * s + v - 16 : -1;
         } else {
@@ -373,10 +376,11 @@ __device__ __forceinline__ void transformer_f64(const ModelView &M, const T64Arg
                     h[e >> 2][e & 3] = 0.0;
                 }
             };
-            auto unpark = [&](const double *__restrict__ bias) {
+            auto unpark = [&] {
+                const double *bias = S.w[buf ^ 1] + kSumBias;  // the step just done, until the next one is ready
 #pragma unroll
                 for (int e = 0; e < 16; e++)
-                    h[e >> 2][e & 3] = (e < kParked ? S.park[w][e][l] : kept[e - kParked]) + (bias[4 * e + lv] + h[e >> 2][e & 3]);
+                    h[e >> 2][e & 3] = (e < kParked ? S.park[w][e][l] : kept[e - kParked]) + (bias[4 * e + lk] + h[e >> 2][e & 3]);
             };
             if (on) {
                 layernorm64(h, Lw + LO.ln1_g, Lw + LO.ln1_b, lv, xn);
@@ -452,7 +456,7 @@ __device__ __forceinline__ void transformer_f64(const ModelView &M, const T64Arg
                 }
             }
             if (on) {
-                unpark(Lw + LO.bo);
+                unpark();
                 layernorm64(h, Lw + LO.ln2_g, Lw + LO.ln2_b, lv, xn);
                 park();
             }
@@ -474,7 +478,7 @@ __device__ __forceinline__ void transformer_f64(const ModelView &M, const T64Arg
                     add_rows(wb, f64x4{g[0], g[1], g[2], g[3]}, l, h);
                 }
             }
-            if (on) unpark(Lw + LO.b2);
+            if (on) unpark();
         }
         // final LayerNorm, head, mask (Eq. 12, read with the lower bound too)
         // and the log-probability of the actual token
