@@ -161,7 +161,9 @@ nnqs_status nnqs_connections(const nnqs_system *sys, const uint64_t *keys, int64
  * count zero the energy's ratios are NaN.  Matrix elements, ratios and sums
  * are FP64; per-sample sums are
  * compensated (Neumaier) and the reduction order is fixed, so repeated
- * calls give bit-identical results.  Calls sharing one table must be ordered
+ * calls give bit-identical results.  The order depends on the path taken (see
+ * nnqs_table_set_tune): the same sample in a call of another size may differ in
+ * its last bits.  Calls sharing one table must be ordered
  * on one stream (the energy reduction uses the table's scratch).
  * Errors: EINVAL, ECONSERVE / ERANGE (VALIDATE), EHIP. */
 nnqs_status nnqs_eloc_table(const nnqs_system *sys, nnqs_table *tab, const uint64_t *keys,
@@ -507,12 +509,11 @@ typedef struct {
 
 /* Sets the launch parameters used by later nnqs_eloc_table calls on `tab`
  * that enumerate the connections of each sample.  A table that is small for
- * the number of connections is read whole for each sample instead,
- * whatever the parameters (the choice depends on the table's size, the number
- * of connections and the number of samples of the call).  The two, and
- * calls of few and many samples on the second, add the same terms in another
- * order: a sample's E_loc may differ in its last bits between calls of
- * different sizes.  NULL restores the defaults.  Errors: EINVAL (out of range). */
+ * the number of connections is read whole for each sample instead, whatever
+ * the parameters (the choice depends on the table's size, the number of
+ * connections and the number of samples of the call).  The two, and calls of
+ * few and of many samples on the second, add the same terms in another order.
+ * NULL restores the defaults.  Errors: EINVAL (out of range). */
 nnqs_status nnqs_table_set_tune(nnqs_table *tab, const nnqs_tune *tune);
 
 /* Reads back the parameters in use. */

@@ -534,7 +534,6 @@ void eloc_model_free(nnqs_model *m) {
     hipFree(m->d_hdr);
     hipFree(m->d_kv64);
     hipFree(m->d_pre64);
-    hipFree(m->d_rag);
     hipFree(m->d_ddk);
     hipFree(m->d_ddi);
     hipFree(m->d_ddhead);
@@ -550,9 +549,7 @@ void eloc_model_free(nnqs_model *m) {
     m->d_repmask = m->d_refmask = nullptr;
     m->ddcap = m->maskcap = 0;
     m->d_kv64 = m->d_pre64 = nullptr;
-    m->d_rag = nullptr;
     m->kv64cap = 0;
-    m->ragcap = 0;
     m->d_kv = nullptr;
     m->d_pre = m->d_csla = nullptr;
     m->d_hdr = nullptr;

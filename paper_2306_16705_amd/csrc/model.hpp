@@ -93,8 +93,6 @@ struct nnqs_model {
     // values of every layer and their prefix log-probability sums
     double *d_kv64 = nullptr, *d_pre64 = nullptr;
     int64_t kv64cap = 0;
-    void *d_rag = nullptr;  // starts, row counts and row offsets of the refined connections
-    size_t ragcap = 0;
     // evaluation of distinct x' (dedup): sort keys / payloads, run heads,
     // best representative per run, representative of every kept connection,
     // the second list, and per-connection masks (representatives, refined runs)
