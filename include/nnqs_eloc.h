@@ -271,12 +271,13 @@ nnqs_status nnqs_model_logpsi(const nnqs_model *model, const uint64_t *keys, int
  * with the prefixes seen: 72 bytes twice (the prefixes and the children they can
  * have, at most `capacity` of each) and 40 of scratch, and in BF16 256 more
  * twice for the paths and 256 n_layers for a prefix's row at every position;
- * arrays are allocated up to twice as long, and rows or paths that would take
- * more than a quarter of the free memory are done without (every position then
- * evaluates whole prefixes).  It stays with the model for the next call, until
- * the model is destroyed, as long as all models of the process together keep no
- * more than 4 GiB.  Errors: EINVAL, ERANGE (more than `capacity` prefixes),
- * ENOMEM, EUNSUPPORTED, EHIP. */
+ * arrays are allocated up to twice as long (at least 2^17 entries, if `capacity`
+ * and n_samples allow as many), and rows or paths that would take more than a
+ * quarter of the free memory are done without (every position then evaluates
+ * whole prefixes).  It stays with the model for the next call, until
+ * the model is destroyed, if it holds no more than 4 GiB and those of all models
+ * of the process no more than 8.  Errors: EINVAL, ERANGE (more than `capacity`
+ * prefixes), ENOMEM, EUNSUPPORTED, EHIP. */
 nnqs_status nnqs_bas(nnqs_model *model, int32_t precision, uint64_t seed, uint64_t n_samples, int64_t capacity,
                      uint64_t *keys_out, uint32_t *counts_out, double *logabs_out, double *phase_out,
                      int64_t *n_unique, void *stream);

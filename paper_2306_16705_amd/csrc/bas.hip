@@ -252,8 +252,9 @@ __global__ void k_bas_init(BasLevel P, uint64_t total) {
 // Workspace of a sampling call: two levels of prefixes, scratch of one level,
 // and for the BF16 network each level's paths and every position's rows, all
 // grown to the number of prefixes seen.  A call takes the model's workspace, or
-// makes one where another call has it, and leaves it with the model as long as
-// all models together hold at most kBasKeep bytes.
+// makes one where another call has it, and leaves it with the model if it holds
+// at most kBasKeep bytes and those of all models at most twice as many (a call
+// that finds none takes 1.3 ms longer at K = 60 and 100,000 samples).
 struct BasWork {
     size_t level_cap[2] = {}, path_cap[2] = {}, scratch_cap = 0, row_bytes[64] = {};
     void *level[2] = {}, *path[2] = {};
@@ -306,7 +307,7 @@ struct BasHold {
         (void)hipStreamSynchronize(st);
         const size_t b = w->bytes();
         size_t kept = g_bas_kept.load();
-        while (!drop && kept + b <= kBasKeep)
+        while (!drop && b <= kBasKeep && kept + b <= 2 * kBasKeep)
             if (g_bas_kept.compare_exchange_weak(kept, kept + b)) {
                 BasWork *none = nullptr;
                 if (m->bas_work.compare_exchange_strong(none, w)) return;
@@ -326,9 +327,10 @@ static bool bas_alloc(void **p, size_t bytes) {
     return false;
 }
 
-// Entries to allocate for `need` of at most `most`: twice as many, so that a
-// call grows its arrays a few times only.
-static size_t bas_want(size_t need, size_t most) { return std::min(std::max(2 * need, (size_t)1 << 16), most); }
+// Entries to allocate for `need` of at most `most`: twice as many and no fewer
+// than 2^17 (45 MB of a level with its paths), so that a call grows its arrays a
+// few times only; each time costs some 0.2 ms.
+static size_t bas_want(size_t need, size_t most) { return std::min(std::max(2 * need, (size_t)1 << 17), most); }
 
 // Room for n prefixes in level i, and for the scratch of a level of n; what was
 // in them is not kept.
