@@ -194,14 +194,15 @@ __global__ void __launch_bounds__(256) k_screen_layer1(int N, int H, const T *__
 // FP32: 85 us with one element per thread, now 15 us (512 blocks, four slices
 // of one memory latency each; the matrix instructions take 3.4 us of it).
 // The blocks past the row tiles of kBack's launch form the partial sums of the
-// output weights' gradient, w3p[ph][c] = sum of gy[k] z2[k][c] over k = ph, ph +
-// 16, ...: 64 columns of one phase each, one wave (a CU takes in few lines at a
-// time, so the sums want many CUs more than full ones).
+// output weights' gradient over all `total` rows (z2 and gy begin at the first),
+// w3p[ph][c] = sum of gy[k] z2[k][c] over k = ph, ph + 16, ...: 64 columns of
+// one phase each, one wave (a CU takes in few lines at a time, so the sums want
+// many CUs more than full ones).
 template <typename T, bool kBack>
 __global__ void __launch_bounds__(256) k_screen_hidden(const T *__restrict__ A, const T *__restrict__ W,
                                                        const T *__restrict__ bias, const T *__restrict__ act, int64_t n,
                                                        int H, T *__restrict__ a2, T *__restrict__ out,
-                                                       const T *__restrict__ z2, const T *__restrict__ gy,
+                                                       const T *__restrict__ z2, const T *__restrict__ gy, int64_t total,
                                                        double *__restrict__ w3p) {
     __shared__ T As[32][68];
     __shared__ T Ws[64][81];
@@ -214,18 +215,18 @@ __global__ void __launch_bounds__(256) k_screen_hidden(const T *__restrict__ A, 
         if (w > 0) return;
         double s = 0.0;
         constexpr int kU = 32;  // loads in flight
-        for (int64_t k0 = ph; k0 < n; k0 += 16 * kU) {
+        for (int64_t k0 = ph; k0 < total; k0 += 16 * kU) {
             T v[kU], g[kU];
 #pragma unroll
             for (int u = 0; u < kU; u++) {
-                const int64_t k = std::min(k0 + 16 * u, n - 1);
+                const int64_t k = std::min(k0 + 16 * u, total - 1);
                 v[u] = z2[k * H + c];
                 g[u] = gy[k];
             }
             __builtin_amdgcn_sched_barrier(0);  // the compiler would wait for each load before the next
 #pragma unroll
             for (int u = 0; u < kU; u++)
-                if (k0 + 16 * u < n) s += (double)(v[u] * g[u]);
+                if (k0 + 16 * u < total) s += (double)(v[u] * g[u]);
         }
         if (c0 + l < H) w3p[ph * H + c0 + l] = s;
         return;
@@ -964,25 +965,29 @@ static nnqs_status screen_fwd_bwd(nnqs_screen *s, const uint64_t *keys, const ui
         hipLaunchKernelGGL(k_convert_f32, dim3(gridfor(o.total)), dim3(256), 0, st, s->w, wc, o.total);
         w = wc;
     }
-    const unsigned rt = gridfor(n, 32), ct = gridfor(H, 64);
-    // a launch holds fewer than 2^32 threads, and these two take 64 and 16 per example
+    const unsigned ct = gridfor(H, 64);
+    // a launch holds fewer than 2^32 threads, and these take up to 64 per example
     constexpr int64_t kMaxRows = (int64_t)1 << 24;
     for (int64_t k0 = 0; k0 < n; k0 += kMaxRows) {
-        const int64_t m = std::min(kMaxRows, n - k0);
+        const int64_t m = std::min(kMaxRows, n - k0), h0 = k0 * H;
+        T *a1k = a1 ? a1 + h0 : nullptr, *a2k = a2 ? a2 + h0 : nullptr;
         hipLaunchKernelGGL(k_screen_layer1<T>, dim3(gridfor(m, 4)), dim3(256), 0, st, N, H, w, keys + 2 * k0, exc + 4 * k0,
-                           m, a1 ? a1 + k0 * H : nullptr, z1 + k0 * H);
-    }
-    hipLaunchKernelGGL((k_screen_hidden<T, false>), dim3(rt, ct), dim3(256), 0, st, (const T *)z1, w + o.W2, w + o.b2,
-                       (const T *)nullptr, n, H, a2, z2, (const T *)nullptr, (const T *)nullptr, (double *)nullptr);
-    for (int64_t k0 = 0; k0 < n; k0 += kMaxRows) {
-        const int64_t m = std::min(kMaxRows, n - k0);
-        hipLaunchKernelGGL(k_screen_out<T>, dim3(gridfor(m, 16)), dim3(256), 0, st, (const T *)(a2 ? a2 + k0 * H : nullptr),
-                           (const T *)(z2 + k0 * H), w, N, H, m, n, grad ? target + k0 : nullptr, y + k0,
-                           pred ? pred + k0 : nullptr, gy + k0, d2 ? d2 + k0 * H : nullptr);
+                           m, a1k, z1 + h0);
+        hipLaunchKernelGGL((k_screen_hidden<T, false>), dim3(gridfor(m, 32), ct), dim3(256), 0, st, (const T *)(z1 + h0),
+                           w + o.W2, w + o.b2, (const T *)nullptr, m, H, a2k, z2 + h0, (const T *)nullptr,
+                           (const T *)nullptr, n, (double *)nullptr);
+        hipLaunchKernelGGL(k_screen_out<T>, dim3(gridfor(m, 16)), dim3(256), 0, st, (const T *)a2k, (const T *)(z2 + h0), w,
+                           N, H, m, n, grad ? target + k0 : nullptr, y + k0, pred ? pred + k0 : nullptr, gy + k0,
+                           d2 ? d2 + h0 : nullptr);
     }
     if (grad) {
-        hipLaunchKernelGGL((k_screen_hidden<T, true>), dim3(rt + 16, ct), dim3(256), 0, st, (const T *)d2, w + o.W2,
-                           (const T *)nullptr, (const T *)a1, n, H, (T *)nullptr, d1, (const T *)z2, (const T *)gy, w3p);
+        for (int64_t k0 = 0; k0 < n; k0 += kMaxRows) {
+            const int64_t m = std::min(kMaxRows, n - k0), h0 = k0 * H;
+            const unsigned sums = k0 + m == n ? 16 : 0;  // the partial sums' blocks, once
+            hipLaunchKernelGGL((k_screen_hidden<T, true>), dim3(gridfor(m, 32) + sums, ct), dim3(256), 0, st,
+                               (const T *)(d2 + h0), w + o.W2, (const T *)nullptr, (const T *)(a1 + h0), m, H,
+                               (T *)nullptr, d1 + h0, (const T *)z2, (const T *)gy, n, w3p);
+        }
         const int jt = (H + 31) / 32, tiles = ((5 * N + 31) / 32 + jt) * jt;
         hipLaunchKernelGGL(k_screen_grads<T>, dim3((unsigned)(2 + tiles)), dim3(256), 0, st, N, H, keys, exc, target, n,
                            (const T *)z1, (const T *)d1, (const T *)d2, (const T *)y, (const T *)gy,

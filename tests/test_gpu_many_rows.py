@@ -1,5 +1,6 @@
 """Calls of more than 2^26 rows, where 64 threads a row no longer fit one
-launch: rows that repeat give results that repeat, bit for bit."""
+launch, and of more than 2^29, where 8 do not: rows that repeat give results
+that repeat, bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -20,8 +21,8 @@ def nn():
     return nn
 
 
-def _repeat(t):
-    return t.repeat((N_ROWS // 36,) + (1,) * (t.dim() - 1))
+def _repeat(t, rows=N_ROWS):
+    return t.repeat((rows // 36,) + (1,) * (t.dim() - 1))
 
 
 def test_samples_of_a_scanned_table(nn):
@@ -36,13 +37,31 @@ def test_samples_of_a_scanned_table(nn):
     assert bool((e.view(-1, 36, 2) == few).all())
 
 
-def test_examples_of_a_screen(nn):
-    print("[case] screen of 2^26 + 32 examples", flush=True)
+@pytest.mark.parametrize("rows", [N_ROWS, 36 * 14913081])  # 2^26 + 32, 2^29 + 4
+def test_examples_of_a_screen(nn, rows):
+    print(f"[case] screen of {rows} examples", flush=True)
     d = synth.config_inputs(1)
     keys = dev(d["keys"])
     exc = torch.randint(0, 9, (36, 4), generator=torch.Generator().manual_seed(3)).to(torch.uint8).cuda()
     scr = nn.Screen(8, 1, np.random.default_rng([16705, 96]).normal(0, 0.3, 5 * 8 + 5))
-    few = scr.forward(keys, exc, nn.NNQS_FP64)
-    y = scr.forward(_repeat(keys), _repeat(exc), nn.NNQS_FP64)
+    prec = nn.NNQS_FP64 if rows == N_ROWS else nn.NNQS_FP32
+    few = scr.forward(keys, exc, prec)
+    y = scr.forward(_repeat(keys, rows), _repeat(exc, rows), prec)
     assert torch.equal(y[:36], few)
-    assert bool((y.view(-1, 36) == few).all())
+    assert all(bool((part.view(-1, 36) == few).all()) for part in y.split(36 << 20))
+
+
+def test_gradient_of_a_screen(nn):
+    """2^24 + 8 examples take two launches of the row kernels; the mean's
+    gradient is that of the 36 they repeat, to the rounding of 1.7e7 additions
+    in a row (1.1e-16 each, 2e-9 if all went one way)."""
+    rows = 36 * 466034
+    print(f"[case] screen gradient of {rows} examples", flush=True)
+    d = synth.config_inputs(1)
+    keys, target = dev(d["keys"]), dev(d["logabs"])
+    exc = torch.randint(0, 9, (36, 4), generator=torch.Generator().manual_seed(3)).to(torch.uint8).cuda()
+    scr = nn.Screen(8, 3, np.random.default_rng([16705, 97]).normal(0, 0.3, 5 * 8 * 3 + 3 + 9 + 3 + 3 + 1))
+    few, l0 = scr.gradient(keys, exc, target, nn.NNQS_FP64)
+    g, l1 = scr.gradient(_repeat(keys, rows), _repeat(exc, rows), _repeat(target, rows), nn.NNQS_FP64)
+    assert float((g - few).abs().max()) <= 2e-9 * float(few.abs().max())
+    assert abs(float(l1) - float(l0)) <= 2e-9 * float(l0)
