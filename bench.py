@@ -45,8 +45,8 @@ SA_OPS_PER_CONNECTION = 11
 # on this workload: VALU wave instructions per connection (SQ_INSTS_VALU /
 # connections) and FETCH_SIZE / WRITE_SIZE in KiB per launch with the
 # copy-calibrated scales.  Valid only for the kernel sources hashed below.
-SA_COUNTERS = {"sources_sha256_16": "a908410fa3c4d92a", "valu_per_connection": 0.5720,
-               "fetch_kib": 56840.2, "write_kib": 4052.2, "fetch_scale": 262144.0 / 131093.0,
+SA_COUNTERS = {"sources_sha256_16": "e99b0c14b8cb5aca", "valu_per_connection": 0.5720,
+               "fetch_kib": 56974.9, "write_kib": 4051.8, "fetch_scale": 262144.0 / 131093.0,
                "write_scale": 1.0}
 SA_SOURCES = ("paper_2306_16705_amd/csrc/eloc_sa.hip", "paper_2306_16705_amd/csrc/enumerate.hpp",
               "paper_2306_16705_amd/csrc/internal.hpp")

@@ -787,18 +787,23 @@ static bool scan_splits(int64_t table_n, int64_t n, int cus) { return n <= 8 * (
 //    C = 4,236, 12,000: 168, 193.)
 //  * Enumeration also takes 30 us to stage its filter and for its second pass,
 //    whatever n is (a single call pays it, a batch shares it), in which a scan
-//    that fills the chip reads 3e7 members and one of up to 2,048 samples, on
-//    its waits for memory, half of that.
-//  * Below a sample per CU neither gets shorter with fewer samples: n = 1, C =
-//    3,193, 100,000 members: 40, 38; a million: 173, 460.  C = 1,425, 256
-//    samples, 16,000: 53, 24; 100,000: 92, 71; C = 703, 2,048 samples, 12,000:
-//    58, 57; C = 1,425, 2,048 samples, 100,000: 97, 180.
+//    that fills the chip reads 3e7 members.
+//  * Up to 2,048 samples, a scan shared by the block's waves takes 0.43 ns a member
+//    up to a sample per CU and 1.1 at 2,048, and enumeration's one round per sample
+//    as long as its C connections take one wave block: 2 ns each while the filter
+//    is sparse and up to 90 once it is so full (three bits of 2^20 or, with two
+//    words, 2^19 a member) that most of them go on to the search.  n = 256: C =
+//    3,193, 100,000 members: 100, 74; a million: 365, 436.  C = 16,471, 200,000:
+//    202, 59; a million: 1,231, 408.  C = 93,825, 500,000: 6,546, 215.  n = 1: C =
+//    1,425, 100,000: 66, 61; C = 756,147, 1.5 million: 40,283, 635.  n = 2,048: C =
+//    703, 12,000: 58, 57; C = 1,425, 100,000: 97, 180; C = 16,471, 48,000: 177,
+//    117; 200,000: 204, 200; C = 3,193, a million: 390, 1,223.
 bool sa_scans(const SysView &S, int64_t table_n, int64_t n, int cus, bool batched) {
-    const double per_sample = 1.8 * (double)S.C + 5000.0;
-    const double start = batched ? 0.0
-                         : scan_splits(table_n, n, cus) ? 1.4e7 / (double)std::max<int64_t>(n, cus)
-                                                        : 3.0e7 / (double)std::max<int64_t>(n, 6000);
-    return (double)table_n <= per_sample + start;
+    const double C = (double)S.C, t = (double)table_n;
+    if (batched) return t <= 1.8 * C + 5000.0;
+    if (!scan_splits(table_n, n, cus)) return t <= 1.8 * C + 5000.0 + 3.0e7 / (double)std::max<int64_t>(n, 6000);
+    const double bit = 1.0 - exp(-3.0 * t / (double)(1 << (S.N > 64 ? kMaxFilterLog2 - 1 : kMaxFilterLog2)));
+    return t <= (3.0 + 100.0 * bit * bit * bit) * C + 5000.0 + 2.3e7 / (double)std::max<int64_t>(n, cus);
 }
 
 void sa_launch_scan(int W, int cus, hipStream_t st, const SysView &S, const TableView &T, const uint64_t *keys,

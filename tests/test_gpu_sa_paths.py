@@ -2,7 +2,10 @@
 library's timing records, and the result of either against the oracle.
 
 Few samples against a table that is large for their number of connections are
-enumerated: a scan is spread over no more than four waves per sample."""
+enumerated: a scan is spread over no more than four waves per sample.  With many
+connections and a table that fills the filter they are scanned all the same."""
+import functools
+
 import numpy as np
 import pytest
 import torch
@@ -43,24 +46,42 @@ def sector():
     return d
 
 
-@pytest.mark.parametrize("members,n,scans", [(1, 1, True), (40000, 1, True), (40000, 256, True), (100000, 1, False),
-                                             (240000, 3, False), (100000, 256, False), (12000, 2048, True),
-                                             (20000, 2048, False), (60000, 2048, False), (7000, 2049, True),
-                                             (7000, 20000, True), (14000, 2049, False), (20000, 14000, False)])
-def test_the_rule(nn, sector, members, n, scans):
-    print(f"[case] path of {n} samples, {members} members", flush=True)
-    d = sector
-    S = nn.System(d["N"], 4, 4, d["h"], d["g"], d["e_core"])
+def _check_path(nn, d, members, n, scans, checked):
+    K, nu, nd = d["K"], d["n_up"], d["n_dn"]
+    S = nn.System(d["N"], nu, nd, d["h"], d["g"], d["e_core"])
     T = nn.Table(S, members)
     keys, la, ph = d["keys"], d["logabs"], d["phase"]
     T.build(dev(keys[:members]), dev(la[:members]), dev(ph[:members]))
     (e, _), got = launches(nn, ("k_eloc_scan", "k_eloc_sa"), lambda: nn.eloc_table(
         S, T, dev(keys[:n]), None, dev(la[:n]), dev(ph[:n]), with_energy=False))
     assert got == ([1, 0] if scans else [0, 1])
-    chk = np.linspace(0, n - 1, min(n, 100)).astype(np.int64)
-    ora, absum = oracle.eloc_table(12, 4, 4, d["h"], d["g"], d["e_core"], keys[:members], la[:members], ph[:members],
+    chk = np.linspace(0, n - 1, min(n, checked)).astype(np.int64)
+    ora, absum = oracle.eloc_table(K, nu, nd, d["h"], d["g"], d["e_core"], keys[:members], la[:members], ph[:members],
                                    keys[chk], la[chk], ph[chk], with_absum=True)
     assert_eloc_close(eloc_complex(e)[chk], ora, absum, label=f"{n} of {members}")
+
+
+@pytest.mark.parametrize("members,n,scans", [(1, 1, True), (40000, 1, True), (40000, 256, True), (150000, 1, False),
+                                             (240000, 3, False), (150000, 256, False), (12000, 2048, True),
+                                             (24000, 2048, False), (60000, 2048, False), (7000, 2049, True),
+                                             (7000, 20000, True), (14000, 2049, False), (20000, 14000, False)])
+def test_the_rule(nn, sector, members, n, scans):
+    print(f"[case] path of {n} samples, {members} members", flush=True)
+    _check_path(nn, sector, members, n, scans, 100)
+
+
+@functools.lru_cache(maxsize=1)
+def _inputs(K, nu, nd, members):
+    return synth.config_inputs(2, K=K, n_up=nu, n_dn=nd, n_unique=members)
+
+
+@pytest.mark.parametrize("K,nu,nd,members,n,scans", [(24, 6, 6, 120000, 1, True), (24, 6, 6, 120000, 300, True),
+                                                     (24, 6, 6, 120000, 2049, False), (36, 4, 4, 100000, 1, True),
+                                                     (36, 4, 4, 100000, 2048, True), (36, 4, 4, 100000, 2049, False)])
+def test_many_connections(nn, K, nu, nd, members, n, scans):
+    d = _inputs(K, nu, nd, members)
+    print(f"[case] path of K={K}, {n} samples, {members} members", flush=True)
+    _check_path(nn, d, members, n, scans, 20)
 
 
 def test_autotuners_keep_a_schedule_that_changes_nothing(nn):
